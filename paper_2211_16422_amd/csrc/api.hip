@@ -524,8 +524,11 @@ homs_status homs_encode_library(homs_ctx* c, int64_t n, const int64_t* d_offsets
     if (e == hipSuccess) e = homs::dev_malloc(&L.charge, (size_t)n);
     // the MFMA epilogue reads library indices in groups past the last row
     const size_t orig_pad = (size_t)homs::search_mfma_row_pad();
-    if (e == hipSuccess) e = homs::dev_malloc(&L.orig, ((size_t)n + orig_pad) * 4);
-    if (e == hipSuccess) e = hipMemsetAsync(L.orig + n, 0, orig_pad * 4, s);
+    if (e == hipSuccess) e = homs::dev_malloc(&L.orig, ((size_t)n + orig_pad + 257) * 4);
+    if (e == hipSuccess) {
+        L.charge_first = L.orig + n + orig_pad;
+        e = hipMemsetAsync(L.orig + n, 0, orig_pad * 4, s);
+    }
     if (e == hipSuccess) e = homs::dev_malloc(&L.slot, (size_t)n * 4);
     if (e == hipSuccess) e = homs::dev_malloc(&L.rowk, ((size_t)n + orig_pad) * 4);
     if (e == hipSuccess) e = homs::dev_malloc(&tmp, tmp_bytes);
@@ -534,6 +537,7 @@ homs_status homs_encode_library(homs_ctx* c, int64_t n, const int64_t* d_offsets
     if (e == hipSuccess)
         e = homs::launch_library_sort(n, d_pmz, d_charge, c->p.charge_match != 0, tmp, tmp_bytes,
                                       L.orig, L.pmz, L.charge, L.slot, s);
+    if (e == hipSuccess) e = homs::launch_charge_first(n, L.charge, L.charge_first, s);
     hipEvent_t e1 = e == hipSuccess ? prof_mark(c, s) : nullptr;
     if (e == hipSuccess) e = homs::launch_encode(c, n, d_offsets, d_bin, d_level, L.slot, L.hv, s);
     hipEvent_t e2 = e == hipSuccess ? prof_mark(c, s) : nullptr;
@@ -620,40 +624,35 @@ bool engine_valid(int32_t engine)
            engine == HOMS_ENGINE_MFMA_F8 || engine == HOMS_ENGINE_MFMA_F4;
 }
 
-int engine_tile(int32_t engine)
+int engine_tile(const homs_ctx* c, int32_t engine, int64_t nq)
 {
     return engine == HOMS_ENGINE_POPCOUNT ? homs::search_popcount_tile()
-                                          : homs::search_mfma_tile();
+                                          : homs::search_mfma_tile(c, nq);
 }
 
 // The search of homs_search_window on validated arguments. The workspace must
-// already hold search_scratch_bytes(nq, engine_tile(engine)) bytes; callers
+// already hold homs::query_plan_bytes(nq, engine_tile(c, engine, nq)) bytes; callers
 // may keep their own buffers after that region.
 homs_status run_search(homs_ctx* c, int64_t nq, const uint32_t* d_q_hv, const double* d_q_pmz,
                        const int8_t* d_q_charge, const homs_window* win, int32_t engine,
                        int64_t* d_out_idx, int32_t* d_out_dist, hipStream_t s,
                        void* scratch_base = nullptr, bool profile = true)
 {
-    const int tile = engine_tile(engine);
-    SearchScratch w = carve(scratch_base ? scratch_base : c->ws.ptr, nq, tile);
+    const int tile = engine_tile(c, engine, nq);
+    const homs::QueryPlan w =
+        homs::query_plan_carve(scratch_base ? scratch_base : c->ws.ptr, nq, tile);
     // without profiling no event is created or recorded
     auto mark = [&]() -> hipEvent_t { return profile ? prof_mark(c, s) : nullptr; };
 
     hipEvent_t e0 = mark();
-    HIP_TRY(c, homs::launch_window_bounds(c, nq, d_q_pmz, d_q_charge, win->kind, win->value,
-                                          nullptr, nullptr, w.lo, w.hi, s),
-            "window kernel");
-    uint32_t* qperm = nullptr;
-    HIP_TRY(c, homs::launch_query_sort(nq, d_q_pmz, d_q_charge, c->p.charge_match != 0, w.sort_tmp,
-                                       w.sort_bytes, w.qk_a, w.qk_b, w.qp_a, w.qp_b, &qperm, s),
-            "query sort");
-    HIP_TRY(c, homs::launch_tile_bounds(nq, qperm, w.lo, w.hi, tile, w.tile_lo, w.tile_hi, s),
-            "tile bounds kernel");
-    HIP_TRY(c, homs::launch_init_keys(nq, w.keys, s), "init keys kernel");
+    HIP_TRY(c, homs::launch_query_plan(c, nq, d_q_pmz, d_q_charge, win->kind, win->value,
+                                       engine == HOMS_ENGINE_MFMA_F4 ? d_q_hv : nullptr, tile, w,
+                                       s),
+            "query plan kernels");
     homs::TilePlan plan;
     hipEvent_t e1 = mark();
     if (engine == HOMS_ENGINE_POPCOUNT)
-        HIP_TRY(c, homs::launch_search_popcount(c, nq, d_q_hv, qperm, w.lo, w.hi, w.tile_lo,
+        HIP_TRY(c, homs::launch_search_popcount(c, nq, d_q_hv, w.qperm, w.lo, w.hi, w.tile_lo,
                                                 w.tile_hi, plan, w.keys, s),
                 "search kernel");
     else
@@ -661,7 +660,8 @@ homs_status run_search(homs_ctx* c, int64_t nq, const uint32_t* d_q_hv, const do
                                                : engine == HOMS_ENGINE_MFMA_F8 ? 1
                                                                                : 2,
                                             nq, d_q_hv,
-                                            qperm, w.lo, w.hi, w.tile_lo, w.tile_hi, w.qoff, w.keys,
+                                            w.qperm, w.lo, w.hi, w.tile_lo, w.tile_hi, w.qoff,
+                                            w.keys,
                                             s),
                 "MFMA search kernel");
     hipEvent_t e2 = mark();
@@ -694,7 +694,7 @@ homs_status homs_search_window(homs_ctx* c, int64_t nq, const uint32_t* d_q_hv,
     if (!aligned16(d_q_hv)) return fail(c, HOMS_E_INVALID, "d_q_hv must be 16-byte aligned");
     DeviceGuard g(c->device);
     hipStream_t s = (hipStream_t)stream;
-    if (homs_status st = ensure_workspace(c, search_scratch_bytes(nq, engine_tile(engine)), s))
+    if (homs_status st = ensure_workspace(c, homs::query_plan_bytes(nq, engine_tile(c, engine, nq)), s))
         return st;
     return run_search(c, nq, d_q_hv, d_q_pmz, d_q_charge, win, engine, d_out_idx, d_out_dist, s);
 }
@@ -713,7 +713,7 @@ homs_status homs_search_window_noalloc(homs_ctx* c, int64_t nq, const uint32_t* 
         return fail(c, HOMS_E_INVALID,
                     "nq out of range for homs_search_window_noalloc (at most " +
                         std::to_string(HOMS_NOALLOC_MAX_QUERIES) + " queries)");
-    if (search_scratch_bytes(nq, engine_tile(engine)) > kNoAllocScratchBytes)
+    if (homs::query_plan_bytes(nq, engine_tile(c, engine, nq)) > kNoAllocScratchBytes)
         return fail(c, HOMS_E_INVALID, "nq needs more than the static scratch holds");
     if (nq == 0) return HOMS_OK;
     if (!d_q_hv || !d_q_pmz || !d_q_charge || !d_out_idx || !d_out_dist)
@@ -772,7 +772,7 @@ homs_status homs_cascade_search(homs_ctx* c, int64_t nq, const uint32_t* d_q_hv,
     DeviceGuard g(c->device);
     hipStream_t s = (hipStream_t)stream;
     const uint32_t dim = c->words * 32;
-    const size_t search_bytes = search_scratch_bytes(nq, engine_tile(engine));
+    const size_t search_bytes = homs::query_plan_bytes(nq, engine_tile(c, engine, nq));
     const size_t off = (search_bytes + 255) & ~(size_t)255;
     if (homs_status st = ensure_workspace(c, off + homs::cascade_scratch_bytes(nq, dim), s))
         return st;
@@ -1688,13 +1688,15 @@ homs_status homs_library_load(homs_ctx* c, const char* path)
         e = homs::dev_malloc(&L.hv, (size_t)n * c->words * 4);
         if (e == hipSuccess) e = homs::dev_malloc(&L.pmz, (size_t)n * 8);
         if (e == hipSuccess) e = homs::dev_malloc(&L.charge, (size_t)n);
-        if (e == hipSuccess) e = homs::dev_malloc(&L.orig, ((size_t)n + orig_pad) * 4);
+        if (e == hipSuccess) e = homs::dev_malloc(&L.orig, ((size_t)n + orig_pad + 257) * 4);
         if (e == hipSuccess) e = homs::dev_malloc(&L.slot, (size_t)n * 4);
         if (e == hipSuccess) e = homs::dev_malloc(&L.rowk, ((size_t)n + orig_pad) * 4);
         if (e == hipSuccess) e = hipMemcpy(L.orig, orig.data(), (size_t)n * 4, hipMemcpyHostToDevice);
         if (e == hipSuccess) e = hipMemset(L.orig + n, 0, orig_pad * 4);
         if (e == hipSuccess) e = hipMemcpy(L.pmz, pmz.data(), (size_t)n * 8, hipMemcpyHostToDevice);
         if (e == hipSuccess) e = hipMemcpy(L.charge, charge.data(), (size_t)n, hipMemcpyHostToDevice);
+        L.charge_first = L.orig + n + orig_pad;
+        if (e == hipSuccess) e = homs::launch_charge_first(n, L.charge, L.charge_first, nullptr);
         if (e == hipSuccess) e = homs::launch_slots(n, L.orig, L.slot, nullptr);
         if (e == hipSuccess) e = hipDeviceSynchronize();
     }

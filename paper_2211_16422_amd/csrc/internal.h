@@ -21,7 +21,9 @@ struct Library {
     uint32_t* hv = nullptr;      // [n][W] rows in sorted order
     double* pmz = nullptr;       // [n] sorted precursor m/z
     int8_t* charge = nullptr;    // [n] sorted charge (all 0 when charge is ignored)
-    uint32_t* orig = nullptr;    // [n] library index of each sorted row
+    uint32_t* orig = nullptr;    // [n + pad] library index of each sorted row
+    uint32_t* charge_first = nullptr;  // [257] first row of charge i - 128 or above (in orig's
+                                       // allocation)
     uint32_t* slot = nullptr;    // [n] sorted row of each library index
     float* rowk = nullptr;       // [n + pad] the fp4 search's per-row constant K
 };
@@ -126,6 +128,8 @@ hipError_t launch_library_sort(int64_t n, const double* pmz, const int8_t* charg
                                uint32_t* slot_out, hipStream_t s);
 hipError_t launch_gather_rows(int64_t n, uint32_t words, const uint32_t* src,
                               const uint32_t* orig, uint32_t* dst, hipStream_t s);
+// first[257]: the charges' runs in the sorted library
+hipError_t launch_charge_first(int64_t n, const int8_t* charge, uint32_t* first, hipStream_t s);
 // slot[orig[j]] = j; orig must be a permutation of [0, n)
 hipError_t launch_slots(int64_t n, const uint32_t* orig, uint32_t* slot, hipStream_t s);
 hipError_t launch_window_bounds(const homs_ctx* c, int64_t nq, const double* q_pmz,
@@ -144,6 +148,28 @@ hipError_t launch_debug_distances(const homs_ctx* c, int64_t nq, const uint32_t*
                                   const int64_t* lo, const int64_t* hi,
                                   const int64_t* row_off, int64_t* out_idx, int32_t* out_dist,
                                   hipStream_t s);
+
+// query_plan.hip: windows, query order and tiles of a one-shot search
+struct QueryPlan {
+    int64_t* lo;         // [nq] candidate windows
+    int64_t* hi;
+    uint64_t* keys;      // [nq] results so far (set to "none")
+    uint32_t* qperm;     // [nq] queries in window order
+    int32_t* qoff;       // [nq] the fp4 form's per-query constants
+    uint32_t* bucket;    // [nq] order in the making
+    uint32_t* place;
+    int64_t* tile_lo;    // per tile: the union of its windows (0, 0: empty),
+    int64_t* tile_hi;
+    int64_t* tile_sum;   // the sum of their sizes
+    int64_t* tile_max;   // and the largest
+    uint32_t* hist;
+};
+size_t query_plan_bytes(int64_t nq, int tile);
+QueryPlan query_plan_carve(void* base, int64_t nq, int tile);
+// q_hv: query rows when the fp4 constants are wanted, else NULL
+hipError_t launch_query_plan(const homs_ctx* c, int64_t nq, const double* q_pmz,
+                             const int8_t* q_charge, int32_t kind, double value,
+                             const uint32_t* q_hv, int tile, const QueryPlan& w, hipStream_t s);
 
 // search_popc.hip
 struct TilePlan {
@@ -169,12 +195,12 @@ hipError_t launch_search_batched(const homs_ctx* c, const BatchedConfig& cfg, vo
                                  hipStream_t s);
 
 // search_mfma.hip (fmt 0: int8, 1: fp8 e4m3, 2: fp4 e2m1)
-int search_mfma_tile();
+int search_mfma_tile(const homs_ctx* c, int64_t nq);  // queries per tile, by the call's size
 int64_t search_mfma_row_pad();  // rows of padding the library's orig array needs
-// qoff: workspace of nq int32 (the fp4 form's per-query constants)
+// qoff: the fp4 form's per-query constants (unused by the others)
 hipError_t launch_search_mfma(const homs_ctx* c, int fmt, int64_t nq, const uint32_t* q_hv,
                               const uint32_t* qperm, const int64_t* lo, const int64_t* hi,
-                              const int64_t* tile_lo, const int64_t* tile_hi, int32_t* qoff,
+                              const int64_t* tile_lo, const int64_t* tile_hi, const int32_t* qoff,
                               uint64_t* keys, hipStream_t s);
 // the fp4 form's per-row constants K of n rows of hv, then search_mfma_row_pad() zeros
 hipError_t launch_fp4_row_consts(int64_t n, uint32_t words, const uint32_t* hv, float* rowk,

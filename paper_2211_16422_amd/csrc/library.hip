@@ -9,6 +9,7 @@
 // different workgroups merge with one 64-bit atomicMin. The sorts are the
 // stable radix sort of sort_scan.hip.
 #include "internal.h"
+#include "window_search.h"
 
 namespace homs {
 namespace {
@@ -59,6 +60,23 @@ __global__ void scatter_sorted_kernel(int64_t n, const uint32_t* __restrict__ pe
     slot[i] = (uint32_t)j;
 }
 
+// first[i] = first sorted row of charge i - 128 or above (257 entries)
+__global__ void charge_first_kernel(int64_t n, const int8_t* __restrict__ charge,
+                                    uint32_t* __restrict__ first)
+{
+    const int i = (int)(blockIdx.x * blockDim.x + threadIdx.x);
+    if (i > 256) return;
+    int64_t lo = 0, hi = n;
+    while (lo < hi) {
+        const int64_t mid = lo + ((hi - lo) >> 1);
+        if ((int)charge[mid] < i - 128)
+            lo = mid + 1;
+        else
+            hi = mid;
+    }
+    first[i] = (uint32_t)lo;
+}
+
 __global__ void slot_kernel(int64_t n, const uint32_t* __restrict__ orig, uint32_t* __restrict__ slot)
 {
     const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -75,33 +93,11 @@ __global__ void gather_rows_kernel(int64_t n, uint32_t w4, const uint4* __restri
     dst[(size_t)orig[j] * w4 + w] = src[(size_t)j * w4 + w];
 }
 
-// first j in [0, n) with (ch[j], pmz[j]) >= (c, x) (strict: > when `upper`)
-__device__ __forceinline__ int64_t lex_bound(const int8_t* __restrict__ ch,
-                                             const double* __restrict__ pmz, int64_t n, int8_t c,
-                                             double x, bool upper)
-{
-    int64_t lo = 0, hi = n;
-    while (lo < hi) {
-        const int64_t mid = lo + ((hi - lo) >> 1);
-        const int8_t cm = ch[mid];
-        bool before;  // row mid precedes the bound
-        if (cm != c)
-            before = cm < c;
-        else
-            before = upper ? (pmz[mid] <= x) : (pmz[mid] < x);
-        if (before)
-            lo = mid + 1;
-        else
-            hi = mid;
-    }
-    return lo;
-}
-
 __global__ void window_kernel(int64_t nq, const double* __restrict__ q_pmz,
                               const int8_t* __restrict__ q_charge, bool use_charge, int32_t kind,
                               double value, const int8_t* __restrict__ kinds,
                               const double* __restrict__ values, const double* __restrict__ lib_pmz,
-                              const int8_t* __restrict__ lib_charge, int64_t nlib,
+                              const uint32_t* __restrict__ charge_first,
                               int64_t* __restrict__ lo_out, int64_t* __restrict__ hi_out)
 {
     const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -109,14 +105,11 @@ __global__ void window_kernel(int64_t nq, const double* __restrict__ q_pmz,
     const double pmz = q_pmz[q];
     const int32_t k = kinds ? (int32_t)kinds[q] : kind;
     const double v = values ? values[q] : value;
-    // tolerance in Da, or ppm of the precursor m/z: (pmz * v) / 1e6
-    const double tol = (k == HOMS_TOL_DA) ? v : __ddiv_rn(__dmul_rn(pmz, v), 1.0e6);
-    const double lo_b = __dsub_rn(pmz, tol);
-    const double hi_b = __dadd_rn(pmz, tol);
+    const double tol = tolerance_da(pmz, k, v);
     const int8_t c = use_charge ? q_charge[q] : (int8_t)0;
-    const int64_t lo = lex_bound(lib_charge, lib_pmz, nlib, c, lo_b, false);
-    int64_t hi = lex_bound(lib_charge, lib_pmz, nlib, c, hi_b, true);
-    if (hi < lo) hi = lo;  // NaN precursor or negative tolerance: empty
+    int64_t r_lo, r_hi, lo, hi;
+    charge_run(charge_first, c, &r_lo, &r_hi);
+    window_bounds(lib_pmz, r_lo, r_hi, __dsub_rn(pmz, tol), __dadd_rn(pmz, tol), &lo, &hi);
     lo_out[q] = lo;
     hi_out[q] = hi;
 }
@@ -221,6 +214,12 @@ hipError_t launch_library_sort(int64_t n, const double* pmz, const int8_t* charg
     return hipGetLastError();
 }
 
+hipError_t launch_charge_first(int64_t n, const int8_t* charge, uint32_t* first, hipStream_t s)
+{
+    charge_first_kernel<<<5, 64, 0, s>>>(n, charge, first);
+    return hipGetLastError();
+}
+
 hipError_t launch_slots(int64_t n, const uint32_t* orig, uint32_t* slot, hipStream_t s)
 {
     if (n <= 0) return hipSuccess;
@@ -246,7 +245,7 @@ hipError_t launch_window_bounds(const homs_ctx* c, int64_t nq, const double* q_p
     if (nq <= 0) return hipSuccess;
     window_kernel<<<blocks_for(nq), kThreads, 0, s>>>(
         nq, q_pmz, q_charge, c->p.charge_match != 0, kind, value, kinds, values, c->lib.pmz,
-        c->lib.charge, c->lib.n, lo, hi);
+        c->lib.charge_first, lo, hi);
     return hipGetLastError();
 }
 

@@ -12,7 +12,7 @@ constexpr int kTile = 256;        // queries per workgroup (4 waves)
 constexpr int kRefs = 32;         // reference rows per accumulator block
 constexpr int kWords = 16;        // words per slice (one s_load_dwordx16 per row)
 constexpr int kGroup = 2;         // rows per scalar prefetch group
-constexpr int64_t kChunk = 2048;  // reference rows per workgroup
+constexpr int64_t kChunk = 2048;  // most reference rows per workgroup
 
 typedef __attribute__((address_space(4))) const uint32_t const_u32;
 
@@ -57,6 +57,7 @@ __device__ __forceinline__ void popcount_tile_rows(
     uint64_t* __restrict__ keys)
 {
     const int64_t qs = tile * kTile + threadIdx.x;  // position in sorted order
+    if (qs - (threadIdx.x & 63) >= nq) return;      // no query in this wave
     const bool valid = qs < nq;
     const uint32_t qi = valid ? qperm[qs] : 0u;
     uint32_t q_lo = 0, q_hi = 0;
@@ -72,6 +73,14 @@ __device__ __forceinline__ void popcount_tile_rows(
         uint32_t acc[kRefs];
 #pragma unroll
         for (int r = 0; r < kRefs; ++r) acc[r] = 0u;
+
+        // the next block's rows on their way into L2 (one word of each
+        // 128-byte line), so that the scalar loads find them there
+        uint32_t ahead = 0;
+        if (rb + kRefs < b)
+            for (uint32_t i = threadIdx.x; i < words; i += kTile)
+                ahead ^= lib_hv[(size_t)min(rb + kRefs + i / (words / 32), b - 1u) * words +
+                                i % (words / 32) * 32];
 
         // rows past the chunk end re-read its last row; they are masked below
         Slice cur[kGroup];
@@ -114,6 +123,7 @@ __device__ __forceinline__ void popcount_tile_rows(
             }
         }
         __builtin_amdgcn_s_waitcnt(kWaitScalar);
+        asm volatile("" ::"v"(ahead));
 
 #pragma unroll
         for (int r = 0; r < kRefs; ++r) {

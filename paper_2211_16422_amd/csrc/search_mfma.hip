@@ -8,6 +8,9 @@
 // in fp32 (int8 works on +-64 components: 4096 times the same integers), so
 // every engine reproduces the popcount distances bit for bit.
 //
+// Two kernels: mfma_direct_kernel for calls of thousands of queries and
+// mfma_stream_kernel, below it, for fewer. What follows is the first.
+//
 // Work decomposition (every engine): a workgroup takes one tile of 256
 // m/z-ordered queries and one chunk of its candidate rows, in blocks of 256
 // library rows (the M dimension). Eight waves form a 2 x 4 grid; each owns a
@@ -27,8 +30,11 @@
 // folded into a per-lane 64-bit running minimum of (distance << 32 | library
 // index); lanes l and l+32 hold the same query columns and are merged with a
 // shuffle before one atomicMin per query.
+#include <algorithm>
+
 #include "internal.h"
 #include "mfma_direct.h"
+#include "window_search.h"
 
 namespace homs {
 namespace {
@@ -36,54 +42,309 @@ namespace {
 // XCD-aware work map of the direct kernels. Workgroups are handed
 // to the eight XCDs in turn (workgroup i to XCD i mod 8), and each XCD has its
 // own L2. Work items are (query tile, library chunk) pairs on absolute chunk
-// boundaries; they are grouped into patches of 4 adjacent tiles x 8 adjacent
-// chunks, and consecutive patches go to consecutive XCDs, so the 32
-// workgroups an XCD runs side by side share 8 chunks of library rows and 4
-// tiles of query rows (about 3 MB per 256-row step) in their L2.
-constexpr int kXcds = 8, kPatchTiles = 4, kPatchChunks = 8;
-constexpr int kPatch = kPatchTiles * kPatchChunks;
+// boundaries; they are grouped into patches of adjacent tiles x adjacent
+// chunks (4 x 8 where there are that many), and consecutive patches go to
+// consecutive XCDs, so the 32 workgroups an XCD runs side by side share 8
+// chunks of library rows and 4 tiles of query rows (about 3 MB per 256-row
+// step) in their L2.
+constexpr int kXcds = 8;
+struct WorkMap {
+  uint32_t n_tiles, n_chunks, chunk;          // chunk: library rows per item
+  uint32_t patch_tiles, patch_chunks;         // items of a patch
+  uint32_t chunk_patches, patches;            // patches along the library, in all
+};
 
 // wave layout of the one-shot kernels
 using DirectLayout = mfd::Layout8;
 
 template <int F>
-__global__ __launch_bounds__(DirectLayout::kThreads, 1) void mfma_direct_kernel(uint32_t words,
+__global__ __launch_bounds__(DirectLayout::kThreads, 1) void mfma_direct_kernel(
+    uint32_t words,
     int64_t nq,
     const uint32_t* __restrict__ q_hv, const uint32_t* __restrict__ qperm,
     const int64_t* __restrict__ lo, const int64_t* __restrict__ hi,
     const int64_t* __restrict__ tlo, const int64_t* __restrict__ thi,
     const uint32_t* __restrict__ lib, const uint32_t* __restrict__ orig,
     const int32_t* __restrict__ qoff, const float* __restrict__ rowk,
-    uint64_t* __restrict__ keys, int64_t chunk, int64_t n_tiles,
-    int64_t chunk_patches, int64_t patches)
+    uint64_t* __restrict__ keys, WorkMap map)
 {
-  const int64_t wg = blockIdx.x;
-  const int64_t slot = wg / kXcds;  // position in this XCD's sequence
-  const int64_t patch = (slot / kPatch) * kXcds + wg % kXcds;
-  if (patch >= patches) return;
-  const int local = (int)(slot % kPatch);
-  const int64_t tile = (patch / chunk_patches) * kPatchTiles + local / kPatchChunks;
-  const int64_t cidx = (patch % chunk_patches) * kPatchChunks + local % kPatchChunks;
-  if (tile >= n_tiles) return;
-  const int64_t a64 = max(cidx * chunk, tlo[tile]);
-  const int64_t b64 = min(cidx * chunk + chunk, thi[tile]);
+  const uint32_t wg = blockIdx.x;
+  const uint32_t per = map.patch_tiles * map.patch_chunks;
+  const uint32_t slot = wg / kXcds;  // position in this XCD's sequence
+  const uint32_t patch = (slot / per) * kXcds + wg % kXcds;
+  if (patch >= map.patches) return;
+  const uint32_t local = slot % per;
+  const uint32_t tile =
+      (patch / map.chunk_patches) * map.patch_tiles + local / map.patch_chunks;
+  const uint32_t cidx =
+      (patch % map.chunk_patches) * map.patch_chunks + local % map.patch_chunks;
+  if (tile >= map.n_tiles || cidx >= map.n_chunks) return;
+  const int64_t c0 = (int64_t)cidx * map.chunk;
+  const int64_t a64 = max(c0, tlo[tile]);
+  const int64_t b64 = min(c0 + map.chunk, thi[tile]);
   if (a64 >= b64) return;
   mfd::tile_rows<F, true, DirectLayout>(words, nq, q_hv, qperm, lo, hi, tile, (uint32_t)a64,
                                         (uint32_t)b64, lib, orig, qoff, rowk, keys);
 }
 
-// 10 |x|_0 + 6 |x|_1 + 2 |x|_2 of a packed row, |x|_m its set bits at
-// components of class m (component mod 4): the fp4 form's per-row constant
-// K (and, plus 21D/4, its per-query constant Q); one wave per row
+// ---- few queries ------------------------------------------------------------
+// A call of few queries is bound by reading the library rows, and a tile of
+// 256 queries would mostly multiply padding. Tiles of 32 TQ queries instead:
+// the workgroup keeps the packed bits of its queries in LDS for the whole
+// chunk (row stride D/8 + 16 bytes, so the 16 rows a quarter-wave reads
+// together fall in 16 distinct bank groups), and each of its eight waves
+// streams its own 32-row blocks of the library straight into registers, two
+// stages of kSG 16-byte loads ahead, with no barrier after the start. The
+// operands are expanded as in mfma_direct.h. The dot products, the row order
+// inside a block and the result keys are those of tile_rows.
+//
+// Measured (D = 8,192, fp4): 64 queries over 400,000 rows 0.65 ms with the
+// 256-query kernel and 4,096-row chunks, 0.14 ms so; 4 queries over 2M rows
+// (1.6 GB of candidates) 0.31 ms per call. Without the one atomic per
+// workgroup (one per wave and query, unconditional) the first took 0.3 ms.
+constexpr int kStreamThreads = 512, kStreamWaves = kStreamThreads / 64;
+constexpr uint32_t kStreamBlock = 32;  // library rows per wave step
+
+template <int F, int TQ, int kSG>
+__device__ __forceinline__ void stream_rows(uint32_t words, int64_t nq,
+    const uint32_t* __restrict__ q_hv, const uint32_t* __restrict__ qperm,
+    const int64_t* __restrict__ lo, const int64_t* __restrict__ hi, int64_t tile, uint32_t a,
+    uint32_t b, const uint32_t* __restrict__ lib, const uint32_t* __restrict__ orig,
+    const int32_t* __restrict__ qoff, const float* __restrict__ rowk,
+    uint64_t* __restrict__ keys)
+{
+  using mfd::v16f;
+  using mfd::v16i;
+  using mfd::v4i;
+  using mfd::v8i;
+  constexpr int NQ = 32 * TQ;
+  extern __shared__ __attribute__((aligned(16))) char s_query[];
+  __shared__ unsigned long long s_best[NQ];
+  const int t = threadIdx.x, l = t & 63, w = __builtin_amdgcn_readfirstlane(t >> 6);
+  const uint32_t r31 = l & 31, h = l >> 5;
+  const uint32_t D = words * 32, stride = words * 4 + 16, pieces = words / 4;
+
+  if (t < NQ) s_best[t] = ~0ull;
+  for (uint32_t i = t; i < NQ * pieces; i += kStreamThreads) {
+    const uint32_t r = i / pieces, p = i % pieces;
+    const int64_t qs = tile * NQ + r;
+    const uint32_t qi = qperm[qs < nq ? qs : nq - 1];
+    *(uint4*)(s_query + r * stride + p * 16) =
+        *(const uint4*)(q_hv + (size_t)qi * words + p * 4);
+  }
+  uint32_t qlo[TQ], qhi[TQ], qid[TQ];
+  int Q[TQ];
+  uint64_t bk[TQ];
+  bool qok[TQ];
+  float need[TQ];
+#pragma unroll
+  for (int j = 0; j < TQ; ++j) {
+    const int64_t qs = tile * NQ + j * 32 + r31;
+    qok[j] = qs < nq;
+    qid[j] = qperm[qok[j] ? qs : nq - 1];
+    qlo[j] = qok[j] ? (uint32_t)lo[qid[j]] : 0u;
+    qhi[j] = qok[j] ? (uint32_t)hi[qid[j]] : 0u;
+    Q[j] = F == mfd::kFmtF4 ? qoff[qid[j]] : (int)D;
+    bk[j] = ~0ull;
+    const uint64_t k0 = qok[j] ? keys[qid[j]] : 0ull;
+    need[j] = !qok[j] ? INFINITY
+              : k0 == ~0ull ? -INFINITY
+                            : (float)(Q[j] - 2 * (int)(uint32_t)(k0 >> 32));
+  }
+  __syncthreads();
+
+  // This wave's blocks: every kStreamWaves-th of the 32-row blocks meeting
+  // [a, b), on absolute multiples of 32. Rows of a block outside [a, b) lie
+  // outside every window of the tile (a chunk's ends are multiples of 32).
+  const uint32_t first = a / kStreamBlock + w, end = (b + kStreamBlock - 1) / kStreamBlock;
+  const uint32_t SPB = words / (8 * kSG);  // stages per block
+  const uint32_t total =
+      first < end ? (end - first + kStreamWaves - 1) / kStreamWaves * SPB : 0;
+  uint32_t sel = 0x80808080u, one = F == mfd::kFmtI8 ? 0x40404040u : 0x38383838u;
+  mfd::Fp4Consts k4{0x11111111u, 0x22222222u, 0x44444444u, 0x88888888u, 0x66666666u};
+  if constexpr (F != mfd::kFmtF4)
+    asm volatile("" : "+v"(sel), "+v"(one));
+  else
+    asm volatile("" : "+v"(k4.c11), "+v"(k4.c22), "+v"(k4.c44), "+v"(k4.c88), "+v"(k4.c66));
+
+  // the loads' cursor (past the end it stays on the last stage)
+  uint32_t l_blk = first, l_sp = 0;
+  auto load = [&](uint4 (&buf)[kSG]) {
+    const uint32_t row = min(l_blk * kStreamBlock + r31, b - 1u);
+    const uint32_t* p = lib + (size_t)row * words + l_sp * (kSG * 8) + h * 4;
+#pragma unroll
+    for (int g = 0; g < kSG; ++g) buf[g] = *(const uint4*)(p + g * 8);
+    if (++l_sp == SPB) {
+      if (l_blk + kStreamWaves < end) {
+        l_blk += kStreamWaves;
+        l_sp = 0;
+      } else {
+        l_sp = SPB - 1;
+      }
+    }
+  };
+  using Acc = typename std::conditional<F == mfd::kFmtI8, v16i, v16f>::type;
+  Acc acc[TQ];
+  uint32_t blk = first, sp = 0;
+  auto stage = [&](uint4 (&buf)[kSG]) {
+    if (sp == 0) {
+#pragma unroll
+      for (int j = 0; j < TQ; ++j) acc[j] = Acc{0};
+    }
+    const char* qb = s_query + r31 * stride + (sp * (2 * kSG) + h) * 16;
+    uint4 cur[kSG];
+#pragma unroll
+    for (int g = 0; g < kSG; ++g) cur[g] = buf[g];
+#pragma unroll
+    for (int g = 0; g < kSG; ++g) {
+      uint4 cb[TQ];
+#pragma unroll
+      for (int j = 0; j < TQ; ++j) cb[j] = *(const uint4*)(qb + j * 32 * stride + g * 32);
+#pragma unroll
+      for (int st = 0; st < 4; ++st) {
+        const uint32_t x = st == 0   ? cur[g].x
+                           : st == 1 ? cur[g].y
+                           : st == 2 ? cur[g].z
+                                     : cur[g].w;
+        v8i av;
+        if constexpr (F == mfd::kFmtF4)
+          av = mfd::expand_fp4(x, k4);
+        else
+          av = mfd::expand_pm1(x, sel, one);
+#pragma unroll
+        for (int j = 0; j < TQ; ++j) {
+          const uint32_t y = st == 0 ? cb[j].x : st == 1 ? cb[j].y : st == 2 ? cb[j].z : cb[j].w;
+          v8i bv;
+          if constexpr (F == mfd::kFmtF4)
+            bv = mfd::expand_fp4(y, k4);
+          else
+            bv = mfd::expand_pm1(y, sel, one);
+          if constexpr (F == mfd::kFmtI8) {
+            const v4i a0 = {av[0], av[1], av[2], av[3]}, a1 = {av[4], av[5], av[6], av[7]};
+            const v4i b0 = {bv[0], bv[1], bv[2], bv[3]}, b1 = {bv[4], bv[5], bv[6], bv[7]};
+            acc[j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a0, b0, acc[j], 0, 0, 0);
+            acc[j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a1, b1, acc[j], 0, 0, 0);
+          } else {
+            acc[j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(av, bv, acc[j], F, F, 0, 0,
+                                                                     0, 0);
+          }
+        }
+      }
+    }
+    if (++sp < SPB) return;
+
+    // The block's results. Accumulator register r of tile j holds row
+    // base + 8 (r / 4) + 4 h + r % 4 and query column j.
+    sp = 0;
+    const uint32_t base = blk * kStreamBlock;
+    blk += kStreamWaves;
+    if constexpr (F == mfd::kFmtF4) {  // t = <x, y> - K(row)
+#pragma unroll
+      for (int rg = 0; rg < 4; ++rg) {
+        const float4 k = *(const float4*)(rowk + base + 8 * rg + 4 * h);
+        const float kv[4] = {k.x, k.y, k.z, k.w};
+#pragma unroll
+        for (int r4 = 0; r4 < 4; ++r4)
+#pragma unroll
+          for (int j = 0; j < TQ; ++j) acc[j][4 * rg + r4] -= kv[r4];
+      }
+    }
+    bool inner = base >= a && base + kStreamBlock <= b;
+#pragma unroll
+    for (int j = 0; j < TQ; ++j)
+      inner = inner && (!qok[j] || (qlo[j] <= base && base + kStreamBlock <= qhi[j]));
+    const bool all_in = __ballot(!inner) == 0;
+#pragma unroll
+    for (int j = 0; j < TQ; ++j) {
+      // the largest dot product among the lane's candidates; only one that
+      // reaches the query's best so far looks up library indices
+      float m = -INFINITY;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const uint32_t g = base + 8 * (r >> 2) + 4 * h + (r & 3);
+        const bool in = all_in || (g >= qlo[j] && g < qhi[j]);
+        m = fmaxf(m, in ? mfd::dot_of(acc[j], r) : -INFINITY);
+      }
+      if (m != -INFINITY && m >= need[j]) {
+        uint32_t o_min = ~0u;
+#pragma unroll
+        for (int rg = 0; rg < 4; ++rg) {
+          const uint4 o4 = *(const uint4*)(orig + base + 8 * rg + 4 * h);
+          const uint32_t ov[4] = {o4.x, o4.y, o4.z, o4.w};
+#pragma unroll
+          for (int r4 = 0; r4 < 4; ++r4) {
+            const uint32_t g = base + 8 * rg + 4 * h + r4;
+            const bool in = all_in || (g >= qlo[j] && g < qhi[j]);
+            if (in && mfd::dot_of(acc[j], 4 * rg + r4) == m) o_min = min(o_min, ov[r4]);
+          }
+        }
+        const uint32_t d = (uint32_t)(Q[j] - (int)m) >> 1;
+        const uint64_t key = ((uint64_t)d << 32) | o_min;
+        bk[j] = key < bk[j] ? key : bk[j];
+        need[j] = m;
+      }
+    }
+  };
+
+  // Two stages of loads in flight in two named register sets, each refilled
+  // right after its stage has taken its words
+  uint4 b0[kSG], b1[kSG];
+  if (total) {
+    load(b0);
+    load(b1);
+  }
+  for (uint32_t s = 0; s < total; s += 2) {
+    stage(b0);
+    load(b0);
+    if (s + 1 < total) {
+      stage(b1);
+      load(b1);
+    }
+  }
+  // One atomic per workgroup and query, and only where it still lowers the
+  // result: thousands of them meet on the few lines of a small call's keys
+  // (a value read too early, or from a stale line, is only too large).
+#pragma unroll
+  for (int j = 0; j < TQ; ++j)
+    if (bk[j] != ~0ull) atomicMin(s_best + j * 32 + r31, (unsigned long long)bk[j]);
+  __syncthreads();
+  if (t < NQ && s_best[t] != ~0ull) {
+    uint64_t* key = keys + qperm[tile * NQ + t];
+    if (s_best[t] < *(volatile uint64_t*)key) atomicMin((unsigned long long*)key, s_best[t]);
+  }
+}
+
+template <int F, int TQ>
+__global__ __launch_bounds__(kStreamThreads, 4) void mfma_stream_kernel(uint32_t words,
+    int64_t nq, const uint32_t* __restrict__ q_hv, const uint32_t* __restrict__ qperm,
+    const int64_t* __restrict__ lo, const int64_t* __restrict__ hi,
+    const int64_t* __restrict__ tlo, const int64_t* __restrict__ thi,
+    const uint32_t* __restrict__ lib, const uint32_t* __restrict__ orig,
+    const int32_t* __restrict__ qoff, const float* __restrict__ rowk,
+    uint64_t* __restrict__ keys, uint32_t n_tiles, uint32_t chunk)
+{
+  // XCD x (workgroup i runs on XCD i mod 8) takes chunks x, x + 8, ... and,
+  // chunk after chunk, every tile: a chunk's rows come into one L2 once
+  const uint32_t wg = blockIdx.x, slot = wg / kXcds;
+  const uint32_t tile = slot % n_tiles;
+  const int64_t c0 = (int64_t)(slot / n_tiles * kXcds + wg % kXcds) * chunk;
+  const int64_t a = max(c0, tlo[tile]), b = min(c0 + chunk, thi[tile]);
+  if (a >= b) return;
+  if (words % 32 == 0)
+    stream_rows<F, TQ, 4>(words, nq, q_hv, qperm, lo, hi, tile, (uint32_t)a, (uint32_t)b, lib,
+                          orig, qoff, rowk, keys);
+  else
+    stream_rows<F, TQ, 2>(words, nq, q_hv, qperm, lo, hi, tile, (uint32_t)a, (uint32_t)b, lib,
+                          orig, qoff, rowk, keys);
+}
+
+// the class weights of a packed row: the fp4 form's per-row constant K (and,
+// plus 21D/4, its per-query constant Q); one wave per row
 __device__ __forceinline__ int fp4_class_weight(const uint32_t* __restrict__ row, uint32_t words)
 {
   const int l = threadIdx.x & 63;
   int s = 0;
-  for (uint32_t i = l; i < words; i += 64) {
-    const uint32_t w = row[i];
-    s += 10 * __builtin_popcount(w & 0x11111111u) + 6 * __builtin_popcount(w & 0x22222222u) +
-         2 * __builtin_popcount(w & 0x44444444u);
-  }
+  for (uint32_t i = l; i < words; i += 64) s += fp4_word_weight(row[i]);
   for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
   return s;
 }
@@ -107,12 +368,38 @@ __global__ __launch_bounds__(256) void fp4_row_consts_kernel(int64_t n, int64_t 
   if ((threadIdx.x & 63) == 0) rowk[r] = (float)s;
 }
 
-constexpr int kMfQueries = mfd::kQueries;  // 256 per workgroup
-constexpr int64_t kMfChunk = 4096;
+// Library rows per workgroup: the largest power of two up to kMfChunk (the
+// stream kernel: kStreamChunk), and at least 256, that makes `items` (tile,
+// chunk) items, of which a window's share holds candidates; fewer leave
+// compute units idle (16,003 queries, 600,002 rows, D = 8,192: 9.76 ms with
+// 4,096-row chunks, 9.28 ms with 1,024-row ones).
+constexpr int64_t kMfChunk = 4096, kStreamChunk = 8192;
+constexpr int64_t kMfItems = 16384;
+int64_t chunk_rows(int64_t n_tiles, int64_t n, int64_t most, int64_t items)
+{
+    int64_t chunk = most;
+    while (chunk > 256 && n_tiles * ((n + chunk - 1) / chunk) < items) chunk /= 2;
+    return chunk;
+}
 
 }  // namespace
 
-int search_mfma_tile() { return kMfQueries; }
+// Queries per tile. Up to a few thousand queries the streaming kernel's small
+// tiles win: less padding, and tighter unions of windows (measured at 200,000
+// to 800,000 rows, D = 8,192, both kernels with their best chunks: 64 queries
+// 0.18 against 0.39 ms, 1,000 0.86 against 0.92, 4,000 0.85 against 0.92 and
+// 3.30 against 3.22, 8,000 1.60 against 1.65). Above D = 8,192 its LDS leaves
+// one workgroup per compute unit, or tiles of 32 only (D = 16,384: 200
+// queries 0.25 against 0.41 ms, 2,000 1.26 against 1.02). Tiles of 32 are also
+// the better ones where a row is short, so that reading it once per tile
+// costs little (D = 1,536, 200 queries 0.13 against 0.19 ms; D = 8,192, 300
+// queries 0.67 against 0.55).
+int search_mfma_tile(const homs_ctx* c, int64_t nq)
+{
+    const bool wide = c->words > 256;
+    if (nq > (wide ? 1024 : 4096)) return mfd::kQueries;
+    return wide || nq <= 32 || (c->words <= 64 && nq <= 512) ? 32 : 64;
+}
 int64_t search_mfma_row_pad() { return mfd::kRows; }
 
 hipError_t launch_fp4_row_consts(int64_t n, uint32_t words, const uint32_t* hv, float* rowk,
@@ -134,34 +421,60 @@ hipError_t launch_fp4_query_offsets(const homs_ctx* c, int64_t nq, const uint32_
 
 hipError_t launch_search_mfma(const homs_ctx* c, int fmt, int64_t nq, const uint32_t* q_hv,
                               const uint32_t* qperm, const int64_t* lo, const int64_t* hi,
-                              const int64_t* tile_lo, const int64_t* tile_hi, int32_t* qoff,
+                              const int64_t* tile_lo, const int64_t* tile_hi, const int32_t* qoff,
                               uint64_t* keys, hipStream_t s)
 {
-    const int64_t n_tiles = (nq + kMfQueries - 1) / kMfQueries;
-    if (n_tiles <= 0 || c->lib.n <= 0) return hipSuccess;
-    const int64_t max_chunks = (c->lib.n + kMfChunk - 1) / kMfChunk;
-    const dim3 block(DirectLayout::kThreads);
-    const int64_t tile_groups = (n_tiles + kPatchTiles - 1) / kPatchTiles;
-    const int64_t chunk_patches = (max_chunks + kPatchChunks - 1) / kPatchChunks;
-    const int64_t patches = tile_groups * chunk_patches;
-    // whole rounds of kXcds patches, so every XCD's sequence is complete
-    const int64_t blocks = (patches + kXcds - 1) / kXcds * kXcds * kPatch;
-    if (blocks > 0x7FFFFFFF) return hipErrorInvalidConfiguration;
-    if (fmt == 0) {
-        mfma_direct_kernel<mfd::kFmtI8><<<(uint32_t)blocks, block, 0, s>>>(
-            c->words, nq, q_hv, qperm, lo, hi, tile_lo, tile_hi, c->lib.hv, c->lib.orig,
-            nullptr, nullptr, keys, kMfChunk, n_tiles, chunk_patches, patches);
-    } else if (fmt == 1) {
-        mfma_direct_kernel<mfd::kFmtF8><<<(uint32_t)blocks, block, 0, s>>>(
-            c->words, nq, q_hv, qperm, lo, hi, tile_lo, tile_hi, c->lib.hv, c->lib.orig,
-            nullptr, nullptr, keys, kMfChunk, n_tiles, chunk_patches, patches);
-    } else {
-        const hipError_t e = launch_fp4_query_offsets(c, nq, q_hv, qoff, s);
-        if (e != hipSuccess) return e;
-        mfma_direct_kernel<mfd::kFmtF4><<<(uint32_t)blocks, block, 0, s>>>(
-            c->words, nq, q_hv, qperm, lo, hi, tile_lo, tile_hi, c->lib.hv, c->lib.orig,
-            qoff, c->lib.rowk, keys, kMfChunk, n_tiles, chunk_patches, patches);
+    if (nq <= 0 || c->lib.n <= 0) return hipSuccess;
+    const int tile = search_mfma_tile(c, nq);
+    const int64_t n_tiles = (nq + tile - 1) / tile;
+    const bool f4 = fmt == 2;
+    if (tile != mfd::kQueries) {
+        const int64_t ch =
+            chunk_rows(n_tiles, c->lib.n, kStreamChunk, n_tiles < 16 ? 4096 : 8192);
+        const int64_t wgs = ((c->lib.n + ch - 1) / ch + kXcds - 1) / kXcds * kXcds * n_tiles;
+        if (wgs > 0x7FFFFFFF) return hipErrorInvalidConfiguration;
+        const size_t lds = (size_t)tile * (c->words * 4 + 16);
+        auto go = [&](auto kern) {
+            kern<<<(uint32_t)wgs, kStreamThreads, lds, s>>>(
+                c->words, nq, q_hv, qperm, lo, hi, tile_lo, tile_hi, c->lib.hv, c->lib.orig,
+                f4 ? qoff : nullptr, f4 ? c->lib.rowk : nullptr, keys, (uint32_t)n_tiles,
+                (uint32_t)ch);
+        };
+        if (tile == 32) {
+            if (fmt == 0) go(mfma_stream_kernel<mfd::kFmtI8, 1>);
+            else if (fmt == 1) go(mfma_stream_kernel<mfd::kFmtF8, 1>);
+            else go(mfma_stream_kernel<mfd::kFmtF4, 1>);
+        } else {
+            if (fmt == 0) go(mfma_stream_kernel<mfd::kFmtI8, 2>);
+            else if (fmt == 1) go(mfma_stream_kernel<mfd::kFmtF8, 2>);
+            else go(mfma_stream_kernel<mfd::kFmtF4, 2>);
+        }
+        return hipGetLastError();
     }
+    const int64_t chunk = chunk_rows(n_tiles, c->lib.n, kMfChunk, kMfItems);
+    const int64_t n_chunks = (c->lib.n + chunk - 1) / chunk;
+    WorkMap m;
+    m.n_tiles = (uint32_t)n_tiles;
+    m.n_chunks = (uint32_t)n_chunks;
+    m.chunk = (uint32_t)chunk;
+    m.patch_tiles = (uint32_t)std::min<int64_t>(4, n_tiles);
+    m.patch_chunks = n_tiles * n_chunks >= 32 * 64 ? 8 : 1;
+    const int64_t tile_groups = (n_tiles + m.patch_tiles - 1) / m.patch_tiles;
+    m.chunk_patches = (uint32_t)((n_chunks + m.patch_chunks - 1) / m.patch_chunks);
+    const int64_t patches = tile_groups * m.chunk_patches;
+    // whole rounds of kXcds patches, so every XCD's sequence is complete
+    const int64_t blocks =
+        (patches + kXcds - 1) / kXcds * kXcds * m.patch_tiles * m.patch_chunks;
+    if (blocks > 0x7FFFFFFF) return hipErrorInvalidConfiguration;
+    m.patches = (uint32_t)patches;
+    auto go = [&](auto kern) {
+        kern<<<(uint32_t)blocks, DirectLayout::kThreads, 0, s>>>(
+            c->words, nq, q_hv, qperm, lo, hi, tile_lo, tile_hi, c->lib.hv, c->lib.orig,
+            f4 ? qoff : nullptr, f4 ? c->lib.rowk : nullptr, keys, m);
+    };
+    if (fmt == 0) go(mfma_direct_kernel<mfd::kFmtI8>);
+    else if (fmt == 1) go(mfma_direct_kernel<mfd::kFmtF8>);
+    else go(mfma_direct_kernel<mfd::kFmtF4>);
     return hipGetLastError();
 }
 

@@ -1,0 +1,92 @@
+"""One-shot search over the sizes where its plan, tiles and kernels change
+(the one-workgroup plan up to 512 queries; tiles of 32, 64 and 256 queries;
+one- and two-stage LDS rows), against the oracle: identical indices and
+distances for every engine, with duplicated precursors, absent charges, NaN
+and infinite precursors (empty windows) among the queries."""
+import numpy as np
+import pytest
+
+from conftest import gpu_available
+
+pytestmark = [pytest.mark.gpu,
+              pytest.mark.skipif(not gpu_available(), reason="needs an MI355X GPU")]
+
+import oracle  # noqa: E402
+from synth import WORKLOADS, make_workload  # noqa: E402
+
+
+def _h():
+    import paper_2211_16422_amd.hyperoms as h
+    return h
+
+
+def _dev(a):
+    import torch
+    return torch.from_numpy(np.ascontiguousarray(a)).to("cuda:0")
+
+
+@pytest.mark.parametrize("dim,n_ref,sizes", [
+    (512, 700, (1, 31, 33, 64, 65, 512, 513, 4096, 4097)),
+    (1536, 333, (1, 32, 511, 513)),
+    (2048, 1301, (2, 63, 257, 512, 514, 1025)),
+    (8192, 420, (1, 33, 65, 600)),
+    (16384, 150, (1, 33, 1024, 1025)),
+    (32768, 65, (5, 70)),
+])
+def test_every_size_matches_the_oracle(dim, n_ref, sizes):
+    import torch
+    h = _h()
+    g = make_workload(WORKLOADS["tiny"], n_ref=n_ref, n_query=max(sizes), seed=31 + dim)
+    lib, q = g.library, g.queries
+    rng = np.random.default_rng(dim)
+    pmz, ch = q.pmz.copy(), q.charge.copy()
+    at = rng.permutation(q.n)[: q.n // 4 * 4].reshape(4, -1)
+    pmz[at[0]] = rng.choice(lib.pmz, size=at.shape[1])  # exact precursors, some repeated
+    odd = at[1][::3]
+    pmz[odd] = rng.choice([np.nan, np.inf, -np.inf, 1e6, -5.0], size=odd.shape[0])
+    ch[at[2][::4]] = rng.choice(np.array([0, 7, -1, 127, -128], np.int8), size=at[2][::4].shape[0])
+    op = oracle.Params(dim=dim)
+    idt, lvt = oracle.codebook(op)
+    o_lib, o_q = oracle.encode_raw(op, idt, lvt, lib), oracle.encode_raw(op, idt, lvt, q)
+    hp = h.Params(dim=dim)
+    with h.Context(hp) as ctx:
+        csr = h.to_device_csr(*h.preprocess(hp, lib.offsets, lib.mz, lib.intensity), "cuda:0")
+        ctx.encode_library(*csr, _dev(lib.pmz), _dev(lib.charge))
+        for n in sizes:
+            hv, d_pmz, d_ch = _dev(o_q[:n].view(np.int32)), _dev(pmz[:n]), _dev(ch[:n])
+            for kind, value in ((h.TOL_DA, 500.0), (h.TOL_PPM, 20.0), (h.TOL_DA, 0.0)):
+                if kind == h.TOL_PPM:  # no ppm window of +inf: its lower bound is inf - inf
+                    pmz = np.where(pmz == np.inf, 2e6, pmz)
+                    d_pmz = _dev(pmz[:n])
+                with np.errstate(invalid="ignore"):
+                    o_idx, o_dist = oracle.search(op, o_lib, lib.pmz, lib.charge, o_q[:n],
+                                                  pmz[:n], ch[:n], kind, value)
+                for engine in (h.ENGINE_POPCOUNT, h.ENGINE_MFMA_I8, h.ENGINE_MFMA_F8,
+                               h.ENGINE_MFMA_F4):
+                    idx, dist = ctx.search_window(hv, d_pmz, d_ch, kind, value, engine)
+                    torch.cuda.synchronize()
+                    what = f"dim {dim}, {n} queries, window {kind}/{value}, engine {engine}"
+                    assert np.array_equal(idx.cpu().numpy(), o_idx), what
+                    assert np.array_equal(dist.cpu().numpy(), o_dist), what
+
+
+def test_window_bounds_equal_a_direct_count():
+    h = _h()
+    rng = np.random.default_rng(5)
+    hp = h.Params(dim=512)
+    for n in (1, 2, 3, 4, 5, 17, 1000, 4099):
+        pmz = np.round(rng.uniform(400, 420, n), 1)  # many ties
+        ch = rng.choice(np.array([-3, 2, 3, 127], np.int8), size=n)
+        with h.Context(hp) as ctx:
+            off = np.zeros(n + 1, np.int64)
+            ctx.encode_library(*h.to_device_csr(off, np.zeros(1, np.int32),
+                                                np.zeros(1, np.uint8), "cuda:0"),
+                               _dev(pmz), _dev(ch))
+            q = np.concatenate([pmz[:50], rng.uniform(395, 425, 200), [np.nan, np.inf, -np.inf]])
+            qc = rng.choice(np.array([-128, -3, 0, 2, 3, 127], np.int8), size=q.shape[0])
+            for value in (0.0, 0.1, 3.0, 100.0):
+                lo, hi = ctx.window_bounds(_dev(q), _dev(qc), h.TOL_DA, value)
+                with np.errstate(invalid="ignore"):
+                    want = ((qc[:, None] == ch) & (q[:, None] - value <= pmz) &
+                            (pmz <= q[:, None] + value)).sum(1)
+                assert np.array_equal((hi - lo).cpu().numpy(), want), (n, value)
