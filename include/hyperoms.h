@@ -122,7 +122,9 @@ typedef struct homs_window {
  * +-64 (int32 accumulate, 4096 <x, y>), fp8 e4m3 +-1.0, or fp4 e2m1 values
  * whose per-query dot product is an exact affine function of H (fp32
  * accumulate). Every partial sum is an integer exactly representable in its
- * accumulator, so all engines return identical results. */
+ * accumulator, so all engines return identical results. Queries whose windows
+ * are too narrow to fill a tile are scored with XOR + population count by
+ * every engine. */
 #define HOMS_ENGINE_POPCOUNT 0
 #define HOMS_ENGINE_MFMA_I8 1
 #define HOMS_ENGINE_MFMA_F8 2

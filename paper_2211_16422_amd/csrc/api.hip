@@ -646,8 +646,7 @@ homs_status run_search(homs_ctx* c, int64_t nq, const uint32_t* d_q_hv, const do
 
     hipEvent_t e0 = mark();
     HIP_TRY(c, homs::launch_query_plan(c, nq, d_q_pmz, d_q_charge, win->kind, win->value,
-                                       engine == HOMS_ENGINE_MFMA_F4 ? d_q_hv : nullptr, tile, w,
-                                       s),
+                                       engine, d_q_hv, tile, w, s),
             "query plan kernels");
     homs::TilePlan plan;
     hipEvent_t e1 = mark();
@@ -665,7 +664,8 @@ homs_status run_search(homs_ctx* c, int64_t nq, const uint32_t* d_q_hv, const do
                                             s),
                 "MFMA search kernel");
     hipEvent_t e2 = mark();
-    HIP_TRY(c, homs::launch_finalize(nq, w.keys, d_out_idx, d_out_dist, s), "finalize kernel");
+    HIP_TRY(c, homs::launch_finish(c, nq, d_q_hv, tile, w, d_out_idx, d_out_dist, s),
+            "result kernel");
     hipEvent_t e3 = mark();
     prof_span(c, e0, e1, homs::kProfPrep);
     prof_span(c, e1, e2, homs::kProfSearch);

@@ -158,18 +158,19 @@ struct QueryPlan {
     int32_t* qoff;       // [nq] the fp4 form's per-query constants
     uint32_t* bucket;    // [nq] order in the making
     uint32_t* place;
-    int64_t* tile_lo;    // per tile: the union of its windows (0, 0: empty),
-    int64_t* tile_hi;
-    int64_t* tile_sum;   // the sum of their sizes
-    int64_t* tile_max;   // and the largest
+    int64_t* tile_lo;    // per tile: the union of its windows (0, 0: no rows for the tile
+    int64_t* tile_hi;    // kernels)
+    uint32_t* tile_narrow;  // windows left to launch_finish
     uint32_t* hist;
 };
 size_t query_plan_bytes(int64_t nq, int tile);
 QueryPlan query_plan_carve(void* base, int64_t nq, int tile);
-// q_hv: query rows when the fp4 constants are wanted, else NULL
 hipError_t launch_query_plan(const homs_ctx* c, int64_t nq, const double* q_pmz,
-                             const int8_t* q_charge, int32_t kind, double value,
+                             const int8_t* q_charge, int32_t kind, double value, int32_t engine,
                              const uint32_t* q_hv, int tile, const QueryPlan& w, hipStream_t s);
+// scans the windows of the narrow tiles and writes every query's result
+hipError_t launch_finish(const homs_ctx* c, int64_t nq, const uint32_t* q_hv, int tile,
+                         const QueryPlan& w, int64_t* out_idx, int32_t* out_dist, hipStream_t s);
 
 // search_popc.hip
 struct TilePlan {

@@ -31,6 +31,29 @@ constexpr int kSmallPlan = 512;   // queries of the one-workgroup plan
 
 inline uint32_t blocks_for(int64_t n) { return (uint32_t)((n + kThreads - 1) / kThreads); }
 
+// Narrow tiles. A tile kernel multiplies a tile's whole union of windows with
+// all its queries; where every window is a small part of the union (standard
+// searches of a few dozen candidates), finish_kernel scans each window on its
+// own instead, one wave per two queries, with XOR and population counts (the
+// same distances). A tile is narrow when ratio x the sum of its windows is at
+// most union x tile, and its largest window leaves the waves evenly loaded.
+// The ratios are where both ways took the same time (D = 8,192): fp4, 256-query
+// tiles: 100,000 queries over 2M rows, scan 2.34 / 3.57 ms at +-50 / 100 ppm
+// against 3.17 ms at either (windows of 1/36 of the union at the crossing);
+// fp8 there 6.0 / 10.8 ms at 200 / 400 ppm against 5.1 / 5.3; small tiles:
+// 2,000 queries, scan 0.43 / 1.55 ms at 200 / 1,000 ppm against 0.70; popcount:
+// 30,000 queries over 400,000 rows, scan 0.53 / 1.38 ms at 200 / 800 ppm
+// against 7.5.
+int64_t narrow_ratio(int32_t engine, int tile)
+{
+    if (engine == HOMS_ENGINE_POPCOUNT) return 3;
+    if (engine == HOMS_ENGINE_MFMA_F4) return tile == 256 ? 36 : 92;
+    return tile == 256 ? 18 : 48;
+}
+// largest window of a narrow tile: few queries are few waves, which a tile
+// kernel's chunks would beat on long windows
+int64_t narrow_max(int64_t nq) { return std::min<int64_t>(2048, 64 + nq / 4); }
+
 struct PlanArgs {
     int64_t nq;
     const double* q_pmz;
@@ -42,6 +65,7 @@ struct PlanArgs {
     const uint32_t* charge_first;
     int64_t nlib;
     int tile;
+    int64_t narrow_ratio, narrow_max;
     uint32_t words;
     const uint32_t* q_hv;  // rows of the fp4 query constants (NULL: not wanted)
     QueryPlan w;
@@ -68,8 +92,8 @@ __device__ __forceinline__ void query_offset(const PlanArgs& a, int64_t q)
     if (l == 0) a.w.qoff[q] = s + (int)(21 * a.words * 8);  // 21D/4
 }
 
-// one wave: the union of tile t's windows, the sum of their sizes and the
-// largest; at(i) is the query in place i of the order
+// one wave: the union of tile t's windows and whether the tile is narrow;
+// at(i) is the query in place i of the order
 template <class At>
 __device__ __forceinline__ void tile_shape(const PlanArgs& a, int64_t t, At at)
 {
@@ -94,10 +118,11 @@ __device__ __forceinline__ void tile_shape(const PlanArgs& a, int64_t t, At at)
         big = max(big, (int64_t)__shfl_xor((long long)big, o));
     }
     if (l == 0) {
-        a.w.tile_lo[t] = mx == 0 ? 0 : mn;
-        a.w.tile_hi[t] = mx;
-        a.w.tile_sum[t] = sum;
-        a.w.tile_max[t] = big;
+        // a narrow tile keeps no rows for the tile kernels
+        const bool narrow = big <= a.narrow_max && sum * a.narrow_ratio <= (mx - mn) * a.tile;
+        a.w.tile_narrow[t] = narrow || mx == 0 ? 1 : 0;
+        a.w.tile_lo[t] = narrow || mx == 0 ? 0 : mn;
+        a.w.tile_hi[t] = narrow ? 0 : mx;
     }
 }
 
@@ -238,6 +263,80 @@ __global__ __launch_bounds__(kThreads) void plan_tiles_kernel(PlanArgs a)
     if (t * a.tile < a.nq) tile_shape(a, t, [&](int64_t i) { return a.w.qperm[i]; });
 }
 
+// ---- after the search: the results of every query, and the narrow tiles
+
+// one wave: the best (distance, library index) of rows [lo, hi) for one query
+// row; 16 lanes per library row (contiguous 256-byte reads), eight rows a step.
+// Bound by fetching the rows: 20,001 queries of 17 rows of 1 KB on average
+// take 72 us (4.8 TB/s) where their 256-query tiles took 1,394 us.
+__device__ __forceinline__ uint64_t scan_window(uint32_t words, const uint32_t* __restrict__ qrow,
+                                                int64_t lo, int64_t hi,
+                                                const uint32_t* __restrict__ lib_hv,
+                                                const uint32_t* __restrict__ lib_orig)
+{
+    const int l = threadIdx.x & 63, g = l >> 4, li = l & 15;
+    const uint32_t nc = words / 4;  // 16-byte pieces per row
+    const uint4* qp = (const uint4*)qrow;
+    uint64_t best = ~0ull;
+    for (int64_t base = lo; base < hi; base += 8) {
+        // rows past the end repeat the last one
+        const int64_t ra = min(base + g, hi - 1), rb = min(base + 4 + g, hi - 1);
+        const uint4* pa = (const uint4*)(lib_hv + (size_t)ra * words);
+        const uint4* pb = (const uint4*)(lib_hv + (size_t)rb * words);
+        const uint32_t oa = lib_orig[ra], ob = lib_orig[rb];
+        uint32_t da = 0, db = 0;
+#pragma unroll 4
+        for (uint32_t c = li; c < nc; c += 16) {
+            const uint4 q = qp[c], x = pa[c], y = pb[c];
+            da += __builtin_popcount(q.x ^ x.x) + __builtin_popcount(q.y ^ x.y) +
+                  __builtin_popcount(q.z ^ x.z) + __builtin_popcount(q.w ^ x.w);
+            db += __builtin_popcount(q.x ^ y.x) + __builtin_popcount(q.y ^ y.y) +
+                  __builtin_popcount(q.z ^ y.z) + __builtin_popcount(q.w ^ y.w);
+        }
+#pragma unroll
+        for (int o = 8; o > 0; o >>= 1) {
+            da += __shfl_xor(da, o);
+            db += __shfl_xor(db, o);
+        }
+        const uint64_t ka = ((uint64_t)da << 32) | oa, kb = ((uint64_t)db << 32) | ob;
+        best = min(best, min(ka, kb));
+    }
+    best = min(best, (uint64_t)__shfl_xor(best, 16));
+    return min(best, (uint64_t)__shfl_xor(best, 32));
+}
+
+// one wave per kPerWave places of the order (of one tile)
+constexpr int kPerWave = 2;
+__global__ __launch_bounds__(kThreads) void finish_kernel(PlanArgs a,
+    const uint32_t* __restrict__ q_hv, const uint32_t* __restrict__ lib_hv,
+    const uint32_t* __restrict__ lib_orig, int64_t* __restrict__ out_idx,
+    int32_t* __restrict__ out_dist)
+{
+    const int64_t p0 =
+        ((int64_t)blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6)) * kPerWave;
+    const int l = threadIdx.x & 63;
+    if (p0 >= a.nq) return;
+    const int n = (int)min((int64_t)kPerWave, a.nq - p0);
+    const uint32_t mine = l < n ? a.w.qperm[p0 + l] : 0u;
+    uint64_t key = ~0ull;
+    if (a.w.tile_narrow[p0 / a.tile]) {  // wave-uniform
+        for (int i = 0; i < n; ++i) {
+            const uint32_t q = __builtin_amdgcn_readlane(mine, i);
+            const int64_t lo = a.w.lo[q], hi = a.w.hi[q];
+            if (hi <= lo) continue;
+            const uint64_t k =
+                scan_window(a.words, q_hv + (size_t)q * a.words, lo, hi, lib_hv, lib_orig);
+            if (l == i) key = k;
+        }
+    } else if (l < n) {
+        key = a.w.keys[mine];
+    }
+    if (l < n) {
+        out_idx[mine] = key == ~0ull ? -1 : (int64_t)(uint32_t)key;
+        out_dist[mine] = key == ~0ull ? -1 : (int32_t)(key >> 32);
+    }
+}
+
 }  // namespace
 
 namespace {
@@ -247,7 +346,7 @@ size_t al(size_t x) { return (x + 255) & ~(size_t)255; }
 size_t query_plan_bytes(int64_t nq, int tile)
 {
     const int64_t nt = (nq + tile - 1) / tile;
-    return 3 * al(nq * 8) + 4 * al(nq * 4) + 4 * al(nt * 8) + al((kBuckets + 1) * 4);
+    return 3 * al(nq * 8) + 4 * al(nq * 4) + 2 * al(nt * 8) + al(nt * 4) + al((kBuckets + 1) * 4);
 }
 
 QueryPlan query_plan_carve(void* base, int64_t nq, int tile)
@@ -269,19 +368,25 @@ QueryPlan query_plan_carve(void* base, int64_t nq, int tile)
     w.place = (uint32_t*)take(nq * 4);
     w.tile_lo = (int64_t*)take(nt * 8);
     w.tile_hi = (int64_t*)take(nt * 8);
-    w.tile_sum = (int64_t*)take(nt * 8);
-    w.tile_max = (int64_t*)take(nt * 8);
+    w.tile_narrow = (uint32_t*)take(nt * 4);
     w.hist = (uint32_t*)take((kBuckets + 1) * 4);
     return w;
 }
 
 hipError_t launch_query_plan(const homs_ctx* c, int64_t nq, const double* q_pmz,
-                             const int8_t* q_charge, int32_t kind, double value,
+                             const int8_t* q_charge, int32_t kind, double value, int32_t engine,
                              const uint32_t* q_hv, int tile, const QueryPlan& w, hipStream_t s)
 {
     if (nq <= 0) return hipSuccess;
-    const PlanArgs a{nq,         q_pmz, q_charge, c->p.charge_match != 0, kind, value, c->lib.pmz,
-                     c->lib.charge_first, c->lib.n, tile, c->words, q_hv, w};
+    if (engine != HOMS_ENGINE_MFMA_F4) q_hv = nullptr;  // no constants wanted
+    const PlanArgs a{nq,          q_pmz,
+                     q_charge,    c->p.charge_match != 0,
+                     kind,        value,
+                     c->lib.pmz,  c->lib.charge_first,
+                     c->lib.n,    tile,
+                     narrow_ratio(engine, tile), narrow_max(nq),
+                     c->words,    q_hv,
+                     w};
     if (nq <= kSmallPlan) {
         const int64_t per = kSmallThreads / 64;
         plan_small_kernel<<<(uint32_t)(1 + (q_hv ? (nq + per - 1) / per : 0)), kSmallThreads, 0,
@@ -295,6 +400,21 @@ hipError_t launch_query_plan(const homs_ctx* c, int64_t nq, const double* q_pmz,
     plan_order_kernel<<<blocks_for(nq), kThreads, 0, s>>>(a);
     const int64_t nt = (nq + tile - 1) / tile;
     plan_tiles_kernel<<<(uint32_t)((nt + 3) / 4), kThreads, 0, s>>>(a);
+    return hipGetLastError();
+}
+
+hipError_t launch_finish(const homs_ctx* c, int64_t nq, const uint32_t* q_hv, int tile,
+                         const QueryPlan& w, int64_t* out_idx, int32_t* out_dist, hipStream_t s)
+{
+    if (nq <= 0) return hipSuccess;
+    PlanArgs a{};
+    a.nq = nq;
+    a.tile = tile;
+    a.words = c->words;
+    a.w = w;
+    const int64_t per = kPerWave * (kThreads / 64);
+    finish_kernel<<<(uint32_t)((nq + per - 1) / per), kThreads, 0, s>>>(
+        a, q_hv, c->lib.hv, c->lib.orig, out_idx, out_dist);
     return hipGetLastError();
 }
 

@@ -90,3 +90,32 @@ def test_window_bounds_equal_a_direct_count():
                     want = ((qc[:, None] == ch) & (q[:, None] - value <= pmz) &
                             (pmz <= q[:, None] + value)).sum(1)
                 assert np.array_equal((hi - lo).cpu().numpy(), want), (n, value)
+
+
+@pytest.mark.parametrize("dim,nq", [(512, 65), (2048, 513), (8192, 4097)])
+@pytest.mark.parametrize("ppm", [5.0, 300.0, 3000.0, 30000.0])
+def test_narrow_and_wide_tiles_agree(dim, nq, ppm):
+    """Windows from a few rows (scanned one by one) to most of a charge (tile
+    kernels), with both kinds in one call at the sizes between: every engine
+    against the oracle."""
+    import torch
+    h = _h()
+    g = make_workload(WORKLOADS["tiny"], n_ref=1500, n_query=nq, seed=77)
+    lib, q = g.library, g.queries
+    pmz = q.pmz.copy()
+    pmz[::7] = lib.pmz[:1] + 1e-3  # a crowd in one place beside the spread ones
+    op = oracle.Params(dim=dim)
+    idt, lvt = oracle.codebook(op)
+    o_lib, o_q = oracle.encode_raw(op, idt, lvt, lib), oracle.encode_raw(op, idt, lvt, q)
+    o_idx, o_dist = oracle.search(op, o_lib, lib.pmz, lib.charge, o_q, pmz, q.charge, h.TOL_PPM,
+                                  ppm)
+    hp = h.Params(dim=dim)
+    with h.Context(hp) as ctx:
+        csr = h.to_device_csr(*h.preprocess(hp, lib.offsets, lib.mz, lib.intensity), "cuda:0")
+        ctx.encode_library(*csr, _dev(lib.pmz), _dev(lib.charge))
+        hv, d_pmz, d_ch = _dev(o_q.view(np.int32)), _dev(pmz), _dev(q.charge)
+        for engine in (h.ENGINE_POPCOUNT, h.ENGINE_MFMA_I8, h.ENGINE_MFMA_F8, h.ENGINE_MFMA_F4):
+            idx, dist = ctx.search_window(hv, d_pmz, d_ch, h.TOL_PPM, ppm, engine)
+            torch.cuda.synchronize()
+            assert np.array_equal(idx.cpu().numpy(), o_idx), (ppm, engine)
+            assert np.array_equal(dist.cpu().numpy(), o_dist), (ppm, engine)
