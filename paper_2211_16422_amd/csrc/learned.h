@@ -35,7 +35,7 @@ struct homs_model {
 
 namespace homs {
 
-constexpr int64_t kEmbedBatch = 16384;  // rows expanded to bf16 per embedding pass
+constexpr int64_t kEmbedBatch = 65536;  // rows per embedding pass (hidden layer kept in bf16)
 
 // Scoring embeddings: the E4M3 format of the OCP 8-bit floating point
 // specification (v1.0, 2023): sign, 4 exponent bits with bias 7, 3 fraction

@@ -27,62 +27,101 @@ constexpr float kEpsNorm = 1e-12f;
 
 inline uint32_t blocks_for(int64_t n) { return (uint32_t)((n + kThreads - 1) / kThreads); }
 
-// packed rows [n][D/32] -> bipolar bf16 rows [n][ld] (+1 = 0x3F80, -1 = 0xBF80)
-__global__ void expand_bits_kernel(int64_t n, uint32_t words, const uint32_t* __restrict__ hv,
-                                   uint16_t* __restrict__ X, int64_t ld)
+// Packed rows of one training batch, both towers stacked: X [M2][words] and
+// its bit transpose XT [words * 32][M2 / 32] (bit i of word j of row d is bit d
+// of X row 32 j + i), the operands of the forward product and of the first
+// layer's weight gradient. Row r < B is query r, row B + r reference r: rows
+// of q_hv / r_hv themselves, or (sel) q_hv[q_rows[perm[step] * B + r]] and
+// r_hv[r_rows[...]]. The first workgroups transpose: a thread turns one
+// 32 x 32 block of bits in registers, and 4 x 16 blocks go through LDS so that
+// the transposed rows are written 64 bytes at a time (in 16-byte pieces this
+// kernel took 19 us of a 2,048 x 8,192 batch); the others copy rows.
+struct PackArgs {
+    const uint32_t* q_hv;
+    const uint32_t* r_hv;
+    RowSelect sel;  // q_rows == nullptr: rows as they are
+};
+
+__global__ __launch_bounds__(64) void pack_batch_kernel(int B, uint32_t words, PackArgs a,
+                                                        int transposers, uint32_t* __restrict__ X,
+                                                        uint32_t* __restrict__ XT)
 {
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= n * (int64_t)words) return;
-    const int64_t r = t / words;
-    const uint32_t w = (uint32_t)(t - r * words);
-    const uint32_t v = hv[r * words + w];
-    uint16_t* o = X + r * ld + (int64_t)w * 32;
+    __shared__ uint32_t tile[4 * 32][17];
+    const int M2 = 2 * B, mws = M2 / 32;
+    auto source = [&](int r) {
+        const bool ref = r >= B;
+        int64_t src = ref ? r - B : r;
+        if (a.sel.q_rows)
+            src = (ref ? a.sel.r_rows : a.sel.q_rows)[(int64_t)a.sel.perm[a.sel.step] * B + src];
+        return (ref ? a.r_hv : a.q_hv) + src * words;
+    };
+    if ((int)blockIdx.x >= transposers) {  // one row per workgroup
+        const int r = (int)blockIdx.x - transposers;
+        const uint32_t* src = source(r);
+        for (uint32_t i = threadIdx.x; i < words; i += 64) X[(size_t)r * words + i] = src[i];
+        return;
+    }
+    const int bx = (int)blockIdx.x % (int)(words / 4), by = (int)blockIdx.x / (int)(words / 4);
+    const int c = threadIdx.x & 3, g = threadIdx.x >> 2;
+    const int mw = by * 16 + g;
+    if (mw < mws) {
+        uint32_t v[32];
 #pragma unroll
-    for (int b = 0; b < 32; b += 2) {
-        const uint32_t lo = ((v >> b) & 1u) ? 0xBF80u : 0x3F80u;
-        const uint32_t hi = ((v >> (b + 1)) & 1u) ? 0xBF80u : 0x3F80u;
-        *(uint32_t*)(o + b) = lo | (hi << 16);
+        for (int i = 0; i < 32; ++i) v[i] = source(mw * 32 + i)[bx * 4 + c];
+        // swap bit blocks of 16, 8, 4, 2, 1
+        uint32_t mask = 0x0000FFFFu;
+#pragma unroll
+        for (int j = 16; j > 0; j >>= 1) {
+#pragma unroll
+            for (int k = 0; k < 32; ++k)
+                if ((k & j) == 0) {
+                    const uint32_t t = ((v[k] >> j) ^ v[k + j]) & mask;
+                    v[k + j] ^= t;
+                    v[k] ^= t << j;
+                }
+            mask ^= mask << (j >> 1);
+        }
+#pragma unroll
+        for (int i = 0; i < 32; ++i) tile[c * 32 + i][g] = v[i];
+    }
+    __syncthreads();
+    for (int i = threadIdx.x; i < 4 * 32 * 16; i += 64) {
+        const int d = i >> 4, j = i & 15;
+        if (by * 16 + j < mws) XT[((size_t)bx * 128 + d) * mws + by * 16 + j] = tile[d][j];
     }
 }
 
-// the same expansion for the rows of one training batch taken through index
-// arrays: row r of the batch is hv[rows[perm[step] * n + r]]
-__global__ void expand_rows_kernel(int64_t n, uint32_t words, const uint32_t* __restrict__ hv,
-                                   const uint32_t* __restrict__ rows,
-                                   const uint32_t* __restrict__ perm, int64_t step,
-                                   uint16_t* __restrict__ X, int64_t ld)
-{
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= n * (int64_t)words) return;
-    const int64_t r = t / words;
-    const uint32_t w = (uint32_t)(t - r * words);
-    const int64_t src = (int64_t)rows[(int64_t)perm[step] * n + r];
-    const uint32_t v = hv[src * words + w];
-    uint16_t* o = X + r * ld + (int64_t)w * 32;
-#pragma unroll
-    for (int b = 0; b < 32; b += 2) {
-        const uint32_t lo = ((v >> b) & 1u) ? 0xBF80u : 0x3F80u;
-        const uint32_t hi = ((v >> (b + 1)) & 1u) ? 0xBF80u : 0x3F80u;
-        *(uint32_t*)(o + b) = lo | (hi << 16);
-    }
-}
-
-// bf16 [R][C] (ld_in) -> bf16 [C][R] (ld_out), 32 x 32 tiles through LDS
-__global__ void transpose_bf16_kernel(int R, int C, const uint16_t* __restrict__ in, int ld_in,
-                                      uint16_t* __restrict__ out, int ld_out)
+// bf16 [R][C] -> bf16 [C][R], 32 x 32 tiles through LDS; up to two matrices
+// in one launch (tiles of the first, then of the second)
+struct Transpose {
+    int R, C;
+    const uint16_t* in;
+    uint16_t* out;
+    __host__ __device__ int tiles() const { return ((R + 31) / 32) * ((C + 31) / 32); }
+};
+__global__ void transpose_bf16_kernel(Transpose a, Transpose b)
 {
     __shared__ uint16_t tile[32][33];
-    const int c0 = blockIdx.x * 32, r0 = blockIdx.y * 32;
+    int at = (int)blockIdx.x;
+    const bool second = at >= a.tiles();
+    const Transpose x = second ? b : a;
+    if (second) at -= a.tiles();
+    const int across = (x.C + 31) / 32;
+    const int c0 = at % across * 32, r0 = at / across * 32;
     const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;  // 256 threads: 8 rows per pass
     for (int i = ty; i < 32; i += 8) {
         const int r = r0 + i, c = c0 + tx;
-        tile[i][tx] = (r < R && c < C) ? in[(size_t)r * ld_in + c] : (uint16_t)0;
+        tile[i][tx] = (r < x.R && c < x.C) ? x.in[(size_t)r * x.C + c] : (uint16_t)0;
     }
     __syncthreads();
     for (int i = ty; i < 32; i += 8) {
         const int c = c0 + i, r = r0 + tx;
-        if (c < C && r < R) out[(size_t)c * ld_out + r] = tile[tx][i];
+        if (c < x.C && r < x.R) x.out[(size_t)c * x.R + r] = tile[tx][i];
     }
+}
+inline void transpose(hipStream_t s, Transpose a, Transpose b = {0, 0, nullptr, nullptr})
+{
+    transpose_bf16_kernel<<<(unsigned)(a.tiles() + b.tiles()), 256, 0, s>>>(a, b);
 }
 
 // unit embedding rows: e = z / sqrt(z.z + eps); one wave per row. With eb8,
@@ -118,16 +157,20 @@ __global__ void normalize_kernel(int64_t M, int E, const float* __restrict__ z,
 }
 
 // InfoNCE over logits S [B][B] (already divided by tau): per row softmax,
-// loss += (logsumexp - S_ii) / B, dS = (P - I) / B stored as bf16 and its
-// transpose. One workgroup per row.
+// row_loss = (logsumexp - S_ii) / B (summed by colsum_final_kernel: an atomic
+// per row on one address took longer than the rows), dS = (P - I) / B stored
+// as bf16. One workgroup per row.
 __global__ void info_nce_kernel(int B, const float* __restrict__ S, uint16_t* __restrict__ dS,
-                                uint16_t* __restrict__ dST, float* __restrict__ loss)
+                                float* __restrict__ row_loss)
 {
+    extern __shared__ float row[];  // the row's logits, read once
     __shared__ float red[kThreads / 64];
     const int i = blockIdx.x;
-    const float* row = S + (size_t)i * B;
     float mx = -INFINITY;
-    for (int j = threadIdx.x; j < B; j += kThreads) mx = fmaxf(mx, row[j]);
+    for (int j = threadIdx.x; j < B; j += kThreads) {
+        row[j] = S[(size_t)i * B + j];
+        mx = fmaxf(mx, row[j]);
+    }
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off));
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = mx;
@@ -145,9 +188,8 @@ __global__ void info_nce_kernel(int B, const float* __restrict__ S, uint16_t* __
         const float p = __expf(row[j] - mx) / sum;
         const float g = (p - (j == i ? 1.f : 0.f)) / (float)B;
         dS[(size_t)i * B + j] = to_bf16(g);
-        dST[(size_t)j * B + i] = to_bf16(g);
     }
-    if (threadIdx.x == 0) atomicAdd(loss, (logf(sum) + mx - row[i]) / (float)B);
+    if (threadIdx.x == 0) row_loss[i] = (logf(sum) + mx - row[i]) / (float)B;
 }
 
 // dz = (dE - e (e.dE)) / s, one wave per row; fp32 and bf16 copies
@@ -171,65 +213,107 @@ __global__ void normalize_backward_kernel(int64_t M, int E, const float* __restr
     }
 }
 
-// column sums of a [M][N] fp32 matrix in two deterministic passes: partial
-// sums of kColRows-row slabs (grid.y = slab), then the slabs in order
+// column sums of two fp32 matrices of M rows (Na and Nb columns) in two
+// deterministic passes: partial sums of kColRows-row slabs (grid.y = slab),
+// then the slabs in order; sums keep their order, with the loads of 16 rows
+// in flight. The second pass also sums the batch's loss.
 constexpr int kColRows = 128;
 
-__global__ void colsum_partial_kernel(int M, int N, const float* __restrict__ a,
-                                      float* __restrict__ part)
+__global__ void colsum_partial_kernel(int M, int Na, int Nb, const float* __restrict__ a,
+                                      const float* __restrict__ b, float* __restrict__ part)
 {
     const int n = blockIdx.x * blockDim.x + threadIdx.x;
-    if (n >= N) return;
+    if (n >= Na + Nb) return;
+    const float* col = n < Na ? a + n : b + (n - Na);
+    const int ld = n < Na ? Na : Nb;
     const int m0 = blockIdx.y * kColRows, m1 = min(m0 + kColRows, M);
     float acc = 0.f;
-    for (int m = m0; m < m1; ++m) acc += a[(size_t)m * N + n];
-    part[(size_t)blockIdx.y * N + n] = acc;
+#pragma unroll 16
+    for (int m = m0; m < m1; ++m) acc += col[(size_t)m * ld];
+    part[(size_t)blockIdx.y * (Na + Nb) + n] = acc;
 }
 
-__global__ void colsum_final_kernel(int P, int N, const float* __restrict__ part,
-                                    float* __restrict__ out)
+__global__ void colsum_final_kernel(int P, int Na, int Nb, const float* __restrict__ part,
+                                    float* __restrict__ out_a, float* __restrict__ out_b, int B,
+                                    const float* __restrict__ row_loss, float* __restrict__ loss)
 {
+    if (blockIdx.x + 1 == gridDim.x) {  // the last one-wave workgroup: the batch's loss
+        float sum = 0.f;
+        for (int i = threadIdx.x; i < B; i += 64) sum += row_loss[i];
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o);
+        if (threadIdx.x == 0) *loss = sum;
+        return;
+    }
     const int n = blockIdx.x * blockDim.x + threadIdx.x;
-    if (n >= N) return;
+    if (n >= Na + Nb) return;
     float acc = 0.f;
-    for (int p = 0; p < P; ++p) acc += part[(size_t)p * N + n];
-    out[n] = acc;
+#pragma unroll 16
+    for (int p = 0; p < P; ++p) acc += part[(size_t)p * (Na + Nb) + n];
+    (n < Na ? out_a[n] : out_b[n - Na]) = acc;
 }
 
-inline void colsum(int M, int N, const float* a, float* part, float* out, hipStream_t s)
+inline void colsums(int M, int Na, int Nb, const float* a, const float* b, float* part,
+                    float* out_a, float* out_b, int B, const float* row_loss, float* loss,
+                    hipStream_t s)
 {
     const int P = (M + kColRows - 1) / kColRows;
-    colsum_partial_kernel<<<dim3((unsigned)((N + 255) / 256), (unsigned)P), 256, 0, s>>>(M, N, a,
-                                                                                         part);
-    colsum_final_kernel<<<(unsigned)((N + 255) / 256), 256, 0, s>>>(P, N, part, out);
+    const unsigned blocks = (unsigned)((Na + Nb + 63) / 64);
+    colsum_partial_kernel<<<dim3(blocks, (unsigned)P), 64, 0, s>>>(M, Na, Nb, a, b, part);
+    colsum_final_kernel<<<blocks + 1, 64, 0, s>>>(P, Na, Nb, part, out_a, out_b, B, row_loss,
+                                                  loss);
 }
 
-__global__ void adam_kernel(int64_t n, float* __restrict__ w, const float* __restrict__ g,
-                            float* __restrict__ m, float* __restrict__ v, float lr, float c1,
-                            float c2, uint16_t* __restrict__ wb)
+// Adam over the four parameter arrays, four elements per thread (every
+// array's size is a multiple of 4); wb: the bf16 copy
+struct AdamArray {
+    float* w;
+    const float* g;
+    float* m;
+    float* v;
+    uint16_t* wb;
+    int64_t quads;
+};
+struct AdamArrays {
+    AdamArray a[4];
+};
+__global__ __launch_bounds__(kThreads) void adam_kernel(AdamArrays all, float lr, float c1,
+                                                        float c2)
 {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const float gi = g[i];
-    const float mi = 0.9f * m[i] + 0.1f * gi;
-    const float vi = 0.999f * v[i] + 0.001f * gi * gi;
-    m[i] = mi;
-    v[i] = vi;
-    const float wi = w[i] - lr * (mi / c1) / (sqrtf(vi / c2) + 1e-8f);
-    w[i] = wi;
-    if (wb) wb[i] = to_bf16(wi);
+    int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const AdamArray& p = all.a[k];
+        if (i < p.quads) {
+            const float4 g4 = ((const float4*)p.g)[i];
+            float4 m4 = ((float4*)p.m)[i], v4 = ((float4*)p.v)[i], w4 = ((float4*)p.w)[i];
+            uint32_t b[4];
+            auto one = [&](float gi, float& m, float& v, float& w, uint32_t& bf) {
+                const float mi = 0.9f * m + 0.1f * gi;
+                const float vi = 0.999f * v + 0.001f * gi * gi;
+                m = mi;
+                v = vi;
+                w = w - lr * (mi / c1) / (sqrtf(vi / c2) + 1e-8f);
+                bf = to_bf16(w);
+            };
+            one(g4.x, m4.x, v4.x, w4.x, b[0]);
+            one(g4.y, m4.y, v4.y, w4.y, b[1]);
+            one(g4.z, m4.z, v4.z, w4.z, b[2]);
+            one(g4.w, m4.w, v4.w, w4.w, b[3]);
+            ((float4*)p.m)[i] = m4;
+            ((float4*)p.v)[i] = v4;
+            ((float4*)p.w)[i] = w4;
+            if (p.wb) ((uint2*)p.wb)[i] = make_uint2(b[0] | (b[1] << 16), b[2] | (b[3] << 16));
+            return;
+        }
+        i -= p.quads;
+    }
 }
 
 __global__ void to_bf16_kernel(int64_t n, const float* __restrict__ a, uint16_t* __restrict__ b)
 {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n) b[i] = to_bf16(a[i]);
-}
-
-__global__ void fill_f32_kernel(int64_t n, float* __restrict__ p, float v)
-{
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) p[i] = v;
 }
 
 size_t al(size_t x) { return (x + 255) & ~(size_t)255; }
@@ -286,8 +370,7 @@ hipError_t model_refresh_bf16(homs_model* m, hipStream_t s)
     const int64_t n1 = (int64_t)m->H * m->D, n2 = (int64_t)m->E * m->H;
     to_bf16_kernel<<<blocks_for(n1), kThreads, 0, s>>>(n1, m->W1, m->W1h);
     to_bf16_kernel<<<blocks_for(n2), kThreads, 0, s>>>(n2, m->W2, m->W2h);
-    transpose_bf16_kernel<<<dim3((m->H + 31) / 32, (m->E + 31) / 32), 256, 0, s>>>(
-        m->E, m->H, m->W2h, m->H, m->W2Th, m->E);
+    transpose(s, {m->E, m->H, m->W2h, m->W2Th});
     return hipGetLastError();
 }
 
@@ -296,7 +379,7 @@ hipError_t model_refresh_bf16(homs_model* m, hipStream_t s)
 
 size_t embed_ws_bytes(const homs_model* m, int64_t rows)
 {
-    return al(rows * m->D * 2) + al(rows * m->H * 2) + 2 * al(rows * m->E * 4) + al(rows * 4);
+    return al(rows * m->H * 2) + al(rows * m->E * 4);
 }
 
 hipError_t model_embed(homs_model* m, int64_t n, const uint32_t* hv, float* out_f32,
@@ -315,29 +398,28 @@ hipError_t model_embed(homs_model* m, int64_t n, const uint32_t* hv, float* out_
         if (e != hipSuccess) return e;
         m->emb_ws_bytes = need;
     }
-    char* p = (char*)m->emb_ws;
-    uint16_t* X = (uint16_t*)p;
-    p += al(rows * m->D * 2);
-    uint16_t* hb = (uint16_t*)p;
-    p += al(rows * m->H * 2);
-    float* a1 = (float*)p;  // also reused for z
-    p += al(rows * m->E * 4);
-    (void)p;
-    const uint32_t words = (uint32_t)(m->D / 32);
+    uint16_t* hb = (uint16_t*)m->emb_ws;
+    float* z = (float*)((char*)m->emb_ws + al(rows * m->H * 2));
+    const int words = m->D / 32;
     for (int64_t r0 = 0; r0 < n; r0 += rows) {
         const int64_t nr = std::min(rows, n - r0);
-        expand_bits_kernel<<<blocks_for(nr * words), kThreads, 0, s>>>(nr, words,
-                                                                        hv + r0 * words, X, m->D);
-        hipError_t e = gemm::gemm_nt<gemm::kBias | gemm::kStoreBf16 | gemm::kReluBf16>(
-            s, (int)nr, m->H, m->D, X, m->D, m->W1h, m->D, 1.f, m->b1, nullptr, nullptr, m->H, hb,
-            m->H);
+        using namespace gemm;
+        Out h;
+        h.bias = m->b1;
+        h.Cb = hb;
+        h.ldcb = m->H;
+        hipError_t e = gemm_nt<kBias | kStoreBf16 | kReluBf16>(
+            s, (int)nr, m->H, m->D, Bits{hv + r0 * words, words}, Bf16{m->W1h, m->D}, h);
         if (e != hipSuccess) return e;
-        e = gemm::gemm_nt<gemm::kBias | gemm::kStoreF32>(s, (int)nr, m->E, m->H, hb, m->H, m->W2h,
-                                                         m->H, 1.f, m->b2, nullptr, a1, m->E,
-                                                         nullptr, 0);
+        Out zo;
+        zo.bias = m->b2;
+        zo.C = z;
+        zo.ldc = m->E;
+        e = gemm_nt<kBias | kStoreF32>(s, (int)nr, m->E, m->H, Bf16{hb, m->H},
+                                       Bf16{m->W2h, m->H}, zo);
         if (e != hipSuccess) return e;
         normalize_kernel<<<(uint32_t)((nr + 3) / 4), 256, 0, s>>>(
-            nr, m->E, a1, nullptr, out_bf16 ? out_bf16 + r0 * m->E : nullptr, nullptr,
+            nr, m->E, z, nullptr, out_bf16 ? out_bf16 + r0 * m->E : nullptr, nullptr,
             out_f32 ? out_f32 + r0 * m->E : nullptr, out_fp8 ? out_fp8 + r0 * m->E : nullptr);
         e = hipGetLastError();
         if (e != hipSuccess) return e;
@@ -351,11 +433,11 @@ hipError_t model_embed(homs_model* m, int64_t n, const uint32_t* hv, float* out_
 size_t train_ws_bytes(const homs_model* m, int B)
 {
     const size_t M2 = 2 * (size_t)B, D = m->D, H = m->H, E = m->E;
-    return 2 * al(M2 * D * 2) + al(M2 * H * 4) + 2 * al(M2 * H * 2) + 3 * al(M2 * E * 4) +
+    return 2 * al(M2 * D / 8) + al(M2 * H * 4) + 2 * al(M2 * H * 2) + 3 * al(M2 * E * 4) +
            al(M2 * E * 2) + al(M2 * 4) + al(E * M2 * 2) + al((size_t)B * B * 4) +
            2 * al((size_t)B * B * 2) + al(M2 * E * 4) + al(M2 * E * 2) + al(E * M2 * 2) +
-           al(M2 * H * 4) + al(M2 * H * 2) + al(H * M2 * 2) +
-           al(((M2 + kColRows - 1) / kColRows) * std::max(H, E) * 4);
+           al(M2 * H * 4) + al(H * M2 * 2) +
+           al(((M2 + kColRows - 1) / kColRows) * (H + E) * 4) + al((size_t)B * 4);
 }
 
 hipError_t model_step(homs_model* m, int B, const uint32_t* q_hv, const uint32_t* r_hv, float tau,
@@ -380,8 +462,8 @@ hipError_t model_step(homs_model* m, int B, const uint32_t* q_hv, const uint32_t
         p += al(bytes);
         return r;
     };
-    uint16_t* X = (uint16_t*)take((size_t)M2 * D * 2);
-    uint16_t* XT = (uint16_t*)take((size_t)M2 * D * 2);
+    uint32_t* X = (uint32_t*)take((size_t)M2 * D / 8);
+    uint32_t* XT = (uint32_t*)take((size_t)M2 * D / 8);
     float* a1 = (float*)take((size_t)M2 * H * 4);
     uint16_t* hb = (uint16_t*)take((size_t)M2 * H * 2);
     uint16_t* hT = (uint16_t*)take((size_t)M2 * H * 2);
@@ -398,9 +480,9 @@ hipError_t model_step(homs_model* m, int B, const uint32_t* q_hv, const uint32_t
     uint16_t* dzb = (uint16_t*)take((size_t)M2 * E * 2);
     uint16_t* dzT = (uint16_t*)take((size_t)E * M2 * 2);
     float* da1 = (float*)take((size_t)M2 * H * 4);
-    uint16_t* da1b = (uint16_t*)take((size_t)M2 * H * 2);
     uint16_t* da1T = (uint16_t*)take((size_t)H * M2 * 2);
-    float* colpart = (float*)take((size_t)((M2 + kColRows - 1) / kColRows) * std::max(H, E) * 4);
+    float* colpart = (float*)take((size_t)((M2 + kColRows - 1) / kColRows) * (H + E) * 4);
+    float* row_loss = (float*)take((size_t)B * 4);
 
     using namespace gemm;
     hipError_t err = hipSuccess;
@@ -410,69 +492,88 @@ hipError_t model_step(homs_model* m, int B, const uint32_t* q_hv, const uint32_t
         if (err != hipSuccess) return err;   \
     } while (0)
     // forward, both towers stacked: rows [0, B) queries, [B, 2B) references
-    if (sel) {
-        expand_rows_kernel<<<blocks_for((int64_t)B * words), kThreads, 0, s>>>(
-            B, words, q_hv, sel->q_rows, sel->perm, sel->step, X, D);
-        expand_rows_kernel<<<blocks_for((int64_t)B * words), kThreads, 0, s>>>(
-            B, words, r_hv, sel->r_rows, sel->perm, sel->step, X + (size_t)B * D, D);
-    } else {
-        expand_bits_kernel<<<blocks_for((int64_t)B * words), kThreads, 0, s>>>(B, words, q_hv, X,
-                                                                                D);
-        expand_bits_kernel<<<blocks_for((int64_t)B * words), kThreads, 0, s>>>(
-            B, words, r_hv, X + (size_t)B * D, D);
+    const PackArgs pack{q_hv, r_hv, sel ? *sel : RowSelect{nullptr, nullptr, nullptr, 0}};
+    const int transposers = (int)(words / 4) * ((M2 / 32 + 15) / 16);
+    pack_batch_kernel<<<(unsigned)(transposers + M2), 64, 0, s>>>(B, words, pack, transposers, X,
+                                                                  XT);
+    {
+        Out o;
+        o.bias = m->b1;
+        o.C = a1;
+        o.ldc = H;
+        o.Cb = hb;
+        o.ldcb = H;
+        o.Ct = hT;
+        o.ldct = M2;
+        STEP(gemm_nt<kBias | kStoreF32 | kStoreBf16 | kReluBf16 | kStoreT>(
+            s, M2, H, D, Bits{X, (int)words}, Bf16{m->W1h, D}, o));
     }
-    STEP(gemm_nt<kBias | kStoreF32 | kStoreBf16 | kReluBf16>(s, M2, H, D, X, D, m->W1h, D, 1.f,
-                                                             m->b1, nullptr, a1, H, hb, H));
-    STEP(gemm_nt<kBias | kStoreF32>(s, M2, E, H, hb, H, m->W2h, H, 1.f, m->b2, nullptr, z, E,
-                                    nullptr, 0));
+    {
+        Out o;
+        o.bias = m->b2;
+        o.C = z;
+        o.ldc = E;
+        STEP(gemm_nt<kBias | kStoreF32>(s, M2, E, H, Bf16{hb, H}, Bf16{m->W2h, H}, o));
+    }
     normalize_kernel<<<(uint32_t)((M2 + 3) / 4), 256, 0, s>>>(M2, E, z, e, eb, sc, nullptr);
     // logits and loss
-    STEP(gemm_nt<kStoreF32>(s, B, B, E, eb, E, eb + (size_t)B * E, E, 1.f / tau, nullptr, nullptr,
-                            S, B, nullptr, 0));
-    fill_f32_kernel<<<1, 64, 0, s>>>(1, loss, 0.f);
-    info_nce_kernel<<<B, kThreads, 0, s>>>(B, S, dS, dST, loss);
+    {
+        Out o;
+        o.alpha = 1.f / tau;
+        o.C = S;
+        o.ldc = B;
+        STEP(gemm_nt<kStoreF32>(s, B, B, E, Bf16{eb, E}, Bf16{eb + (size_t)B * E, E}, o));
+    }
+    info_nce_kernel<<<B, kThreads, (size_t)B * 4, s>>>(B, S, dS, row_loss);
     // dE_q = dS E_r / tau, dE_r = dS^T E_q / tau (B operands are E^T slices)
-    transpose_bf16_kernel<<<dim3((E + 31) / 32, (M2 + 31) / 32), 256, 0, s>>>(M2, E, eb, E, eT,
-                                                                                M2);
-    STEP(gemm_nt<kStoreF32>(s, B, E, B, dS, B, eT + B, M2, 1.f / tau, nullptr, nullptr, dE, E,
-                            nullptr, 0));
-    STEP(gemm_nt<kStoreF32>(s, B, E, B, dST, B, eT, M2, 1.f / tau, nullptr, nullptr,
-                            dE + (size_t)B * E, E, nullptr, 0));
+    transpose(s, {B, B, dS, dST}, {M2, E, eb, eT});
+    {
+        Out o;
+        o.alpha = 1.f / tau;
+        o.C = dE;
+        o.ldc = E;
+        o.batch = 2;
+        o.nextA = dST - dS;
+        o.nextB = -B;
+        o.nextC = (int64_t)B * E;
+        STEP(gemm_nt<kStoreF32>(s, B, E, B, Bf16{dS, B}, Bf16{eT + B, M2}, o));
+    }
     normalize_backward_kernel<<<(uint32_t)((M2 + 3) / 4), 256, 0, s>>>(M2, E, e, sc, dE, dz, dzb);
-    colsum(M2, E, dz, colpart, m->gb2, s);
-    transpose_bf16_kernel<<<dim3((E + 31) / 32, (M2 + 31) / 32), 256, 0, s>>>(M2, E, dzb, E, dzT,
-                                                                                M2);
-    transpose_bf16_kernel<<<dim3((H + 31) / 32, (M2 + 31) / 32), 256, 0, s>>>(M2, H, hb, H, hT,
-                                                                                M2);
-    // dW2 = dz^T h
-    STEP(gemm_nt<kStoreF32>(s, E, H, M2, dzT, M2, hT, M2, 1.f, nullptr, nullptr, m->gW2, H,
-                            nullptr, 0));
-    // da1 = (dz W2) * [a1 > 0]
-    STEP(gemm_nt<kMask | kStoreF32 | kStoreBf16>(s, M2, H, E, dzb, E, m->W2Th, E, 1.f, nullptr,
-                                                 a1, da1, H, da1b, H));
-    colsum(M2, H, da1, colpart, m->gb1, s);
-    transpose_bf16_kernel<<<dim3((H + 31) / 32, (M2 + 31) / 32), 256, 0, s>>>(M2, H, da1b, H,
-                                                                                da1T, M2);
-    // dW1 = da1^T X
-    transpose_bf16_kernel<<<dim3((D + 31) / 32, (M2 + 31) / 32), 256, 0, s>>>(M2, D, X, D, XT,
-                                                                                M2);
-    STEP(gemm_nt<kStoreF32>(s, H, D, M2, da1T, M2, XT, M2, 1.f, nullptr, nullptr, m->gW1, D,
-                            nullptr, 0));
+    transpose(s, {M2, E, dzb, dzT});
+    {  // dW2 = dz^T h
+        Out o;
+        o.C = m->gW2;
+        o.ldc = H;
+        STEP(gemm_nt<kStoreF32>(s, E, H, M2, Bf16{dzT, M2}, Bf16{hT, M2}, o));
+    }
+    {  // da1 = (dz W2) * [a1 > 0]
+        Out o;
+        o.mask = a1;
+        o.C = da1;
+        o.ldc = H;
+        o.Ct = da1T;
+        o.ldct = M2;
+        STEP(gemm_nt<kMask | kStoreF32 | kStoreT>(s, M2, H, E, Bf16{dzb, E}, Bf16{m->W2Th, E}, o));
+    }
+    colsums(M2, E, H, dz, da1, colpart, m->gb2, m->gb1, B, row_loss, loss, s);
+    {  // dW1 = da1^T X
+        Out o;
+        o.C = m->gW1;
+        o.ldc = D;
+        STEP(gemm_nt<kStoreF32>(s, H, D, M2, Bf16{da1T, M2}, Bits{XT, M2 / 32}, o));
+    }
     STEP(hipGetLastError());
     if (!update) return hipSuccess;
     m->step += 1;
     const float c1 = 1.f - powf(0.9f, (float)m->step), c2 = 1.f - powf(0.999f, (float)m->step);
-    const int64_t n1 = (int64_t)H * D, n2 = (int64_t)E * H;
-    adam_kernel<<<blocks_for(n1), kThreads, 0, s>>>(n1, m->W1, m->gW1, m->mW1, m->vW1, lr, c1, c2,
-                                                    m->W1h);
-    adam_kernel<<<blocks_for(H), kThreads, 0, s>>>(H, m->b1, m->gb1, m->mb1, m->vb1, lr, c1, c2,
-                                                   nullptr);
-    adam_kernel<<<blocks_for(n2), kThreads, 0, s>>>(n2, m->W2, m->gW2, m->mW2, m->vW2, lr, c1, c2,
-                                                    m->W2h);
-    adam_kernel<<<blocks_for(E), kThreads, 0, s>>>(E, m->b2, m->gb2, m->mb2, m->vb2, lr, c1, c2,
-                                                   nullptr);
-    transpose_bf16_kernel<<<dim3((H + 31) / 32, (E + 31) / 32), 256, 0, s>>>(E, H, m->W2h, H,
-                                                                              m->W2Th, E);
+    AdamArrays all{{{m->W1, m->gW1, m->mW1, m->vW1, m->W1h, (int64_t)H * D / 4},
+                    {m->W2, m->gW2, m->mW2, m->vW2, m->W2h, (int64_t)E * H / 4},
+                    {m->b1, m->gb1, m->mb1, m->vb1, nullptr, H / 4},
+                    {m->b2, m->gb2, m->mb2, m->vb2, nullptr, E / 4}}};
+    int64_t quads = 0;
+    for (const AdamArray& p : all.a) quads += p.quads;
+    adam_kernel<<<blocks_for(quads), kThreads, 0, s>>>(all, lr, c1, c2);
+    transpose(s, {E, H, m->W2h, m->W2Th});
 #undef STEP
     return hipGetLastError();
 }

@@ -136,6 +136,33 @@ struct SampleGrid {
 // each accumulator register holds 32 consecutive samples of one query and
 // the stores are contiguous.
 constexpr int kSampleSplit = 8;
+constexpr int kTM = 128, kTN = 128, kTK = 32, kRowBytes = 80;
+
+// One thread's share of a K step: pieces c = 2t and 2t + 1 of the 512
+// 16-byte pieces of a 128 x 32 bf16 tile (row c / 4, piece c % 4), for A and B.
+struct Stage {
+    uint4 a0, a1, b0, b1;
+};
+
+__device__ __forceinline__ Stage load_stage(const uint16_t* a_row, const uint16_t* b_row, int k0)
+{
+    Stage st;
+    st.a0 = *(const uint4*)(a_row + k0);
+    st.a1 = *(const uint4*)(a_row + k0 + 8);
+    st.b0 = *(const uint4*)(b_row + k0);
+    st.b1 = *(const uint4*)(b_row + k0 + 8);
+    return st;
+}
+
+__device__ __forceinline__ void store_stage(const Stage& st, uint8_t* sa, uint8_t* sb, int buf)
+{
+    const int off = buf * (kTM * kRowBytes);
+    *(uint4*)(sa + off) = st.a0;
+    *(uint4*)(sa + off + 16) = st.a1;
+    *(uint4*)(sb + off) = st.b0;
+    *(uint4*)(sb + off + 16) = st.b1;
+}
+
 __global__ __launch_bounds__(256) void sample_scores_kernel(
     int E, int64_t q_begin, int64_t q_end, const uint16_t* __restrict__ q_sorted,
     const int64_t* __restrict__ tile_lo, const int64_t* __restrict__ tile_hi,
