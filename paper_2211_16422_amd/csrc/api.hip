@@ -394,14 +394,46 @@ homs_status homs_create(const homs_params* p, int32_t device, homs_ctx** out)
         delete c;
         return fail(nullptr, HOMS_E_OOM, "host allocation failed (codebook)");
     }
-    homs::generate_codebook(p->dim, (uint32_t)c->n_bins, p->n_levels, c->p.id_flips, p->seed,
-                            p->encoding, id.data(), lv.data());
+    homs::CodebookOrders orders;
+    homs::EncodeClasses cls;
+    try {
+        homs::generate_codebook(p->dim, (uint32_t)c->n_bins, p->n_levels, c->p.id_flips, p->seed,
+                                p->encoding, id.data(), lv.data(), &orders);
+        if (p->encoding == HOMS_ENCODING_ID_LEVEL && homs::step_encode_takes(c->p))
+            cls = homs::make_encode_classes(p->dim, p->n_levels, c->p.id_flips, id.data(),
+                                            lv.data(), orders);
+    } catch (const std::bad_alloc&) {
+        delete c;
+        return fail(nullptr, HOMS_E_OOM, "host allocation failed (codebook)");
+    }
+    // the level table and, behind it, the step-function encoding's tables: one
+    // allocation and one copy
+    const size_t lv_bytes = al(lv.size() * 4);
+    const size_t b0 = lv_bytes + al(cls.start.size() * 4), b1 = b0 + al(cls.source.size() * 2);
+    if (cls.classes > 0) {
+        try {
+            lv.resize((b1 + al(cls.first_off.size() * 2)) / 4);
+        } catch (const std::bad_alloc&) {
+            delete c;
+            return fail(nullptr, HOMS_E_OOM, "host allocation failed (codebook)");
+        }
+        char* t = (char*)lv.data();
+        std::memcpy(t + lv_bytes, cls.start.data(), cls.start.size() * 4);
+        std::memcpy(t + b0, cls.source.data(), cls.source.size() * 2);
+        std::memcpy(t + b1, cls.first_off.data(), cls.first_off.size() * 2);
+    }
     hipError_t e = homs::dev_malloc(&c->d_id, id.size() * 4);
     if (e == hipSuccess) e = homs::dev_malloc(&c->d_level, lv.size() * 4);
     if (e == hipSuccess) e = homs::dev_malloc(&c->d_err, 256);
     if (e == hipSuccess) e = hipMemcpy(c->d_id, id.data(), id.size() * 4, hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemcpy(c->d_level, lv.data(), lv.size() * 4, hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemset(c->d_err, 0, 256);
+    if (e == hipSuccess && cls.classes > 0) {
+        const char* t = (const char*)c->d_level;
+        c->step = homs::StepEncode{cls.classes, cls.slots, c->p.id_flips,
+                                   (const uint32_t*)(t + lv_bytes), (const uint16_t*)(t + b0),
+                                   (const uint16_t*)(t + b1)};
+    }
     if (e == hipSuccess) e = scratch_address(device, &c->noalloc_scratch);
     if (e != hipSuccess) {
         std::string msg = std::string("context setup: ") + hipGetErrorString(e);
@@ -449,6 +481,7 @@ homs_status homs_set_codebook(homs_ctx* c, const uint32_t* h_id, const uint32_t*
 {
     if (homs_status s = usable(c)) return s;
     DeviceGuard g(c->device);
+    if (h_id || h_level) c->step.classes = 0;  // the caller's tables need not be step functions
     if (h_id)
         HIP_TRY(c, hipMemcpy(c->d_id, h_id, (size_t)c->n_bins * c->words * 4, hipMemcpyHostToDevice),
                 "hipMemcpy(id table)");

@@ -28,6 +28,16 @@ struct Library {
     float* rowk = nullptr;       // [n + pad] the fp4 search's per-row constant K
 };
 
+// Device tables of the step-function encoding of ID_LEVEL spectra
+// (codebook.h, EncodeClasses), in the level table's allocation; classes = 0:
+// not available.
+struct StepEncode {
+    uint32_t classes = 0, slots = 0, alpha = 0;
+    const uint32_t* start = nullptr;
+    const uint16_t* source = nullptr;
+    const uint16_t* first_off = nullptr;
+};
+
 struct Workspace {
     void* ptr = nullptr;
     size_t bytes = 0;
@@ -74,6 +84,7 @@ struct homs_ctx {
     uint32_t* d_id = nullptr;     // [f][W]
     uint32_t* d_level = nullptr;  // [Q][W]
     uint32_t* d_err = nullptr;    // device error flags
+    homs::StepEncode step;        // tables of the step-function encoding (codebook as generated)
     homs::Library lib;
     bool lib_valid = false;
     uint64_t lib_gen = 0;  // bumped by every homs_encode_library
@@ -104,6 +115,8 @@ inline hipError_t dev_malloc(T** p, size_t bytes)
 // ---- kernel launchers (each in its own translation unit) -------------------
 
 // encode.hip
+// whether the step-function encoding serves these parameters (id_flips resolved)
+bool step_encode_takes(const homs_params& p);
 hipError_t launch_encode(const homs_ctx* c, int64_t n, const int64_t* off, const int32_t* bin,
                          const uint8_t* level, const uint32_t* slot, uint32_t* out,
                          hipStream_t s);

@@ -15,6 +15,7 @@
 #include <string>
 #include <vector>
 
+#include "bits.h"
 #include "gemm_bf16.h"
 #include "learned.h"
 
@@ -68,19 +69,7 @@ __global__ __launch_bounds__(64) void pack_batch_kernel(int B, uint32_t words, P
         uint32_t v[32];
 #pragma unroll
         for (int i = 0; i < 32; ++i) v[i] = source(mw * 32 + i)[bx * 4 + c];
-        // swap bit blocks of 16, 8, 4, 2, 1
-        uint32_t mask = 0x0000FFFFu;
-#pragma unroll
-        for (int j = 16; j > 0; j >>= 1) {
-#pragma unroll
-            for (int k = 0; k < 32; ++k)
-                if ((k & j) == 0) {
-                    const uint32_t t = ((v[k] >> j) ^ v[k + j]) & mask;
-                    v[k + j] ^= t;
-                    v[k] ^= t << j;
-                }
-            mask ^= mask << (j >> 1);
-        }
+        transpose32(v);
 #pragma unroll
         for (int i = 0; i < 32; ++i) tile[c * 32 + i][g] = v[i];
     }
