@@ -162,12 +162,46 @@ homs_status usable(homs_ctx* c)
 void free_library(homs::Library& L)
 {
     if (L.hv) (void)hipFree(L.hv);
-    if (L.pmz) (void)hipFree(L.pmz);
-    if (L.charge) (void)hipFree(L.charge);
-    if (L.orig) (void)hipFree(L.orig);
-    if (L.slot) (void)hipFree(L.slot);
-    if (L.rowk) (void)hipFree(L.rowk);
+    if (L.meta) (void)hipFree(L.meta);
     L = homs::Library{};
+}
+
+inline size_t al(size_t x) { return (x + 255) & ~(size_t)255; }
+
+// A library of n rows in L's buffers where they fit it without keeping more
+// than four times its size, else in new ones (L's are freed first). The pads
+// of orig and rowk, which the matrix-core epilogue reads past the last row,
+// are left to the caller.
+hipError_t place_library(homs::Library& L, int64_t n, uint32_t words)
+{
+    if (L.cap < n || L.cap / 4 > n) {
+        free_library(L);
+        const size_t pad = (size_t)homs::search_mfma_row_pad();
+        hipError_t e = homs::dev_malloc(&L.hv, (size_t)n * words * 4);
+        if (e == hipSuccess)
+            e = homs::dev_malloc(&L.meta, al(n * 8) + al(n) + 2 * al((n + pad) * 4) + al(n * 4) +
+                                              al(257 * 4));
+        if (e != hipSuccess) {
+            free_library(L);
+            return e;
+        }
+        L.cap = n;
+    }
+    const size_t rows = (size_t)L.cap, pad = (size_t)homs::search_mfma_row_pad();
+    char* p = (char*)L.meta;
+    auto take = [&](size_t bytes) {
+        void* r = p;
+        p += al(bytes);
+        return r;
+    };
+    L.pmz = (double*)take(rows * 8);
+    L.charge = (int8_t*)take(rows);
+    L.orig = (uint32_t*)take((rows + pad) * 4);
+    L.rowk = (float*)take((rows + pad) * 4);
+    L.slot = (uint32_t*)take(rows * 4);
+    L.charge_first = (uint32_t*)take(257 * 4);
+    L.n = n;
+    return hipSuccess;
 }
 
 void drop_graph(homs_ctx* c);
@@ -185,8 +219,6 @@ homs_status ensure_workspace(homs_ctx* c, size_t bytes, hipStream_t s)
     c->ws.bytes = want;
     return HOMS_OK;
 }
-
-inline size_t al(size_t x) { return (x + 255) & ~(size_t)255; }
 
 // Scratch of homs_search_window_noalloc: a file-scope device array, one copy
 // per GPU, held until the process ends. Host code never passes the symbol
@@ -539,38 +571,33 @@ homs_status homs_encode_library(homs_ctx* c, int64_t n, const int64_t* d_offsets
         return fail(c, HOMS_E_INVALID, "NULL device pointer");
     DeviceGuard g(c->device);
     hipStream_t s = (hipStream_t)stream;
-    HIP_TRY(c, hipStreamSynchronize(s), "hipStreamSynchronize");
-    free_library(c->lib);
+    // the old library's buffers are written again: no search may still read them
+    HIP_TRY(c, hipDeviceSynchronize(), "hipDeviceSynchronize");
+    homs::Library L = c->lib;
+    c->lib = homs::Library{};
     c->lib_valid = false;
     drop_graph(c);
     c->lib_gen += 1;
     if (n == 0) {
+        free_library(L);
         c->lib_valid = true;
         return HOMS_OK;
     }
-    homs::Library L;
-    L.n = n;
+    hipError_t e = place_library(L, n, c->words);
+    if (e != hipSuccess) return hip_fail(c, e, "encode_library");
     const size_t tmp_bytes = homs::library_sort_temp_bytes(n);
-    void* tmp = nullptr;
-    hipError_t e = homs::dev_malloc(&L.hv, (size_t)n * c->words * 4);
-    if (e == hipSuccess) e = homs::dev_malloc(&L.pmz, (size_t)n * 8);
-    if (e == hipSuccess) e = homs::dev_malloc(&L.charge, (size_t)n);
-    // the MFMA epilogue reads library indices in groups past the last row
-    const size_t orig_pad = (size_t)homs::search_mfma_row_pad();
-    if (e == hipSuccess) e = homs::dev_malloc(&L.orig, ((size_t)n + orig_pad + 257) * 4);
-    if (e == hipSuccess) {
-        L.charge_first = L.orig + n + orig_pad;
-        e = hipMemsetAsync(L.orig + n, 0, orig_pad * 4, s);
+    if (homs_status st = ensure_workspace(c, tmp_bytes, s)) {
+        free_library(L);
+        return st;
     }
-    if (e == hipSuccess) e = homs::dev_malloc(&L.slot, (size_t)n * 4);
-    if (e == hipSuccess) e = homs::dev_malloc(&L.rowk, ((size_t)n + orig_pad) * 4);
-    if (e == hipSuccess) e = homs::dev_malloc(&tmp, tmp_bytes);
+    void* tmp = c->ws.ptr;
+    const size_t orig_pad = (size_t)homs::search_mfma_row_pad();
+    e = hipMemsetAsync(L.orig + n, 0, orig_pad * 4, s);
     if (e == hipSuccess) e = hipMemsetAsync(c->d_err, 0, 4, s);
     hipEvent_t e0 = e == hipSuccess ? prof_mark(c, s) : nullptr;
     if (e == hipSuccess)
         e = homs::launch_library_sort(n, d_pmz, d_charge, c->p.charge_match != 0, tmp, tmp_bytes,
-                                      L.orig, L.pmz, L.charge, L.slot, s);
-    if (e == hipSuccess) e = homs::launch_charge_first(n, L.charge, L.charge_first, s);
+                                      L.orig, L.pmz, L.charge, L.slot, L.charge_first, s);
     hipEvent_t e1 = e == hipSuccess ? prof_mark(c, s) : nullptr;
     if (e == hipSuccess) e = homs::launch_encode(c, n, d_offsets, d_bin, d_level, L.slot, L.hv, s);
     hipEvent_t e2 = e == hipSuccess ? prof_mark(c, s) : nullptr;
@@ -580,7 +607,6 @@ homs_status homs_encode_library(homs_ctx* c, int64_t n, const int64_t* d_offsets
     uint32_t flags = 0;
     if (e == hipSuccess) e = hipMemcpyAsync(&flags, c->d_err, 4, hipMemcpyDeviceToHost, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
-    if (tmp) (void)hipFree(tmp);
     if (e != hipSuccess) {
         free_library(L);
         return hip_fail(c, e, "encode_library");
@@ -1111,8 +1137,10 @@ homs_status homs_device_errors(homs_ctx* c, uint32_t* flags, void* stream)
     uint32_t f = 0;
     HIP_TRY(c, hipMemcpyAsync(&f, c->d_err, 4, hipMemcpyDeviceToHost, s), "read error flags");
     HIP_TRY(c, hipStreamSynchronize(s), "hipStreamSynchronize");
-    HIP_TRY(c, hipMemsetAsync(c->d_err, 0, 4, s), "clear error flags");
-    HIP_TRY(c, hipStreamSynchronize(s), "hipStreamSynchronize");
+    if (f) {
+        HIP_TRY(c, hipMemsetAsync(c->d_err, 0, 4, s), "clear error flags");
+        HIP_TRY(c, hipStreamSynchronize(s), "hipStreamSynchronize");
+    }
     *flags = f;
     return HOMS_OK;
 }
@@ -1718,17 +1746,11 @@ homs_status homs_library_load(homs_ctx* c, const char* path)
     const size_t orig_pad = (size_t)homs::search_mfma_row_pad();
     hipError_t e = hipSuccess;
     if (n > 0) {
-        e = homs::dev_malloc(&L.hv, (size_t)n * c->words * 4);
-        if (e == hipSuccess) e = homs::dev_malloc(&L.pmz, (size_t)n * 8);
-        if (e == hipSuccess) e = homs::dev_malloc(&L.charge, (size_t)n);
-        if (e == hipSuccess) e = homs::dev_malloc(&L.orig, ((size_t)n + orig_pad + 257) * 4);
-        if (e == hipSuccess) e = homs::dev_malloc(&L.slot, (size_t)n * 4);
-        if (e == hipSuccess) e = homs::dev_malloc(&L.rowk, ((size_t)n + orig_pad) * 4);
+        e = place_library(L, n, c->words);
         if (e == hipSuccess) e = hipMemcpy(L.orig, orig.data(), (size_t)n * 4, hipMemcpyHostToDevice);
         if (e == hipSuccess) e = hipMemset(L.orig + n, 0, orig_pad * 4);
         if (e == hipSuccess) e = hipMemcpy(L.pmz, pmz.data(), (size_t)n * 8, hipMemcpyHostToDevice);
         if (e == hipSuccess) e = hipMemcpy(L.charge, charge.data(), (size_t)n, hipMemcpyHostToDevice);
-        L.charge_first = L.orig + n + orig_pad;
         if (e == hipSuccess) e = homs::launch_charge_first(n, L.charge, L.charge_first, nullptr);
         if (e == hipSuccess) e = homs::launch_slots(n, L.orig, L.slot, nullptr);
         if (e == hipSuccess) e = hipDeviceSynchronize();

@@ -80,11 +80,11 @@ void generate_codebook(uint32_t D, uint32_t f, uint32_t Q, uint32_t alpha, uint6
     base_row(g, D, base.data());
     std::vector<uint32_t> order = flip_order(g, D);
     fill_table(D, f, alpha, base.data(), order, id_table);
-    if (orders && encoding == 0) orders->id_order = order;
+    if (orders && encoding == 0) orders->id_order.swap(order);
     base_row(g, D, base.data());
     order = flip_order(g, D);
     fill_table(D, Q, D / 2, base.data(), order, level_table);
-    if (orders && encoding == 0) orders->level_order = order;
+    if (orders && encoding == 0) orders->level_order.swap(order);
     // the baselines of Section 4.2: independent random position vectors,
     // drawn row after row after the level table's draws
     if (encoding != 0)
@@ -96,32 +96,34 @@ EncodeClasses make_encode_classes(uint32_t D, uint32_t Q, uint32_t alpha, const 
 {
     // first level that flips each component: the least j whose m_j exceeds
     // the component's place in the level order
-    std::vector<uint32_t> cls(D);
-    uint32_t u = 1;
-    for (uint32_t r = 0; r < D; ++r) {
-        while (u < Q && ((uint64_t)(D / 2) * u) / (Q - 1) <= r) ++u;
-        const uint32_t d = orders.level_order[r];
-        const uint32_t c0 = ((id_row0[d >> 5] ^ level_row0[d >> 5]) >> (d & 31u)) & 1u;
-        cls[d] = 2 * (u - 1) + c0;
+    std::vector<uint8_t> cls(D);
+    uint32_t r0 = 0;
+    for (uint32_t u = 1; u <= Q; ++u) {
+        const uint32_t r1 = u < Q ? (uint32_t)(((uint64_t)(D / 2) * u) / (Q - 1)) : D;
+        for (; r0 < r1; ++r0) {
+            const uint32_t d = orders.level_order[r0];
+            const uint32_t c0 = ((id_row0[d >> 5] ^ level_row0[d >> 5]) >> (d & 31u)) & 1u;
+            cls[d] = (uint8_t)(2 * (u - 1) + c0);
+        }
     }
     EncodeClasses e;
     e.classes = 2 * Q;
     std::vector<uint32_t> active(e.classes, 0);
     for (uint32_t r = 0; r < alpha; ++r) ++active[cls[orders.id_order[r]]];
     e.start.resize(e.classes);
+    std::vector<uint16_t> next(e.classes);
     for (uint32_t c = 0; c < e.classes; ++c) {
         e.start[c] = e.slots;
+        next[c] = (uint16_t)e.slots;
         e.slots += active[c] + 1;
     }
     e.source.resize(D);
     e.first_off.resize((size_t)e.classes * (alpha + 1));
-    std::vector<uint32_t> next = e.start;
     for (uint32_t r = 0; r <= alpha; ++r) {
-        for (uint32_t c = 0; c < e.classes; ++c)
-            e.first_off[(size_t)r * e.classes + c] = (uint16_t)next[c];
+        std::memcpy(e.first_off.data() + (size_t)r * e.classes, next.data(), e.classes * 2);
         if (r < alpha) {
             const uint32_t d = orders.id_order[r];
-            e.source[d] = (uint16_t)next[cls[d]]++;
+            e.source[d] = next[cls[d]]++;
         }
     }
     for (uint32_t r = alpha; r < D; ++r) {

@@ -18,14 +18,15 @@ constexpr uint32_t kErrPeaks = 2u;  // a spectrum keeping more peaks than device
 
 struct Library {
     int64_t n = 0;
+    int64_t cap = 0;             // rows its two allocations (hv and meta) hold
+    void* meta = nullptr;        // everything below but hv
     uint32_t* hv = nullptr;      // [n][W] rows in sorted order
     double* pmz = nullptr;       // [n] sorted precursor m/z
     int8_t* charge = nullptr;    // [n] sorted charge (all 0 when charge is ignored)
     uint32_t* orig = nullptr;    // [n + pad] library index of each sorted row
-    uint32_t* charge_first = nullptr;  // [257] first row of charge i - 128 or above (in orig's
-                                       // allocation)
+    uint32_t* charge_first = nullptr;  // [257] first row of charge i - 128 or above
     uint32_t* slot = nullptr;    // [n] sorted row of each library index
-    float* rowk = nullptr;       // [n + pad] the fp4 search's per-row constant K
+    float* rowk = nullptr;       // [n + pad] the fp4 search's per-row constant K (pads: zeros)
 };
 
 // Device tables of the step-function encoding of ID_LEVEL spectra
@@ -138,7 +139,7 @@ size_t library_sort_temp_bytes(int64_t n);
 hipError_t launch_library_sort(int64_t n, const double* pmz, const int8_t* charge,
                                bool use_charge, void* temp, size_t temp_bytes,
                                uint32_t* perm_out, double* pmz_out, int8_t* charge_out,
-                               uint32_t* slot_out, hipStream_t s);
+                               uint32_t* slot_out, uint32_t* charge_first, hipStream_t s);
 hipError_t launch_gather_rows(int64_t n, uint32_t words, const uint32_t* src,
                               const uint32_t* orig, uint32_t* dst, hipStream_t s);
 // first[257]: the charges' runs in the sorted library

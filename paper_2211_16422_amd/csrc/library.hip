@@ -50,14 +50,21 @@ __global__ void scatter_sorted_kernel(int64_t n, const uint32_t* __restrict__ pe
                                       const double* __restrict__ pmz,
                                       const int8_t* __restrict__ charge, bool use_charge,
                                       double* __restrict__ pmz_out, int8_t* __restrict__ charge_out,
-                                      uint32_t* __restrict__ slot)
+                                      uint32_t* __restrict__ slot, uint32_t* __restrict__ first)
 {
     const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (j >= n) return;
     const uint32_t i = perm[j];
     pmz_out[j] = pmz[i];
-    charge_out[j] = use_charge ? charge[i] : (int8_t)0;
+    const int c = use_charge ? (int)charge[i] : 0;
+    charge_out[j] = (int8_t)c;
     slot[i] = (uint32_t)j;
+    // the row where a charge begins is the first of every charge since the
+    // last row's; the end closes the table
+    const int before = j == 0 ? -129 : use_charge ? (int)charge[perm[j - 1]] : 0;
+    for (int k = before + 1; k <= c; ++k) first[k + 128] = (uint32_t)j;
+    if (j == n - 1)
+        for (int k = c + 1; k <= 128; ++k) first[k + 128] = (uint32_t)n;
 }
 
 // first[i] = first sorted row of charge i - 128 or above (257 entries)
@@ -183,7 +190,8 @@ size_t library_sort_temp_bytes(int64_t n)
 
 hipError_t launch_library_sort(int64_t n, const double* pmz, const int8_t* charge, bool use_charge,
                                void* temp, size_t temp_bytes, uint32_t* perm_out, double* pmz_out,
-                               int8_t* charge_out, uint32_t* slot_out, hipStream_t s)
+                               int8_t* charge_out, uint32_t* slot_out, uint32_t* charge_first,
+                               hipStream_t s)
 {
     if (n <= 0) return hipSuccess;
     char* p = (char*)temp;
@@ -210,7 +218,8 @@ hipError_t launch_library_sort(int64_t n, const double* pmz, const int8_t* charg
     if (e != hipSuccess) return e;
     if (!alt) return hipErrorInvalidValue;  // one pass ends in ka / perm_out
     scatter_sorted_kernel<<<blocks_for(n), kThreads, 0, s>>>(n, perm_out, pmz, charge, use_charge,
-                                                             pmz_out, charge_out, slot_out);
+                                                             pmz_out, charge_out, slot_out,
+                                                             charge_first);
     return hipGetLastError();
 }
 
