@@ -131,7 +131,9 @@ __device__ __forceinline__ bf16x8 expand8(uint32_t b, uint32_t sel, uint32_t one
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
         const uint32_t x = y << (15 - 2 * j);
-        asm("v_bfi_b32 %0, %1, %2, %3" : "=v"(o.d[j]) : "v"(sel), "v"(x), "v"(one));
+        // one v_bfi_b32 (not inline asm: the compiler must count the wait states
+        // between this write and the matrix instruction)
+        o.d[j] = (sel & x) | (~sel & one);
     }
     return o.v;
 }
