@@ -131,7 +131,7 @@ __device__ __forceinline__ bf16x8 expand8(uint32_t b, uint32_t sel, uint32_t one
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
         const uint32_t x = y << (15 - 2 * j);
-        // one v_bfi_b32 (not inline asm: the compiler must count the wait states
+        // one operation (not inline asm: the compiler must count the wait states
         // between this write and the matrix instruction)
         o.d[j] = (sel & x) | (~sel & one);
     }

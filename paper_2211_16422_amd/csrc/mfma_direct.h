@@ -34,10 +34,21 @@
 // query rows move into LDS in stages of 4 groups (1,024 components, one
 // 128-byte line per row) by direct global-to-LDS loads, one stage ahead of
 // their use, with one barrier per stage; every wave reads its operands from
-// LDS (16 bytes per row and group) and expands them in registers right before
-// the matrix instructions. Staging loads every line once per workgroup
-// instead of once per wave, which was the bound of an earlier version whose
-// lanes loaded their own operand rows from global memory.
+// LDS (16 bytes per row and group) and expands them in registers. Staging
+// loads every line once per workgroup instead of once per wave, which was the
+// bound of an earlier version whose lanes loaded their own operand rows from
+// global memory.
+//
+// What bounds it: the matrix cores, at the clock that the card's power limit
+// leaves (about 2.1 GHz here; a loop of nothing but fp4 instructions on these
+// codes runs at 2.24 GHz). A 256-row block of 8,192 components is 65.5k cycles
+// of matrix instructions. With a step's expansions in one run before its first
+// matrix instruction, and the stage barrier between two groups, it took 83k to
+// 86k; with the expansions spread between the matrix instructions (about three
+// after each, which issue in its shadow), the operands read in a group's last
+// step and the barrier before that step it takes 79k to 81k: 164.8 -> 159.1 ms
+// for 100,000 queries with +-500 Da windows of a library of 1,000,000 rows,
+// 17.8 -> 15.3 ms in fp8 for 16,000 queries of 300,000 rows.
 #pragma once
 
 #include <type_traits>
@@ -72,9 +83,6 @@ struct Layout {
 };
 // 8 waves (two per SIMD) of 4 x 2 tiles: 8 accumulators of 16 registers
 using Layout8 = Layout<2, 4, 4, 2>;
-// 4 waves (one per SIMD) of 4 x 4 tiles: 16 accumulators (AGPRs), each
-// expanded library operand feeding four matrix instructions
-using Layout4 = Layout<2, 2, 4, 4>;
 
 constexpr int kThreads = Layout8::kThreads;   // 512 (the persistent kernel's layout)
 constexpr int kRows = 256;      // library rows per block step
@@ -82,6 +90,14 @@ constexpr int kQueries = 256;   // queries per tile
 
 // s_waitcnt immediate: vmcnt(n), expcnt and lgkmcnt left at their maxima
 constexpr int waitcnt_vm(int n) { return (n & 15) | ((n >> 4) << 14) | 0x70 | 0xF00; }
+
+// bits of x where sel is set, else of y: one v_bfi_b32 while the compiler does
+// not see sel's value. Not inline asm: a matrix instruction must not read a
+// register within two wait states of its vector write, and the compiler counts
+// those only for instructions it knows.
+__device__ __forceinline__ uint32_t bfi(uint32_t sel, uint32_t x, uint32_t y) {
+  return (sel & x) | (~sel & y);
+}
 
 // 32 packed bits -> 32 bytes of +-v whose two values differ only in the sign
 // bit: fp8 e4m3 +-1.0 (0x38 / 0xB8) or int8 +-64 (0x40 / 0xC0). Byte j of
@@ -96,9 +112,7 @@ __device__ __forceinline__ v8i expand_pm1(uint32_t w, uint32_t sel, uint32_t one
 #pragma unroll
   for (int m = 0; m < 8; ++m) {
     const uint32_t x = w << (7 - m);
-    uint32_t r;
-    asm("v_bfi_b32 %0, %1, %2, %3" : "=v"(r) : "v"(sel), "v"(x), "v"(one));
-    o[m] = (int)r;
+    o[m] = (int)bfi(sel, x, one);
   }
   return o;
 }
@@ -112,11 +126,6 @@ __device__ __forceinline__ v8i expand_pm1(uint32_t w, uint32_t sel, uint32_t one
 struct Fp4Consts {
   uint32_t c11, c22, c44, c88, c66;  // kept in VGPRs (VOP3 takes no literals)
 };
-__device__ __forceinline__ uint32_t bfi(uint32_t sel, uint32_t x, uint32_t y) {
-  uint32_t r;
-  asm("v_bfi_b32 %0, %1, %2, %3" : "=v"(r) : "v"(sel), "v"(x), "v"(y));
-  return r;
-}
 __device__ __forceinline__ v8i expand_fp4(uint32_t w, const Fp4Consts& k) {
   v8i o = v8i{0};
   o[0] = (int)bfi(k.c11, w, k.c66);
@@ -141,21 +150,22 @@ __device__ __forceinline__ char* stage_lds() {
   __shared__ __attribute__((aligned(16))) char buf[kStageBytes];
   return buf;
 }
-// library indices of each wave's rows of a block, two blocks in flight
+// library indices of each wave's rows of a block: the block whose results are
+// due, and up to two blocks whose first stage is on its way
 __device__ __forceinline__ uint32_t* orig_lds() {
-  __shared__ __attribute__((aligned(16))) uint32_t buf[2 * Layout8::NW * Layout8::TR * 32];
+  __shared__ __attribute__((aligned(16))) uint32_t buf[3 * Layout8::NW * Layout8::TR * 32];
   return buf;
 }
 // the fp4 row constants K of the same rows
 __device__ __forceinline__ float* rowk_lds() {
-  __shared__ __attribute__((aligned(16))) float buf[2 * Layout8::NW * Layout8::TR * 32];
+  __shared__ __attribute__((aligned(16))) float buf[3 * Layout8::NW * Layout8::TR * 32];
   return buf;
 }
 
 // qoff / rowk: the per-query constant Q and the per-row constant K of the fp4
 // form (by query index and by sorted row, rowk padded like orig; unused by fp8
 // and int8)
-template <int F, int kSG, bool kAhead, class L>
+template <int F, int kSG, class L>
 __device__ __forceinline__ void tile_rows_staged(uint32_t words, int64_t nq,
     const uint32_t* __restrict__ q_hv, const uint32_t* __restrict__ qperm,
     const int64_t* __restrict__ lo, const int64_t* __restrict__ hi, int64_t tile, uint32_t a,
@@ -206,12 +216,11 @@ __device__ __forceinline__ void tile_rows_staged(uint32_t words, int64_t nq,
                             : (float)(Q[j] - 2 * (int)(uint32_t)(k0 >> 32));
   }
   // query rows this lane moves into LDS: rows w * RPW + x * kRPI + l / kP
-  const char* qld[kLI];
+  uint32_t qrow[kLI];
 #pragma unroll
   for (int x = 0; x < kLI; ++x) {
     const int64_t qs = tile * NQ + w * RPW + x * kRPI + l / kP;
-    const uint32_t qi = qs < nq ? qperm[qs] : qperm[nq - 1];
-    qld[x] = (const char*)(q_hv + (size_t)qi * words);
+    qrow[x] = qperm[qs < nq ? qs : nq - 1];
   }
   // Consume these loads here: the compiler does not see the direct loads
   // below, and a wait of its own placed after them would drain them too.
@@ -219,7 +228,7 @@ __device__ __forceinline__ void tile_rows_staged(uint32_t words, int64_t nq,
   for (int j = 0; j < TQ; ++j)
     asm volatile("" : "+v"(qlo[j]), "+v"(qhi[j]), "+v"(qid[j]), "+v"(need[j]), "+v"(Q[j]));
 #pragma unroll
-  for (int x = 0; x < kLI; ++x) asm volatile("" : "+v"(qld[x]));
+  for (int x = 0; x < kLI; ++x) asm volatile("" : "+v"(qrow[x]));
 
   const uint32_t SPB = words / (8 * kSG);  // stages per block
   const uint32_t nblk = (b - a + MR - 1) / MR;
@@ -231,33 +240,30 @@ __device__ __forceinline__ void tile_rows_staged(uint32_t words, int64_t nq,
   else
     asm volatile("" : "+v"(k4.c11), "+v"(k4.c22), "+v"(k4.c44), "+v"(k4.c88), "+v"(k4.c66));
 
-  // piece loaded by this lane in instruction x: LDS position l % kP of row
-  // w * RPW + x * kRPI + l / kP holds piece position ^ f(row)
-  auto lpos = [&](int x) {
-    const uint32_t row = (uint32_t)(w * RPW + x * kRPI + l / kP);
-    return (uint32_t)(l % kP) ^ ((row / kRPB) % kP);
-  };
+  // Direct loads of a stage: instruction x of this wave moves rows w * RPW +
+  // x * kRPI + l / kP; lane l's LDS position l % kP of its row holds piece
+  // position ^ f(row).
+  auto vrow = [&](int x) { return (uint32_t)(w * RPW + x * kRPI + l / kP); };
+  auto vpos = [&](int x) { return ((uint32_t)(l % kP) ^ ((vrow(x) / kRPB) % kP)) * 16u; };
   // Stage S into buffer S % 2: library rows (clamped to the chunk's last
   // row) and query rows, preceded at a block's first stage by the block's
   // library indices. A direct load writes lane l's 16 (4) bytes to M0 + 16 l
-  // (M0 + 4 l). 2 kLI loads per stage, 2 more at a block's first stage.
-  auto issue = [&](uint32_t S) {
-    const uint32_t B = S / SPB, sp = S % SPB;
-    const uint32_t rb = a + B * MR;
-    const uint32_t lim = b - 1u - rb;
-    if (sp == 0) {
+  // (M0 + 4 l). The stages are issued in order: is, ib (its block), isp.
+  uint32_t is = 0, ib3 = 0, isp = 0, irb = a;
+  auto issue = [&]() {
+    if (isp == 0) {
 #pragma unroll
       for (int x = 0; x < 2; ++x) {
-        const uint32_t voff = (rb + wr * TR * 32 + 64 * x + l) * 4u;  // orig is padded
+        const uint32_t voff = (irb + wr * TR * 32 + 64 * x + l) * 4u;  // orig is padded
         const uint32_t m0 = __builtin_amdgcn_readfirstlane(
-            (uint32_t)(uintptr_t)(s_orig + ((B & 1) * WR * WQ + w) * TR * 32 + 64 * x));
+            (uint32_t)(uintptr_t)(s_orig + (ib3 * WR * WQ + w) * TR * 32 + 64 * x));
         asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dword %0, %1"
                      :
                      : "v"(voff), "s"(orig), "s"(m0)
                      : "memory", "m0");
         if constexpr (F == kFmtF4) {  // the rows' K, same positions (rowk is padded)
           const uint32_t mk = __builtin_amdgcn_readfirstlane(
-              (uint32_t)(uintptr_t)(s_rowk + ((B & 1) * WR * WQ + w) * TR * 32 + 64 * x));
+              (uint32_t)(uintptr_t)(s_rowk + (ib3 * WR * WQ + w) * TR * 32 + 64 * x));
           asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dword %0, %1"
                        :
                        : "v"(voff), "s"(rowk), "s"(mk)
@@ -265,13 +271,13 @@ __device__ __forceinline__ void tile_rows_staged(uint32_t words, int64_t nq,
         }
       }
     }
-    char* const sA = lds + (S & 1) * kBuf;
+    char* const sA = lds + (is & 1) * kBuf;
     char* const sB = sA + MR * kRowBytes;
-    const char* gA = (const char*)(lib + (size_t)rb * words);  // uniform
+    const char* gA = (const char*)(lib + (size_t)irb * words) + isp * kRowBytes;  // uniform
+    const uint32_t lim = b - 1u - irb;
 #pragma unroll
     for (int x = 0; x < kLI; ++x) {
-      const uint32_t row = (uint32_t)(w * RPW + x * kRPI + l / kP);
-      const uint32_t voff = min(row, lim) * words * 4u + sp * kRowBytes + lpos(x) * 16u;
+      const uint32_t voff = __umul24(min(vrow(x), lim), words * 4u) + vpos(x);
       const uint32_t m0 = __builtin_amdgcn_readfirstlane(
           (uint32_t)(uintptr_t)(sA + (w * RPW + x * kRPI) * kRowBytes));
       asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1"
@@ -281,13 +287,20 @@ __device__ __forceinline__ void tile_rows_staged(uint32_t words, int64_t nq,
     }
 #pragma unroll
     for (int x = 0; x < kLI; ++x) {
-      const char* src = qld[x] + sp * kRowBytes + lpos(x) * 16u;
+      const char* src =
+          (const char*)(q_hv + (size_t)qrow[x] * words) + isp * kRowBytes + vpos(x);
       const uint32_t m0 = __builtin_amdgcn_readfirstlane(
           (uint32_t)(uintptr_t)(sB + (w * RPW + x * kRPI) * kRowBytes));
       asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off"
                    :
                    : "v"(src), "s"(m0)
                    : "memory", "m0");
+    }
+    ++is;
+    if (++isp == SPB) {
+      isp = 0;
+      ib3 = ib3 == 2 ? 0 : ib3 + 1;
+      irb += MR;
     }
   };
 
@@ -296,122 +309,142 @@ __device__ __forceinline__ void tile_rows_staged(uint32_t words, int64_t nq,
   // and B). Every tile of a wave starts at a multiple of 32 rows, so the
   // position of the piece depends on the lane only.
   const uint32_t r31 = (uint32_t)(l & 31);
-  uint32_t roff[kSG];
-#pragma unroll
-  for (int g = 0; g < kSG; ++g)
-    roff[g] = r31 * kRowBytes + 16u * ((uint32_t)(2 * g + h) ^ ((r31 / kRPB) % kP));
+  // piece 2 g + h of the row sits at (h ^ f) ^ 2 g: the groups' offsets differ
+  // in bits 5 and up by xor
+  const uint32_t roff0 = r31 * kRowBytes + 16u * ((uint32_t)h ^ ((r31 / kRPB) % kP));
 
-  issue(0);
   using Acc = typename std::conditional<F == kFmtI8, v16i, v16f>::type;
   Acc acc[TR][TQ];
-  for (uint32_t S = 0; S < total; ++S) {
-    __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));  // this wave's loads of stage S
-    __syncthreads();  // every wave's loads landed; stage S - 1 is fully read
-    if (S + 1 < total) issue(S + 1);
-    const uint32_t sp = S % SPB;
-    if (sp == 0) {
-#pragma unroll
-      for (int i = 0; i < TR; ++i)
-#pragma unroll
-        for (int j = 0; j < TQ; ++j) acc[i][j] = Acc{0};
-    }
-    const char* bufA = lds + (S & 1) * kBuf + wr * TR * 32 * kRowBytes;
-    const char* bufB = lds + (S & 1) * kBuf + MR * kRowBytes + wq * TQ * 32 * kRowBytes;
-    // kAhead: the operand words of group g + 1 are read while group g
-    // computes (the scheduling barrier keeps the compiler from sinking the
-    // reads back to their use); 24 more registers
-    uint4 pa[2][TR], pb[2][TQ];
-    if constexpr (kAhead) {
-#pragma unroll
-      for (int i = 0; i < TR; ++i) pa[0][i] = *(const uint4*)(bufA + i * 32 * kRowBytes + roff[0]);
-#pragma unroll
-      for (int j = 0; j < TQ; ++j) pb[0][j] = *(const uint4*)(bufB + j * 32 * kRowBytes + roff[0]);
-    }
-#pragma unroll
-    for (int g = 0; g < kSG; ++g) {
-      uint4 ca[TR], cb[TQ];
-      if constexpr (kAhead) {
-        if (g + 1 < kSG) {
-#pragma unroll
-          for (int i = 0; i < TR; ++i)
-            pa[(g + 1) & 1][i] = *(const uint4*)(bufA + i * 32 * kRowBytes + roff[g + 1]);
-#pragma unroll
-          for (int j = 0; j < TQ; ++j)
-            pb[(g + 1) & 1][j] = *(const uint4*)(bufB + j * 32 * kRowBytes + roff[g + 1]);
-        }
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int i = 0; i < TR; ++i) ca[i] = pa[g & 1][i];
-#pragma unroll
-        for (int j = 0; j < TQ; ++j) cb[j] = pb[g & 1][j];
-      } else {
-#pragma unroll
-        for (int i = 0; i < TR; ++i) ca[i] = *(const uint4*)(bufA + i * 32 * kRowBytes + roff[g]);
-#pragma unroll
-        for (int j = 0; j < TQ; ++j) cb[j] = *(const uint4*)(bufB + j * 32 * kRowBytes + roff[g]);
-      }
-#pragma unroll
-      for (int st = 0; st < 4; ++st) {
-        v8i bv[TQ];
-#pragma unroll
-        for (int j = 0; j < TQ; ++j) {
-          const uint32_t x = st == 0 ? cb[j].x : st == 1 ? cb[j].y : st == 2 ? cb[j].z : cb[j].w;
-          if constexpr (F == kFmtF4)
-            bv[j] = expand_fp4(x, k4);
-          else
-            bv[j] = expand_pm1(x, sel, one);
-        }
-#pragma unroll
-        for (int i = 0; i < TR; ++i) {
-          const uint32_t x = st == 0 ? ca[i].x : st == 1 ? ca[i].y : st == 2 ? ca[i].z : ca[i].w;
-          v8i av;
-          if constexpr (F == kFmtF4)
-            av = expand_fp4(x, k4);
-          else
-            av = expand_pm1(x, sel, one);
-#pragma unroll
-          for (int j = 0; j < TQ; ++j) {
-            if constexpr (F == kFmtI8) {
-              // bytes 0-15 and 16-31 of each lane: two K = 32 halves of the
-              // same 64 components, split alike on both operands
-              const v4i a0 = {av[0], av[1], av[2], av[3]}, a1 = {av[4], av[5], av[6], av[7]};
-              const v4i b0 = {bv[j][0], bv[j][1], bv[j][2], bv[j][3]};
-              const v4i b1 = {bv[j][4], bv[j][5], bv[j][6], bv[j][7]};
-              acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a0, b0, acc[i][j], 0, 0, 0);
-              acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a1, b1, acc[i][j], 0, 0, 0);
-            } else {
-              acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(av, bv[j], acc[i][j], F,
-                                                                           F, 0, 0, 0, 0);
-            }
-          }
-        }
-      }
-    }
-    if (sp != SPB - 1) continue;
-
-    // Epilogue of block blk. Accumulator register r of tile (i, j) holds row
-    // base + 32 i + 8 (r / 4) + 4 (l / 32) + r % 4 and query column j; the
-    // block's library indices are in LDS (their load is older than stage S's).
-    const uint32_t blk = S / SPB;
-    const uint32_t base = a + blk * MR + wr * TR * 32;
-    const uint32_t* so = s_orig + ((blk & 1) * WR * WQ + w) * TR * 32 + 4 * (l >> 5);
+  // A block's accumulators start from zero, or (fp4) from -K of their rows,
+  // so that they end as t = <x, y> - K (sums of integers, exact in any order).
+  auto start_block = [&](uint32_t b3) {
     if constexpr (F == kFmtF4) {
-      // fp4: t = <x, y> - K(row) in place (the accumulators restart with the
-      // next block); from here on the epilogue is that of fp8 with t for the
-      // dot product and Q(b) for D
-      const float* sk = s_rowk + ((blk & 1) * WR * WQ + w) * TR * 32 + 4 * (l >> 5);
+      const float* sk = s_rowk + (b3 * WR * WQ + w) * TR * 32 + 4 * (l >> 5);
 #pragma unroll
       for (int i = 0; i < TR; ++i)
 #pragma unroll
         for (int rg = 0; rg < 4; ++rg) {
           const float4 kq = *(const float4*)(sk + i * 32 + 8 * rg);
-          const float kv[4] = {kq.x, kq.y, kq.z, kq.w};
+          const float kv[4] = {-kq.x, -kq.y, -kq.z, -kq.w};
 #pragma unroll
           for (int r4 = 0; r4 < 4; ++r4)
 #pragma unroll
-            for (int j = 0; j < TQ; ++j) acc[i][j][4 * rg + r4] -= kv[r4];
+            for (int j = 0; j < TQ; ++j) acc[i][j][4 * rg + r4] = kv[r4];
         }
+    } else {
+#pragma unroll
+      for (int i = 0; i < TR; ++i)
+#pragma unroll
+        for (int j = 0; j < TQ; ++j) acc[i][j] = Acc{0};
     }
+  };
+  // Operand words of the current group, and the expanded operands of the next
+  // matrix instructions. A step is 32 components (word st of the pieces) of
+  // one row tile and the queries; its operands are expanded one step ahead, so
+  // that only a few expansions issue between any two matrix instructions (in
+  // one run before a step's first they outlast the instruction before). A
+  // word's registers are free once it is expanded: the next group's pieces are
+  // read into them during the group's last step.
+  // The next stage is published before the last step of a stage: by then every
+  // wave has this stage's words in registers and its loads of the next stage
+  // had a whole stage to land; after the barrier the loads of the stage after
+  // next go into the buffer that is free now. The barrier and the first reads
+  // of the next stage hide behind that step's matrix instructions.
+  uint4 ca[TR], cb[TQ];
+  auto read_a = [&](int i, uint32_t S, int g) {
+    ca[i] = *(const uint4*)(lds + (S & 1) * kBuf + (wr * TR + i) * 32 * kRowBytes +
+                            (roff0 ^ (uint32_t)(32 * g)));
+  };
+  auto read_b = [&](int j, uint32_t S, int g) {
+    cb[j] = *(const uint4*)(lds + (S & 1) * kBuf + (MR + (wq * TQ + j) * 32) * kRowBytes +
+                            (roff0 ^ (uint32_t)(32 * g)));
+  };
+  auto expand = [&](const uint4& q, int st) -> v8i {
+    const uint32_t x = st == 0 ? q.x : st == 1 ? q.y : st == 2 ? q.z : q.w;
+    if constexpr (F == kFmtF4)
+      return expand_fp4(x, k4);
+    else
+      return expand_pm1(x, sel, one);
+  };
+  static_assert(TQ < TR, "query operands are expanded beside row tiles 1 .. TQ");
+  issue();
+  __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));
+  __syncthreads();
+  if (total > 1) issue();
+#pragma unroll
+  for (int i = 0; i < TR; ++i) read_a(i, 0, 0);
+#pragma unroll
+  for (int j = 0; j < TQ; ++j) read_b(j, 0, 0);
+  start_block(0);
+  v8i acur = expand(ca[0], 0), bcur[TQ];
+#pragma unroll
+  for (int j = 0; j < TQ; ++j) bcur[j] = expand(cb[j], 0);
+  uint32_t sp = 0, blk = 0, blk3 = 0;
+  for (uint32_t S = 0; S < total; ++S) {
+    // the stage after this one (past the end its operands are read again from
+    // this one and not used)
+    const uint32_t Sn = S + 1 < total ? S + 1 : S;
+#pragma unroll
+    for (int g = 0; g < kSG; ++g) {
+      const int gn = g + 1 < kSG ? g + 1 : 0;
+#pragma unroll
+      for (int st = 0; st < 4; ++st) {
+        if (st == 3) {
+          if (g + 1 == kSG && S + 1 < total) {
+            __builtin_amdgcn_s_waitcnt(waitcnt_vm(0) & ~0xF00);  // and lgkmcnt(0)
+            __syncthreads();
+            if (S + 2 < total) issue();
+          }
+#pragma unroll
+          for (int j = 0; j < TQ; ++j) read_b(j, gn ? S : Sn, gn);
+          read_a(0, gn ? S : Sn, gn);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        v8i bnext[TQ];
+#pragma unroll
+        for (int i = 0; i < TR; ++i) {
+#pragma unroll
+          for (int j = 0; j < TQ; ++j) {
+            if constexpr (F == kFmtI8) {
+              // bytes 0-15 and 16-31 of each lane: two K = 32 halves of the
+              // same 64 components, split alike on both operands
+              const v4i a0 = {acur[0], acur[1], acur[2], acur[3]};
+              const v4i a1 = {acur[4], acur[5], acur[6], acur[7]};
+              const v4i b0 = {bcur[j][0], bcur[j][1], bcur[j][2], bcur[j][3]};
+              const v4i b1 = {bcur[j][4], bcur[j][5], bcur[j][6], bcur[j][7]};
+              acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a0, b0, acc[i][j], 0, 0, 0);
+              acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a1, b1, acc[i][j], 0, 0, 0);
+            } else {
+              acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(acur, bcur[j], acc[i][j],
+                                                                           F, F, 0, 0, 0, 0);
+            }
+          }
+          acur = i + 1 < TR ? expand(ca[i + 1], st) : expand(ca[0], (st + 1) & 3);
+          if (st == 3 && i + 1 < TR) read_a(i + 1, gn ? S : Sn, gn);
+          if (i >= 1 && i <= TQ) bnext[i - 1] = expand(cb[i - 1], (st + 1) & 3);
+        }
+#pragma unroll
+        for (int j = 0; j < TQ; ++j) bcur[j] = bnext[j];
+#pragma unroll
+        for (int m = 0; m < TR * TQ; ++m) {
+          __builtin_amdgcn_sched_group_barrier(0x008, F == kFmtI8 ? 2 : 1, 0);  // matrix
+          __builtin_amdgcn_sched_group_barrier(0x002, F == kFmtF4 ? 3 : 12, 0);  // vector
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+    if (++sp != SPB) continue;
+    sp = 0;
+
+    // Epilogue of block blk. Accumulator register r of tile (i, j) holds row
+    // base + 32 i + 8 (r / 4) + 4 (l / 32) + r % 4 and query column j; the
+    // block's library indices are in LDS. For fp4 the accumulators hold t, the
+    // dot product less the row's K; from here on the epilogue is that of fp8
+    // with t for the dot product and Q(b) for D.
+    const uint32_t base = a + blk * MR + wr * TR * 32;
+    const uint32_t* so = s_orig + (blk3 * WR * WQ + w) * TR * 32 + 4 * (l >> 5);
+    ++blk;
+    blk3 = blk3 == 2 ? 0 : blk3 + 1;
     bool inner = base + TR * 32 <= b;
 #pragma unroll
     for (int j = 0; j < TQ; ++j)
@@ -473,6 +506,7 @@ __device__ __forceinline__ void tile_rows_staged(uint32_t words, int64_t nq,
         if (bk[j] != ~0ull)
           need[j] = fmaxf(need[j], (float)(Q[j] - 2 * (int)(uint32_t)(bk[j] >> 32)));
     }
+    if (S + 1 < total) start_block(blk3);
   }
   __syncthreads();  // LDS is free again when the caller starts another tile
 #pragma unroll
@@ -485,10 +519,8 @@ __device__ __forceinline__ void tile_rows_staged(uint32_t words, int64_t nq,
   }
 }
 
-// 4-group stages when D / 256 is a multiple of 4, else 2-group stages;
-// kAhead reads each group's operands one group early (for callers with 24
-// registers to spare)
-template <int F, bool kAhead = false, class L = Layout8>
+// 4-group stages when D / 256 is a multiple of 4, else 2-group stages
+template <int F, class L = Layout8>
 __device__ __forceinline__ void tile_rows(uint32_t words, int64_t nq,
     const uint32_t* __restrict__ q_hv, const uint32_t* __restrict__ qperm,
     const int64_t* __restrict__ lo, const int64_t* __restrict__ hi, int64_t tile, uint32_t a,
@@ -497,10 +529,10 @@ __device__ __forceinline__ void tile_rows(uint32_t words, int64_t nq,
     uint64_t* __restrict__ keys)
 {
   if (words % 32 == 0)
-    tile_rows_staged<F, 4, kAhead, L>(words, nq, q_hv, qperm, lo, hi, tile, a, b, lib, orig,
+    tile_rows_staged<F, 4, L>(words, nq, q_hv, qperm, lo, hi, tile, a, b, lib, orig,
                                       qoff, rowk, keys);
   else
-    tile_rows_staged<F, 2, kAhead, L>(words, nq, q_hv, qperm, lo, hi, tile, a, b, lib, orig,
+    tile_rows_staged<F, 2, L>(words, nq, q_hv, qperm, lo, hi, tile, a, b, lib, orig,
                                       qoff, rowk, keys);
 }
 

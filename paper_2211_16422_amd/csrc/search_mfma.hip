@@ -83,7 +83,7 @@ __global__ __launch_bounds__(DirectLayout::kThreads, 1) void mfma_direct_kernel(
   const int64_t a64 = max(c0, tlo[tile]);
   const int64_t b64 = min(c0 + map.chunk, thi[tile]);
   if (a64 >= b64) return;
-  mfd::tile_rows<F, true, DirectLayout>(words, nq, q_hv, qperm, lo, hi, tile, (uint32_t)a64,
+  mfd::tile_rows<F, DirectLayout>(words, nq, q_hv, qperm, lo, hi, tile, (uint32_t)a64,
                                         (uint32_t)b64, lib, orig, qoff, rowk, keys);
 }
 
