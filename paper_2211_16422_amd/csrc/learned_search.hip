@@ -16,8 +16,8 @@
 //     windows of at most kSample (= kCapacity) candidates keep everything;
 //  2. collect: score every (query, candidate) pair on matrix cores (E4M3
 //     scoring embeddings, fp32 accumulation; a workgroup takes 128
-//     m/z-ordered queries and an 8,192-row chunk of the library in 32-row
-//     block steps) and append in-window pairs at or above the query's
+//     m/z-ordered queries and an 8,192-row chunk of the library in 64-row
+//     stages) and append in-window pairs at or above the query's
 //     threshold to its buffer of kCapacity 64-bit keys (order-preserving
 //     score << 32 | sorted row), in two passes: pass 0 over every eighth
 //     absolute 128-row block with the sampled threshold; then per query a
@@ -57,7 +57,7 @@ constexpr int kCapacity = 8192;  // buffer entries per query
 constexpr int kCountStride = 32;
 constexpr int kTileQ = 128;      // queries per collection workgroup
 constexpr int64_t kCollectChunk = 8192;  // library rows per collection workgroup
-constexpr int kRowGroups = 1;  // row groups of a collection workgroup (32-row block steps)
+constexpr int kRowGroups = 1;  // row groups of a collection workgroup (64-row stages)
 constexpr int kThreads = 256;
 constexpr int64_t kFallbackRows = 512;   // window rows per wave in the exhaustive fallback
 
@@ -297,6 +297,26 @@ __device__ RadixDigit radix_digit(const uint32_t* hist, uint32_t r)
     return out;
 }
 
+// The r-th largest (r in 1 .. n) of v[0, n), n <= 64 N, by one wave: the bits of
+// the largest x that at least r values reach, from the top.
+template <int N>
+__device__ uint32_t wave_rth_largest(const uint32_t* v, int n, uint32_t r)
+{
+    const int l = threadIdx.x & 63;
+    uint32_t k[N];
+#pragma unroll
+    for (int j = 0; j < N; ++j) k[j] = l + 64 * j < n ? v[l + 64 * j] : 0u;
+    uint32_t x = 0;
+    for (int b = 31; b >= 0; --b) {
+        const uint32_t y = x | (1u << b);
+        uint32_t c = 0;
+#pragma unroll
+        for (int j = 0; j < N; ++j) c += (uint32_t)__popcll(__ballot(k[j] >= y));
+        if (c >= r) x = y;
+    }
+    return x;
+}
+
 // One workgroup per query of the pass: the r-th largest of its in-window
 // sample scores (radix select over order-preserving keys, 8 bits per round),
 // with r chosen so that about `target` window candidates are expected at or
@@ -306,7 +326,8 @@ __global__ __launch_bounds__(kThreads) void threshold_kernel(
     const int64_t* __restrict__ lo, const int64_t* __restrict__ hi,
     const SampleGrid* __restrict__ grids, const float* __restrict__ S, float* __restrict__ thr)
 {
-    __shared__ uint32_t hist[256];
+    constexpr int kList = 512;
+    __shared__ uint32_t hist[256], s_list[kList], s_n;
     __shared__ RadixDigit s_rd;
     const int64_t qp = blockIdx.x;  // position in the pass
     const int64_t p = q_begin + qp;
@@ -334,6 +355,38 @@ __global__ __launch_bounds__(kThreads) void threshold_kernel(
     for (int j = 0; j < kPer; ++j) {
         const int i = (int)threadIdx.x + j * kThreads;
         key[j] = i < ns ? fkey(v[i]) : 0u;
+    }
+    // A small r (the usual case) needs only the largest few keys: the r-th
+    // largest L of the threads' maxima has at least r keys at or above it, and
+    // hardly more; those go to a list, and its r-th largest is the answer. The
+    // radix rounds below count every key four times, and most keys share a few
+    // leading digits, so their counts serialise: 285 -> 210 us for 16,384
+    // queries of 8,192 samples.
+    if (r <= kThreads / 2) {  // uniform
+        uint32_t mx = key[0];
+#pragma unroll
+        for (int j = 1; j < kPer; ++j) mx = max(mx, key[j]);
+        s_list[threadIdx.x] = mx;
+        if (threadIdx.x == 0) s_n = 0;
+        __syncthreads();
+        const uint32_t L = wave_rth_largest<kThreads / 64>(s_list, kThreads, r);
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < kPer; ++j)
+            if (key[j] >= L && (int)threadIdx.x + j * kThreads < ns) {
+                const uint32_t at = atomicAdd(&s_n, 1u);
+                if (at < (uint32_t)kList) s_list[at] = key[j];
+            }
+        __syncthreads();
+        const uint32_t c = s_n;
+        if (c <= (uint32_t)kList && c >= r) {  // uniform
+            if (threadIdx.x < 64) {
+                const uint32_t x = wave_rth_largest<kList / 64>(s_list, (int)c, r);
+                if (threadIdx.x == 0) thr[p] = fkey_inv(x);
+            }
+            return;
+        }
+        __syncthreads();
     }
     uint32_t prefix = 0, mask = 0;
     for (int shift = 24; shift >= 0; shift -= 8) {
@@ -404,8 +457,11 @@ __global__ __launch_bounds__(kThreads) void refine_threshold_kernel(
     const uint64_t* keys = buf + (size_t)qp * kCapacity;
     constexpr int kPer = kCapacity / kThreads;
     uint32_t key[kPer];  // score halves of the keys, in registers
+    // a few hundred keys as a rule: only the steps that hold any
+    const int used = (n + kThreads - 1) / kThreads;  // uniform
 #pragma unroll
     for (int j = 0; j < kPer; ++j) {
+        if (j >= used) break;
         const int i = (int)threadIdx.x + j * kThreads;
         key[j] = i < n ? (uint32_t)(keys[i] >> 32) : 0u;
     }
@@ -415,6 +471,7 @@ __global__ __launch_bounds__(kThreads) void refine_threshold_kernel(
         __syncthreads();
 #pragma unroll
         for (int j = 0; j < kPer; ++j) {
+            if (j >= used) break;
             const int i = (int)threadIdx.x + j * kThreads;
             if (i < n && (key[j] & mask) == prefix) atomicAdd(&hist[(key[j] >> shift) & 255u], 1u);
         }
@@ -431,7 +488,7 @@ __global__ __launch_bounds__(kThreads) void refine_threshold_kernel(
     if (threadIdx.x == 0) thr2[p] = fmaxf(t1, fkey_inv(prefix));
 }
 
-// Scores BR = 32 NWR library rows x 128 m/z-ordered queries per block step on
+// Scores BR = 64 NWR library rows x 128 m/z-ordered queries per stage on
 // matrix cores and appends every in-window pair at or above the query's
 // threshold.
 //
@@ -440,45 +497,44 @@ __global__ __launch_bounds__(kThreads) void refine_threshold_kernel(
 // of two codes is exact in fp32, and the accumulator holds 256 times the
 // score of the rounded embeddings.
 //
-// 2 NWR waves per workgroup, two per SIMD: wave (wr, wn) owns rows 32 wr ..
-// + 31 of each block and the 64 queries of half wn (two 32-query tiles),
-// whose codes are its B operands for the whole chunk (E / 64 steps of 32
-// bytes per tile), so every A operand read from LDS feeds two matrix
-// instructions. Library rows
-// stream through four LDS buffers filled by direct global-to-LDS loads
-// (global_load_lds_dwordx4, no staging registers): one load moves 1 KB (64
-// lanes x 16 bytes) of a block's rows, so a block of BR E-byte rows takes
-// E / 64 loads per wave. The barrier of a block step couples only the waves
-// of one workgroup: with NWR = 1 (32-row steps, two waves) four workgroups
-// share a compute unit and the matrix cores run the waves of the others
-// while one workgroup waits at its barrier (with 1M + 1M rows and 100k
-// queries the scoring takes 22.4 ms with NWR = 2 and 21.0 ms with NWR = 1,
-// against 27.3 ms with NWR = 4, one workgroup per compute unit). Per block
-// step, the block's A operands are in registers (read from LDS one step
-// ahead), the next block waits in LDS and
-// two more are in flight; one barrier per block both publishes the landed
-// block and frees the buffer of the block in registers. The 16-byte piece
-// p of row R sits at slot p ^ swz(R) of the row, swz(R) = (R / (16 / P)) mod
-// P with P = E / 16 pieces per row, so the 16 rows a quarter-wave reads
-// together land on 16 distinct 16-byte bank groups. The loads are issued
-// from inline asm with explicit vmcnt waits: the compiler would otherwise
-// drain every outstanding LDS load before any LDS read and cap the prefetch
-// at one block.
+// 2 NWR waves per workgroup, two per SIMD: wave (wr, wn) owns rows 64 wr ..
+// + 63 of each stage, as two blocks of 32, and the 64 queries of half wn (two
+// 32-query tiles), whose codes are its B operands for the whole chunk (E / 64
+// steps of 32 bytes per tile), so every A operand read from LDS feeds two
+// matrix instructions. Library rows stream through two LDS stage buffers
+// filled by direct global-to-LDS loads (global_load_lds_dwordx4, no staging
+// registers): one load moves 1 KB (64 lanes x 16 bytes), so a stage of BR
+// E-byte rows takes E / 32 loads per wave. The barrier of a stage couples only
+// the waves of one workgroup: with NWR = 1 (two waves) four workgroups share a
+// compute unit and the matrix cores run the waves of the others while one
+// workgroup waits at its barrier. The 16-byte piece p of row R sits at slot
+// p ^ swz(R) of the row, swz(R) = (R / (16 / P)) mod P with P = E / 16 pieces
+// per row, so the 16 rows a quarter-wave reads together land on 16 distinct
+// 16-byte bank groups. The loads are issued from inline asm with explicit
+// vmcnt waits: the compiler would otherwise drain every outstanding LDS load
+// before any LDS read.
 //
-// Epilogue, software-pipelined: two accumulator sets are used in turn. The
-// straight-line part of a step's other work (the hit pre-check of block
-// b - 1, the next loads, the next block's LDS reads, bookkeeping) is placed
-// between block b's matrix instructions, where the wave issues it while the
-// matrix core runs; the hits of block b - 1 follow the matrix instructions.
-// When the wave's 32 rows of the block lie inside every window of its
-// queries (the usual case), one ballot per query tile on each lane's largest
-// score first tells whether the tile has any hit; only such tiles take a
-// compare and a ballot per position (skipped unless some lane hits).
-// Otherwise the block's positions are masked row by row. Hits go to the
-// wave's own LDS list at positions counted from the ballot (no atomics, no
-// global loads), flushed to the per-query global buffers when half full and
-// at the end.
-constexpr int kWaveList = 384;  // LDS entries per wave
+// What bounds it: a step (32 rows x 64 queries of one wave) is 512 cycles of
+// matrix instructions, two waves share a SIMD, and whatever a wave does that
+// is not between two of its own matrix instructions is time in which only the
+// other wave feeds the core. A step takes about 1,600 cycles of both waves'
+// time for 1,024 of matrix instructions; the memory waits are nil. 30,000
+// queries of 500,000 rows (+-500 Da, E = 256, k = 64): 4.03 ms for both passes
+// with a compare, branch and append per register of the flagged tiles (110 KB
+// of code) and 32-row stages; 3.28 with hits found by bits, 3.06 with records,
+// 2.95 with 64-row stages, and 2.65 with the records, the loads and the LDS
+// reads spread between the matrix instructions.
+//
+// Epilogue, software-pipelined: two accumulator sets are used in turn, and
+// the hit pre-check and records of a block are part of the next block's step.
+// One ballot per query tile on each lane's largest score first tells whether
+// the tile has any hit; only then do the lanes that have one write their
+// scores to the wave's own records in LDS, at positions counted from the
+// ballot (no atomics, no global loads). A lane takes one record when they are
+// full or at the end, finds its hits (within the window's rows, where the
+// wave's 32 rows of the block do not lie inside every window of its queries)
+// and appends them to the query's global buffer with one atomic.
+constexpr int kRec = 52;  // records per wave (of at most 64, the lanes of a flush)
 
 // s_waitcnt immediate: vmcnt(n), expcnt and lgkmcnt left at their maxima
 constexpr int waitcnt_vm(int n) { return (n & 15) | ((n >> 4) << 14) | 0x70 | 0xF00; }
@@ -506,20 +562,24 @@ __global__ __launch_bounds__(64 * 2 * NWR, 2) void collect_kernel(
 {
     using namespace gemm;
     constexpr int KS = E / 64;                    // 32 x 32 x 64 steps
-    constexpr int PPK = 16 / KS;                  // epilogue positions per step
     constexpr int P = E / 16;                     // 16-byte pieces per row
     constexpr int RPS = 16 / P;                   // rows sharing one swizzle value
     constexpr int NW = 2 * NWR;                   // waves: NWR row groups x 2 query halves
-    constexpr int BR = 32 * NWR;                  // rows per block step
-    constexpr uint32_t S = 128 / BR;              // block steps per 128-row pass block
-    constexpr int NL = E / 64;                    // direct loads per wave per block
+    constexpr int BR = 64 * NWR;                  // rows per stage: two 32-row blocks of a wave
+    constexpr uint32_t S = 128 / BR;              // stages per 128-row pass block
+    constexpr int NL = E / 32;                    // direct loads per wave per stage
     constexpr float kScoreScale2 = kScoreScale * kScoreScale;
-    constexpr int kBufs = 4;                      // LDS block buffers: kBufs blocks in flight
-    static_assert(KS * PPK == 16 && NL >= 1, "E in {64, 128, 256}");
-    static_assert(NWR == 1 || NWR == 2 || NWR == 4, "32-, 64- or 128-row block steps");
+    constexpr int kBufs = 2;                      // LDS stage buffers
+    static_assert(NL == 2 * KS, "one load per matrix instruction of a step");
+    static_assert(E == 64 || E == 128 || E == 256, "rows of 4, 8 or 16 pieces");
+    static_assert(NWR == 1 || NWR == 2, "64- or 128-row stages");
     __shared__ __attribute__((aligned(16))) uint8_t sA[kBufs][BR * E];
-    __shared__ uint64_t s_key[NW][kWaveList];
-    __shared__ uint8_t s_col[NW][kWaveList];  // query of the entry within the tile
+    __shared__ float4 s_score[NW][4][kRec];  // registers 4 p .. 4 p + 3 of a record's lane
+    // and its row of register 0, its query within the tile and which registers
+    // are candidates (<< 16): four workgroups' buffers and records fill the
+    // compute unit's LDS
+    __shared__ uint2 s_meta[NW][kRec];
+    __shared__ float s_thr[kTileQ];
     // Chunks are fixed row ranges of the sorted library, clipped to the
     // tile's candidate range. Workgroups go to the eight XCDs in turn
     // (workgroup i to XCD i mod 8, each with its own L2): XCD x takes chunks
@@ -542,10 +602,10 @@ __global__ __launch_bounds__(64 * 2 * NWR, 2) void collect_kernel(
     const int t = threadIdx.x, l = t & 63, w = __builtin_amdgcn_readfirstlane(t >> 6);
     const int wr = w % NWR, wn = w / NWR;
     const int64_t p0 = q_begin + tile * kTileQ;  // first sorted query of the tile
-    // This pass's BR-row blocks meeting [c0, c1), in the absolute 128-row
+    // This pass's BR-row stages meeting [c0, c1), in the absolute 128-row
     // blocks of the pass (pass 0 the multiples of kPassStride, pass 1 the
-    // others): block g lies in pass-0 block g / S when g mod G < S. Rows of a
-    // block below c0 lie below every window of the tile (c0 is the chunk's
+    // others): stage g lies in pass-0 block g / S when g mod G < S. Rows of a
+    // stage below c0 lie below every window of the tile (c0 is the chunk's
     // first row or the tile's lowest window start) and are masked like any
     // row outside a window.
     constexpr int64_t G = kPassStride * S;
@@ -554,9 +614,9 @@ __global__ __launch_bounds__(64 * 2 * NWR, 2) void collect_kernel(
     const int64_t n0 = below0(g_hi) - below0(g_lo);
     const int nblk = (int)(pass == 0 ? n0 : (g_hi - g_lo) - n0);
     if (nblk == 0) return;
-    // The pass's blocks in order (32-bit: the library has fewer than 2^31
-    // rows): two walkers, one for the loads (kBufs - 1 blocks ahead) and one
-    // for the epilogue, each stepping to the next block of the pass.
+    // The pass's stages in order (32-bit: the library has fewer than 2^31
+    // rows): two walkers, one for the loads (up to two stages ahead) and one
+    // for the epilogue, each stepping to the next stage of the pass.
     const bool lo_in0 = g_lo % G < (int64_t)S;
     const uint32_t first =
         pass == 0 ? (uint32_t)(lo_in0 ? g_lo : (g_lo / G + 1) * G)
@@ -567,39 +627,40 @@ __global__ __launch_bounds__(64 * 2 * NWR, 2) void collect_kernel(
         return g % (uint32_t)G == 0 ? g + S : g;
     };
     uint32_t g_issue = first, g_epi = first;
-    // the pass's last block in the chunk: the loads issued for block steps
+    // the pass's last stage in the chunk: the loads issued for stages
     // past the end re-read it into a buffer that is never scored, so that
-    // every step waits for the same number of loads, with no branch
+    // the loop needs no branch for them
     const int64_t y = g_hi - 1, ym = y % G;
     const uint32_t g_last = pass == 0 ? (uint32_t)(ym < (int64_t)S ? y : y - ym + S - 1)
                                       : (uint32_t)(ym >= (int64_t)S ? y : y - ym - 1);
 
-    // rows [BR g, + BR) of the block g_issue points to into sA[b % kBufs]:
+    // rows [BR g, + BR) of the stage g_issue points to into sA[st % kBufs]:
     // load x of wave w fills bytes [1024 (NL w + x), + 1024) of the buffer
     // (the destination of a direct load is M0 + 16 x lane), lane l the slot
     // of row R = o / E, o the byte offset of the lane, with the row's piece
     // (slot ^ swz(R)); rows past c1 repeat the last row
-    auto issue = [&](int b) {  // block b, the one g_issue points to
-        const uint32_t mb = (b < nblk ? g_issue : g_last) * (uint32_t)BR;
-        g_issue = next_block(g_issue);
-        const uint32_t base = (uint32_t)(uintptr_t)&sA[b % kBufs][0];
+    auto issue_one = [&](int st, int x) {  // load x of stage st, the one g_issue points to
+        const uint32_t mb = (st < nblk ? g_issue : g_last) * (uint32_t)BR;
+        const uint32_t base = (uint32_t)(uintptr_t)&sA[st % kBufs][0];
         const uint8_t* gbase = lib_emb8 + (size_t)mb * E;  // wave-uniform
         const int last = (int)min((uint32_t)BR - 1u, e1 - 1u - mb);
-#pragma unroll
-        for (int x = 0; x < NL; ++x) {
-            const int ci = w * NL + x;
-            const int o = ci * 1024 + 16 * l;
-            const int R = o / E;
-            const int sl = (o % E) / 16;
-            const int pc = sl ^ ((R / RPS) % P);
-            const uint32_t voff = (uint32_t)(min(R, last) * E + pc * 16);
-            const uint32_t lds = __builtin_amdgcn_readfirstlane(base + (uint32_t)(ci * 1024));
-            asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1"
-                         :
-                         : "v"(voff), "s"(gbase), "s"(lds)
-                         : "memory", "m0");
-        }
+        const int ci = w * NL + x;
+        const int o = ci * 1024 + 16 * l;
+        const int R = o / E;
+        const int sl = (o % E) / 16;
+        const int pc = sl ^ ((R / RPS) % P);
+        const uint32_t voff = (uint32_t)(min(R, last) * E + pc * 16);
+        const uint32_t lds = __builtin_amdgcn_readfirstlane(base + (uint32_t)(ci * 1024));
+        asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1"
+                     :
+                     : "v"(voff), "s"(gbase), "s"(lds)
+                     : "memory", "m0");
+        if (x == NL - 1) g_issue = next_block(g_issue);
     };
+#pragma unroll
+    for (int st = 0; st < 2; ++st)
+#pragma unroll
+        for (int x = 0; x < NL; ++x) issue_one(st, x);
 
     // this lane's two query columns: epilogue state (32-bit rows: the library
     // has fewer than 2^31 rows) and B operands
@@ -621,6 +682,7 @@ __global__ __launch_bounds__(64 * 2 * NWR, 2) void collect_kernel(
             qhi[j] = (uint32_t)hi[qi];
             qthr[j] = thr[p] * kScoreScale2;  // exact: a power of two
         }
+        if (l < 32) s_thr[col[j]] = qthr[j];  // read by this wave alone with one row group
         const uint8_t* qrow = q_sorted8 + (size_t)min(p, q_end - 1) * E + 32 * (l >> 5);
 #pragma unroll
         for (int kk = 0; kk < KS; ++kk) {
@@ -634,7 +696,7 @@ __global__ __launch_bounds__(64 * 2 * NWR, 2) void collect_kernel(
     // 4 kk + 2 (l / 32) + c of the 64-byte step kk
     uint32_t aoff[KS][2];
     {
-        const int R = wr * 32 + (l & 31);
+        const int R = wr * 64 + (l & 31);  // of the stage's first block; + 32 of its second
         const int sw = (R / RPS) % P;
 #pragma unroll
         for (int kk = 0; kk < KS; ++kk)
@@ -664,167 +726,183 @@ __global__ __launch_bounds__(64 * 2 * NWR, 2) void collect_kernel(
     }
     // The B operands are in registers before the pipeline starts, so that no
     // wait for them is left inside the loop, where it would also wait for the
-    // prefetched blocks (vmcnt counts in issue order). The empty asm
-    // statements consume the loaded values here, so the compiler can neither
-    // sink the loads below the prefetch (the restrict-qualified query rows
-    // would let it) nor leave their wait to the loop.
+    // prefetched stages (vmcnt counts in issue order). The empty asm
+    // statements consume the loaded values here, so the compiler cannot leave
+    // their wait to the loop.
 #pragma unroll
     for (int j = 0; j < 2; ++j)
 #pragma unroll
         for (int kk = 0; kk < KS; ++kk) asm volatile("" : "+v"(bq[j][kk]));
     __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));
-    for (int b = 0; b < kBufs; ++b) issue(b);
 
-    // the wave's LDS hit list and its flush to the per-query global buffers
+    // the wave's records and their flush to the per-query global buffers
     uint32_t wcount = 0;  // wave-uniform
     const int64_t qbase = tile * kTileQ;  // pass slot of the tile's first query
-    // one hit straight to the global buffer (score key << 32 | sorted row:
-    // the select kernel turns rows into library indices)
-    auto put = [&](int64_t qs, uint64_t v) {
-        const uint32_t slot = atomicAdd(count + qs * kCountStride, 1u);
-        if (slot < (uint32_t)kCapacity) buf[(size_t)qs * kCapacity + slot] = v;
-    };
-    // the wave's list to the global buffers, four entries per lane at a time
-    // so that their atomics are in flight together
+    // One record per lane: the hits among its 16 scores go to its query's
+    // buffer (score key << 32 | sorted row: the select kernel turns rows into
+    // library indices, so no global load, whose wait would also drain the
+    // prefetch, happens here).
     auto flush = [&]() {
-        for (uint32_t e0 = 0; e0 < wcount; e0 += 256) {
-            uint32_t slot[4];
-            int64_t qs[4];
-            uint64_t v[4];
+        if ((uint32_t)l < wcount) {
+            const uint32_t gl = s_meta[w][l].x, cv = s_meta[w][l].y;
+            const float th = s_thr[cv & 0xFFFFu];
+            uint32_t mk = 0;
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const uint32_t e = e0 + 64 * u + l;
-                qs[u] = e < wcount ? qbase + s_col[w][e] : -1;
-                v[u] = e < wcount ? s_key[w][e] : 0;
-                slot[u] = qs[u] >= 0 ? atomicAdd(count + qs[u] * kCountStride, 1u) : 0xFFFFFFFFu;
+            for (int p = 0; p < 4; ++p) {
+                const float4 f = s_score[w][p][l];
+                mk |= (f.x >= th ? 1u << (4 * p) : 0u) | (f.y >= th ? 2u << (4 * p) : 0u) |
+                      (f.z >= th ? 4u << (4 * p) : 0u) | (f.w >= th ? 8u << (4 * p) : 0u);
             }
-#pragma unroll
-            for (int u = 0; u < 4; ++u)
-                if (slot[u] < (uint32_t)kCapacity) buf[(size_t)qs[u] * kCapacity + slot[u]] = v[u];
+            mk &= cv >> 16;
+            if (mk != 0) {
+                const int64_t qs = qbase + (cv & 0xFFFFu);
+                uint32_t slot = atomicAdd(count + qs * kCountStride, (uint32_t)__popc(mk));
+                for (; mk != 0; mk &= mk - 1u, ++slot) {
+                    const uint32_t r = (uint32_t)__builtin_ctz(mk);
+                    const float sc = ((const float*)&s_score[w][r >> 2][l])[r & 3u];
+                    if (slot < (uint32_t)kCapacity)
+                        buf[(size_t)qs * kCapacity + slot] =
+                            ((uint64_t)fkey(sc * (1.f / kScoreScale2)) << 32) |
+                            (uint64_t)(gl + 8u * (r >> 2) + (r & 3u));
+                }
+            }
         }
         wcount = 0;
-    };
-    // append the hits of one position of query tile j (m: the wave's hit
-    // mask, uniform; sc: 256 times the score)
-    auto append = [&](uint64_t m, bool ok, float sc, uint32_t g, int j) {
-        const uint64_t v = ((uint64_t)fkey(sc * (1.f / kScoreScale2)) << 32) | (uint64_t)g;
-        if (wcount + 64 <= kWaveList) {
-            // the sorted row: its library index is looked up by the select
-            // kernel, so no global load (and no vmcnt wait, which would also
-            // drain the prefetch) happens in this kernel
-            if (ok) {
-                const uint32_t pos =
-                    wcount + __builtin_amdgcn_mbcnt_hi(
-                                 (uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
-                s_key[w][pos] = v;
-                s_col[w][pos] = (uint8_t)col[j];
-            }
-            wcount += (uint32_t)__popcll(m);
-        } else if (ok) {  // list full inside a dense block: direct
-            put(qbase + col[j], v);
-        }
     };
 
     // Accumulator register r of query tile j holds matrix row
     // i = 8 (r / 4) + 4 (l / 32) + r % 4 of the wave's tile, library row
-    // wb + i with wb = the block's first row + 32 wr: gl + roff(r) with
-    // gl = wb + 4 (l / 32).
-    auto roff = [](int r) -> uint32_t { return (uint32_t)(8 * (r >> 2) + (r & 3)); };
+    // wb + i with wb = the block's first row + 32 wr: gl + 8 (r / 4) + r % 4
+    // with gl = wb + 4 (l / 32).
     // The scores of a scored block are examined while the next block's
     // matrix instructions run: gl = the row of accumulator register 0 in this
     // lane, fast = every row of the wave lies inside every window of its
-    // queries. The pre-check (fast case): which query tiles have a hit at
-    // all, from the largest of each lane's 16 scores (one query, 16 rows)
-    // against its threshold, one ballot per tile; straight-line code, so it
-    // can sit between matrix instructions.
-    auto precheck = [&](const f32x16(&a)[2], uint64_t (&hit)[2]) {
+    // queries. The pre-check: which query tiles have a score at or above a
+    // threshold at all, from the largest of each lane's 16 scores (one query,
+    // 16 rows), one ballot per tile; straight-line code, so it can sit between
+    // matrix instructions.
+    auto above = [&](const f32x16& a, int j) { return max16(a) >= qthr[j]; };
+    // The flagged tiles: every lane whose largest score reaches its threshold
+    // (one or two of 64 as a rule) writes its 16 scores to the wave's records,
+    // and the flush looks for the hits in up to kRec records at a time, a lane
+    // each. To look for them here, where most lanes have none, took 70 vector
+    // operations a flagged tile, as long as its matrix instructions; and what
+    // follows a step's matrix instructions, rather than standing between them,
+    // is time in which this wave's matrix core waits for the other wave.
+    auto put = [&](const f32x16& a, uint32_t pos, uint32_t gl, uint32_t cv) {
 #pragma unroll
-        for (int j = 0; j < 2; ++j) hit[j] = __ballot(max16(a[j]) >= qthr[j]);
+        for (int p = 0; p < 4; ++p)
+            s_score[w][p][pos] =
+                make_float4(a[4 * p], a[4 * p + 1], a[4 * p + 2], a[4 * p + 3]);
+        s_meta[w][pos] = make_uint2(gl, cv);
     };
-    // the hits themselves: in the fast case a compare and a ballot per
-    // position of the tiles the pre-check flagged, else per-row masks
+    auto rank_in = [](uint64_t m) {
+        return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
+                                         __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+    };
+    // the general case: records that do not fit, rows outside windows
     auto examine = [&](const f32x16(&a)[2], uint32_t gl, bool fast, const uint64_t (&hit)[2]) {
-        if (fast) {
 #pragma unroll
-            for (int j = 0; j < 2; ++j) {
-                if (hit[j] == 0) continue;  // one test per tile, not per position
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const float sc = a[j][r];
-                    const uint64_t m = __ballot(sc >= qthr[j]);
-                    if (m != 0) append(m, sc >= qthr[j], sc, gl + roff(r), j);
-                }
+        for (int j = 0; j < 2; ++j) {
+            if (hit[j] == 0) continue;  // one test per tile, not per position
+            uint32_t cv = 0xFFFF0000u | (uint32_t)col[j];
+            if (!fast) {
+                // rows gl + [x0, x1) of the 32 from gl on are candidates; the
+                // lane's registers are rows 0-3, 8-11, 16-19 and 24-27
+                const uint32_t x1 = min(max(min(qhi[j], e1), gl) - gl, 32u);
+                const uint32_t x0 = min(max(qlo[j], gl) - gl, 32u);
+                const uint32_t in = (uint32_t)((1ull << x1) - 1) & ~(uint32_t)((1ull << x0) - 1);
+                cv = (uint32_t)col[j] | (in & 0xFu) << 16 | (in & 0xF00u) << 12 |
+                     (in & 0xF0000u) << 8 | (in & 0xF000000u) << 4;
             }
-        } else {  // window or chunk edge inside the wave's rows: per-row masks
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const uint32_t g = gl + roff(r);
-#pragma unroll
-                for (int j = 0; j < 2; ++j) {
-                    const float sc = a[j][r];
-                    const bool ok = sc >= qthr[j] && g < e1 && g >= qlo[j] && g < qhi[j];
-                    const uint64_t m = __ballot(ok);
-                    if (m != 0) append(m, ok, sc, g, j);
-                }
+            const uint32_t n = (uint32_t)__popcll(hit[j]), rank = rank_in(hit[j]);
+            const bool mine = (hit[j] >> l) & 1u;
+            for (uint32_t off = 0;;) {  // records written; a second round if they fill up
+                const uint32_t pos = wcount + rank - off;
+                if (mine && rank >= off && pos < (uint32_t)kRec) put(a[j], pos, gl, cv);
+                const uint32_t some = min(n - off, (uint32_t)kRec - wcount);
+                wcount += some;
+                off += some;
+                if (off == n) break;
+                flush();
             }
         }
     };
-    auto block_info = [&](uint32_t& gl, bool& fast) {  // the block g_epi points to
-        const uint32_t wb = g_epi * (uint32_t)BR + wr * 32;
-        g_epi = next_block(g_epi);
+    // block h of the stage g_epi points to
+    auto block_info = [&](int h, uint32_t& gl, bool& fast) {
+        const uint32_t wb = g_epi * (uint32_t)BR + wr * 64 + 32 * h;
+        if (h) g_epi = next_block(g_epi);
         gl = wb + 4u * (uint32_t)(l >> 5);
         fast = wb >= wlo && wb + 32 <= whi;
     };
-    // block b's A operands (this lane's row, all E / 64 steps) from LDS
-    auto read_a = [&](int b, v8i32(&av)[KS]) {
-        const uint8_t* Ab = sA[b % kBufs];
-#pragma unroll
-        for (int kk = 0; kk < KS; ++kk) {
-            const uint4 u0 = *(const uint4*)(Ab + aoff[kk][0]);
-            const uint4 u1 = *(const uint4*)(Ab + aoff[kk][1]);
-            av[kk] = v8i32{(int)u0.x, (int)u0.y, (int)u0.z, (int)u0.w,
-                           (int)u1.x, (int)u1.y, (int)u1.z, (int)u1.w};
-        }
+    // step kk of the A operands (this lane's row) of block h of a stage
+    auto read_a = [&](int st, int h, int kk, v8i32(&av)[KS]) {
+        const uint8_t* Ab = sA[st % kBufs] + 32 * h * E;
+        const uint4 u0 = *(const uint4*)(Ab + aoff[kk][0]);
+        const uint4 u1 = *(const uint4*)(Ab + aoff[kk][1]);
+        av[kk] = v8i32{(int)u0.x, (int)u0.y, (int)u0.z, (int)u0.w,
+                       (int)u1.x, (int)u1.y, (int)u1.z, (int)u1.w};
     };
 
-    // Software pipeline, one step per block b: block b's A operands are in
-    // registers (read from LDS during step b - 1), block b + 1 sits in LDS,
-    // blocks b + 2 and b + 3 are in flight. Step b waits for block b + 1 (own
-    // loads, then the barrier for everyone's; the barrier also means every
-    // wave has its block-b operands, so block b's buffer is free), issues the
-    // loads of block b + 4 into that buffer and runs block b's matrix
-    // instructions with the rest of the step's work placed between them:
-    // the pre-check of block b - 1, the loads, the LDS reads of block b + 1
-    // and the block bookkeeping. A wave keeps issuing while its matrix
-    // instruction runs, so that work is hidden behind the matrix core; the
-    // scheduling barriers keep the compiler from regrouping it. The hits of
-    // block b - 1 (branches, rare) follow the matrix instructions. Two
-    // accumulator and two operand sets are used in turn.
-    auto step = [&](int b, f32x16(&cur)[2], const f32x16(&prev)[2], const v8i32(&avc)[KS],
-                    v8i32(&avn)[KS], uint32_t glp, bool fastp, uint32_t& glc, bool& fastc) {
-        // this wave's LDS reads of block b are complete before the barrier,
-        // so no wave can refill block b's buffer under them
-        __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0((kBufs - 2) * NL));
-        __syncthreads();
+    // Software pipeline, one step per 32-row block, two per stage: a block's A
+    // operands are in registers (read from LDS during the step before), the
+    // stage after its own is in flight. The second block's step first waits
+    // for the next stage (own loads, then the barrier for everyone's; the
+    // barrier also means that every wave has this stage's operands, so its
+    // buffer is free) and issues the loads of the stage after next into the
+    // free buffer; the first block's step has no barrier. The rest of a step's
+    // work is placed between its matrix instructions: the pre-check of the
+    // block before, the loads, the LDS reads of the next block and the block
+    // bookkeeping. A wave keeps issuing while its matrix instruction runs, so
+    // that work is hidden behind the matrix core; the scheduling barriers keep
+    // the compiler from regrouping it. The records of the block before
+    // (branches) follow the matrix instructions. Two accumulator and two
+    // operand sets are used in turn.
+    auto step = [&](int st, auto half, f32x16(&cur)[2], const f32x16(&prev)[2],
+                    const v8i32(&avc)[KS], v8i32(&avn)[KS], uint32_t glp, bool fastp,
+                    uint32_t& glc, bool& fastc) {
+        constexpr int h = decltype(half)::value;
+        if constexpr (h == 1) {
+            __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(0));
+            __syncthreads();
+        }
         uint64_t hit[2];
-        // work item t runs after matrix instruction min(at[t], 2 KS - 1); the
-        // LDS reads of block b + 1 come late, when most of block b's operand
-        // registers are free again
-        constexpr int at[5] = {0, 1, 2, 3, 5};
+        bool up[2], fits = false;
+        uint32_t at0 = 0, at1 = 0;
+        // Work item t runs after matrix instruction min(at[t], 2 KS - 1), and
+        // one load of the stage after each: about as much as an instruction's
+        // 64 cycles hold, so that the next one is not late where the other
+        // wave has none to run.
+        constexpr int kWork = 5 + KS;
+        constexpr int at[9] = {0, 1, 2, 3, 5, 3, 4, 5, 6};
         auto work = [&](int t) {
-            if (t == 0) hit[0] = __ballot(max16(prev[0]) >= qthr[0]);
-            if (t == 1) hit[1] = __ballot(max16(prev[1]) >= qthr[1]);
-            if (t == 2) issue(b + kBufs);
-            if (t == 3) block_info(glc, fastc);
-            if (t == 4) read_a(b + 1, avn);
+            if (t < 2) {
+                up[t] = above(prev[t], t);
+                hit[t] = __ballot(up[t]);
+            }
+            if (t == 1) {
+                const uint32_t n0 = (uint32_t)__popcll(hit[0]), n1 = (uint32_t)__popcll(hit[1]);
+                // wave-uniform (in scalar registers)
+                fits = __builtin_amdgcn_readfirstlane(fastp && wcount + n0 + n1 <= (uint32_t)kRec);
+                at0 = wcount;
+                at1 = wcount + n0;
+                wcount = __builtin_amdgcn_readfirstlane(fits ? at1 + n1 : wcount);
+            }
+            if (t == 2 || t == 3) {
+                const int j = t - 2;
+                const uint32_t pos = (j ? at1 : at0) + rank_in(hit[j]);
+                if (up[j] && fits) put(prev[j], pos, glp, 0xFFFF0000u | (uint32_t)col[j]);
+            }
+            if (t == 4) block_info(h, glc, fastc);
+            if (t > 4) read_a(st + h, 1 - h, t - 5, avn);
         };
-        constexpr int kWork = 5;
 #pragma unroll
         for (int i = 0; i < 2 * KS; ++i) {
             const int kk = i >> 1, j = i & 1;
             cur[j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(
                 avc[kk], bq[j][kk], kk == 0 ? f32x16{0} : cur[j], 0, 0, 0, 0, 0, 0);
             __builtin_amdgcn_sched_barrier(0);
+            if (h == 1) issue_one(st + 2, i);
 #pragma unroll
             for (int t = 0; t < kWork; ++t)
                 if (min(at[t], 2 * KS - 1) == i) {
@@ -832,8 +910,8 @@ __global__ __launch_bounds__(64 * 2 * NWR, 2) void collect_kernel(
                     __builtin_amdgcn_sched_barrier(0);
                 }
         }
-        if (b > 0) examine(prev, glp, fastp, hit);
-        if (wcount > kWaveList / 2) flush();  // wave-uniform
+        // (the first step's prev is no block's scores)
+        if (!fits && (hit[0] | hit[1]) != 0 && (h == 1 || st > 0)) examine(prev, glp, fastp, hit);
     };
 
     f32x16 accA[2], accB[2];
@@ -842,23 +920,16 @@ __global__ __launch_bounds__(64 * 2 * NWR, 2) void collect_kernel(
     v8i32 avA[KS], avB[KS];
     uint32_t glA = 0, glB = 0;
     bool fastA = false, fastB = false;
-    // block 0 landed (the loads of blocks 1 .. kBufs - 1 stay in flight)
-    __builtin_amdgcn_s_waitcnt(waitcnt_vm((kBufs - 1) * NL));
-    __syncthreads();
-    read_a(0, avA);
-    for (int b = 0; b < nblk; b += 2) {
-        step(b, accA, accB, avA, avB, glB, fastB, glA, fastA);
-        if (b + 1 < nblk) step(b + 1, accB, accA, avB, avA, glA, fastA, glB, fastB);
+    __syncthreads();  // stages 0 and 1 landed
+#pragma unroll
+    for (int kk = 0; kk < KS; ++kk) read_a(0, 0, kk, avA);
+    for (int st = 0; st < nblk; ++st) {
+        step(st, std::integral_constant<int, 0>{}, accA, accB, avA, avB, glB, fastB, glA, fastA);
+        step(st, std::integral_constant<int, 1>{}, accB, accA, avB, avA, glA, fastA, glB, fastB);
     }
     {  // the last block's hits
-        uint64_t hit[2];
-        if (nblk & 1) {
-            precheck(accA, hit);
-            examine(accA, glA, fastA, hit);
-        } else {
-            precheck(accB, hit);
-            examine(accB, glB, fastB, hit);
-        }
+        const uint64_t hit[2] = {__ballot(above(accB[0], 0)), __ballot(above(accB[1], 1))};
+        examine(accB, glB, fastB, hit);
     }
     flush();
     // the re-reads issued past the end land before the LDS is released
@@ -914,8 +985,13 @@ __global__ __launch_bounds__(kThreads) void select_kernel(
         } else {
             constexpr int kPer = kCapacity / kThreads;
             uint64_t kv[kPer];  // this thread's keys, in registers
+            // A few hundred keys as a rule: only the steps that hold any (at
+            // k = 64 and 480 keys, all 32 steps in every round took 28 ns a
+            // query instead of 8).
+            const int used = (n + kThreads - 1) / kThreads;
 #pragma unroll
             for (int j = 0; j < kPer; ++j) {
+                if (j >= used) break;
                 const int i = (int)threadIdx.x + j * kThreads;
                 kv[j] = i < n ? keys[i] : 0ull;
             }
@@ -926,6 +1002,7 @@ __global__ __launch_bounds__(kThreads) void select_kernel(
                 __syncthreads();
 #pragma unroll
                 for (int j = 0; j < kPer; ++j) {
+                    if (j >= used) break;
                     const uint32_t h = (uint32_t)(kv[j] >> 32);
                     if ((int)threadIdx.x + j * kThreads < n && (h & mask) == prefix)
                         atomicAdd(&hist[(h >> shift) & 255u], 1u);
@@ -953,6 +1030,7 @@ __global__ __launch_bounds__(kThreads) void select_kernel(
                     __syncthreads();
 #pragma unroll
                     for (int j = 0; j < kPer; ++j) {
+                        if (j >= used) break;
                         if ((int)threadIdx.x + j * kThreads < n &&
                             (uint32_t)(kv[j] >> 32) == prefix) {
                             const uint32_t lw = (uint32_t)lib_key(kv[j]);
@@ -975,6 +1053,7 @@ __global__ __launch_bounds__(kThreads) void select_kernel(
             __syncthreads();
 #pragma unroll
             for (int j = 0; j < kPer; ++j) {
+                if (j >= used) break;
                 const uint32_t h = (uint32_t)(kv[j] >> 32);
                 if ((int)threadIdx.x + j * kThreads >= n || h < prefix) continue;
                 const uint64_t key = lib_key(kv[j]);
