@@ -707,11 +707,10 @@ homs_status run_search(homs_ctx* c, int64_t nq, const uint32_t* d_q_hv, const do
     HIP_TRY(c, homs::launch_query_plan(c, nq, d_q_pmz, d_q_charge, win->kind, win->value,
                                        engine, d_q_hv, tile, w, s),
             "query plan kernels");
-    homs::TilePlan plan;
     hipEvent_t e1 = mark();
     if (engine == HOMS_ENGINE_POPCOUNT)
         HIP_TRY(c, homs::launch_search_popcount(c, nq, d_q_hv, w.qperm, w.lo, w.hi, w.tile_lo,
-                                                w.tile_hi, plan, w.keys, s),
+                                                w.tile_hi, w.keys, s),
                 "search kernel");
     else
         HIP_TRY(c, homs::launch_search_mfma(c, engine == HOMS_ENGINE_MFMA_I8   ? 0
@@ -720,6 +719,8 @@ homs_status run_search(homs_ctx* c, int64_t nq, const uint32_t* d_q_hv, const do
                                             nq, d_q_hv,
                                             w.qperm, w.lo, w.hi, w.tile_lo, w.tile_hi, w.qoff,
                                             w.keys,
+                                            win->value <= (win->kind == HOMS_TOL_PPM ? 1000.0
+                                                                                     : 1.0),
                                             s),
                 "MFMA search kernel");
     hipEvent_t e2 = mark();

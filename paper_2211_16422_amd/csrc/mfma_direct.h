@@ -184,7 +184,11 @@ __device__ __forceinline__ void tile_rows_staged(uint32_t words, int64_t nq,
   constexpr int kBuf = (MR + NQ) * kRowBytes;
   static_assert(2 * kBuf <= kStageBytes, "stage buffers");
   const uint32_t D = words * 32;
-  const int t = threadIdx.x, l = t & 63, w = t >> 6, wr = w % WR, wq = w / WR;
+  // opaque, so that nothing derived from it is kept in registers across the
+  // tiles of a workgroup that takes several
+  int t = threadIdx.x;
+  asm volatile("" : "+v"(t));
+  const int l = t & 63, w = __builtin_amdgcn_readfirstlane(t >> 6), wr = w % WR, wq = w / WR;
   const int h = l >> 5;
   char* const lds = stage_lds();
   uint32_t* const s_orig = orig_lds();

@@ -38,8 +38,8 @@ inline uint32_t blocks_for(int64_t n) { return (uint32_t)((n + kThreads - 1) / k
 // same distances). A tile is narrow when ratio x the sum of its windows is at
 // most union x tile, and its largest window leaves the waves evenly loaded.
 // The ratios are where both ways took the same time (D = 8,192): fp4, 256-query
-// tiles: 100,000 queries over 2M rows, scan 2.34 / 3.57 ms at +-50 / 100 ppm
-// against 3.17 ms at either (windows of 1/36 of the union at the crossing);
+// tiles: 100,000 queries over 2M rows, scan 1.76 ms at +-50 ppm against 2.25 ms
+// of tiles at 75 and 100 (windows of 1/36 of the union at the crossing);
 // fp8 there 6.0 / 10.8 ms at 200 / 400 ppm against 5.1 / 5.3; small tiles:
 // 2,000 queries, scan 0.43 / 1.55 ms at 200 / 1,000 ppm against 0.70; popcount:
 // 30,000 queries over 400,000 rows, scan 0.53 / 1.38 ms at 200 / 800 ppm

@@ -43,15 +43,21 @@ namespace {
 // to the eight XCDs in turn (workgroup i to XCD i mod 8), and each XCD has its
 // own L2. Work items are (query tile, library chunk) pairs on absolute chunk
 // boundaries; they are grouped into patches of adjacent tiles x adjacent
-// chunks (4 x 8 where there are that many), and consecutive patches go to
-// consecutive XCDs, so the 32 workgroups an XCD runs side by side share 8
-// chunks of library rows and 4 tiles of query rows (about 3 MB per 256-row
-// step) in their L2.
+// chunks (8 x 4 where there are that many), and consecutive patches go to
+// consecutive XCDs, so the 32 workgroups an XCD runs side by side share 4
+// chunks of library rows and 8 tiles of query rows (about 3 MB per 256-row
+// step) in their L2. The patches of a window's share are few (200 for 16,003
+// queries of 600,002 rows with 2,048-row chunks), so their sizes also decide
+// how evenly the XCDs are loaded: 16,003 queries 8.44 ms with 4 x 8 patches
+// and 2,048-row chunks, 7.89 ms with 8 x 4 and 1,024; 100,000 queries of
+// 2,000,000 rows 157.0 ms with 4 x 8 and 4,096, 152.3 ms with 8 x 4 and 2,048
+// (152.2 with 8 x 2, which is 2% slower at 8,000 to 16,000 queries).
 constexpr int kXcds = 8;
 struct WorkMap {
   uint32_t n_tiles, n_chunks, chunk;          // chunk: library rows per item
   uint32_t patch_tiles, patch_chunks;         // items of a patch
   uint32_t chunk_patches, patches;            // patches along the library, in all
+  uint32_t items;                             // kXcds rounds of whole patches
 };
 
 // wave layout of the one-shot kernels
@@ -68,23 +74,49 @@ __global__ __launch_bounds__(DirectLayout::kThreads, 1) void mfma_direct_kernel(
     const int32_t* __restrict__ qoff, const float* __restrict__ rowk,
     uint64_t* __restrict__ keys, WorkMap map)
 {
-  const uint32_t wg = blockIdx.x;
-  const uint32_t per = map.patch_tiles * map.patch_chunks;
-  const uint32_t slot = wg / kXcds;  // position in this XCD's sequence
-  const uint32_t patch = (slot / per) * kXcds + wg % kXcds;
-  if (patch >= map.patches) return;
-  const uint32_t local = slot % per;
-  const uint32_t tile =
-      (patch / map.chunk_patches) * map.patch_tiles + local / map.patch_chunks;
-  const uint32_t cidx =
-      (patch % map.chunk_patches) * map.patch_chunks + local % map.patch_chunks;
-  if (tile >= map.n_tiles || cidx >= map.n_chunks) return;
-  const int64_t c0 = (int64_t)cidx * map.chunk;
-  const int64_t a64 = max(c0, tlo[tile]);
-  const int64_t b64 = min(c0 + map.chunk, thi[tile]);
-  if (a64 >= b64) return;
-  mfd::tile_rows<F, DirectLayout>(words, nq, q_hv, qperm, lo, hi, tile, (uint32_t)a64,
-                                        (uint32_t)b64, lib, orig, qoff, rowk, keys);
+  // the rows [*a, *b) of an item (none: a >= b)
+  auto rows_of = [&](uint32_t item, uint32_t* tile, int64_t* a, int64_t* b) {
+    const uint32_t per = map.patch_tiles * map.patch_chunks;
+    const uint32_t slot = item / kXcds;  // position in its XCD's sequence
+    const uint32_t patch = (slot / per) * kXcds + item % kXcds;
+    const uint32_t local = slot % per;
+    *tile = (patch / map.chunk_patches) * map.patch_tiles + local / map.patch_chunks;
+    const uint32_t cidx =
+        (patch % map.chunk_patches) * map.patch_chunks + local % map.patch_chunks;
+    *a = *b = 0;
+    if (patch >= map.patches || *tile >= map.n_tiles || cidx >= map.n_chunks) return;
+    const int64_t c0 = (int64_t)cidx * map.chunk;
+    *a = max(c0, tlo[*tile]);
+    *b = min(c0 + map.chunk, thi[*tile]);
+  };
+  // Item blockIdx.x, + gridDim.x, ...: one where the grid covers them all;
+  // otherwise each thread looks at one, and those with candidates are listed.
+  __shared__ uint32_t s_items[DirectLayout::kThreads], s_n;
+  for (uint64_t i0 = blockIdx.x; i0 < map.items;
+       i0 += (uint64_t)gridDim.x * DirectLayout::kThreads) {
+    uint32_t n = 1;
+    if (gridDim.x < map.items) {
+      if (threadIdx.x == 0) s_n = 0;
+      __syncthreads();
+      const uint64_t item = i0 + (uint64_t)threadIdx.x * gridDim.x;
+      uint32_t tile;
+      int64_t a = 0, b = 0;
+      if (item < map.items) rows_of((uint32_t)item, &tile, &a, &b);
+      if (a < b) s_items[atomicAdd(&s_n, 1u)] = (uint32_t)item;
+      __syncthreads();
+      n = s_n;
+    }
+    for (uint32_t k = 0; k < n; ++k) {
+      uint32_t tile;
+      int64_t a, b;
+      rows_of(gridDim.x < map.items ? __builtin_amdgcn_readfirstlane(s_items[k]) : blockIdx.x,
+              &tile, &a, &b);
+      if (a < b)
+        mfd::tile_rows<F, DirectLayout>(words, nq, q_hv, qperm, lo, hi, tile, (uint32_t)a,
+                                        (uint32_t)b, lib, orig, qoff, rowk, keys);
+    }
+    __syncthreads();  // the list is read
+  }
 }
 
 // ---- few queries ------------------------------------------------------------
@@ -371,10 +403,11 @@ __global__ __launch_bounds__(256) void fp4_row_consts_kernel(int64_t n, int64_t 
 // Library rows per workgroup: the largest power of two up to kMfChunk (the
 // stream kernel: kStreamChunk), and at least 256, that makes `items` (tile,
 // chunk) items, of which a window's share holds candidates; fewer leave
-// compute units idle (16,003 queries, 600,002 rows, D = 8,192: 9.76 ms with
-// 4,096-row chunks, 9.28 ms with 1,024-row ones).
-constexpr int64_t kMfChunk = 4096, kStreamChunk = 8192;
-constexpr int64_t kMfItems = 16384;
+// compute units idle (16,003 queries, 600,002 rows, D = 8,192, 8 x 4 patches:
+// 8.19 ms with 16,384 items, 7.89 ms with 24,576, 7.91 ms with 49,152).
+constexpr int64_t kMfChunk = 2048, kStreamChunk = 8192;
+constexpr int64_t kMfItems = 24576;
+constexpr int64_t kShortGrid = 1024;  // workgroups of a call of short windows (of kXcds rounds)
 int64_t chunk_rows(int64_t n_tiles, int64_t n, int64_t most, int64_t items)
 {
     int64_t chunk = most;
@@ -422,7 +455,7 @@ hipError_t launch_fp4_query_offsets(const homs_ctx* c, int64_t nq, const uint32_
 hipError_t launch_search_mfma(const homs_ctx* c, int fmt, int64_t nq, const uint32_t* q_hv,
                               const uint32_t* qperm, const int64_t* lo, const int64_t* hi,
                               const int64_t* tile_lo, const int64_t* tile_hi, const int32_t* qoff,
-                              uint64_t* keys, hipStream_t s)
+                              uint64_t* keys, bool short_windows, hipStream_t s)
 {
     if (nq <= 0 || c->lib.n <= 0) return hipSuccess;
     const int tile = search_mfma_tile(c, nq);
@@ -457,8 +490,8 @@ hipError_t launch_search_mfma(const homs_ctx* c, int fmt, int64_t nq, const uint
     m.n_tiles = (uint32_t)n_tiles;
     m.n_chunks = (uint32_t)n_chunks;
     m.chunk = (uint32_t)chunk;
-    m.patch_tiles = (uint32_t)std::min<int64_t>(4, n_tiles);
-    m.patch_chunks = n_tiles * n_chunks >= 32 * 64 ? 8 : 1;
+    m.patch_tiles = (uint32_t)std::min<int64_t>(8, n_tiles);
+    m.patch_chunks = n_tiles * n_chunks >= 32 * 64 ? 4 : 1;
     const int64_t tile_groups = (n_tiles + m.patch_tiles - 1) / m.patch_tiles;
     m.chunk_patches = (uint32_t)((n_chunks + m.patch_chunks - 1) / m.patch_chunks);
     const int64_t patches = tile_groups * m.chunk_patches;
@@ -467,8 +500,17 @@ hipError_t launch_search_mfma(const homs_ctx* c, int fmt, int64_t nq, const uint
         (patches + kXcds - 1) / kXcds * kXcds * m.patch_tiles * m.patch_chunks;
     if (blocks > 0x7FFFFFFF) return hipErrorInvalidConfiguration;
     m.patches = (uint32_t)patches;
+    m.items = (uint32_t)blocks;
+    // A workgroup of an item without candidates costs 2 ns of dispatch: with
+    // windows of a few dozen rows hardly any item has some (20,001 queries of
+    // 1,000,000 rows: 39,000 items, 84 us of nothing else). A fixed grid whose
+    // workgroups first list their items with candidates, one item a thread,
+    // passes over them in 5 us; where most items hold work, one workgroup each
+    // is the better balanced.
+    const uint32_t grid =
+        (uint32_t)(short_windows ? std::min<int64_t>(blocks, kShortGrid) : blocks);
     auto go = [&](auto kern) {
-        kern<<<(uint32_t)blocks, DirectLayout::kThreads, 0, s>>>(
+        kern<<<grid, DirectLayout::kThreads, 0, s>>>(
             c->words, nq, q_hv, qperm, lo, hi, tile_lo, tile_hi, c->lib.hv, c->lib.orig,
             f4 ? qoff : nullptr, f4 ? c->lib.rowk : nullptr, keys, m);
     };

@@ -105,9 +105,8 @@ hipError_t launch_tile_bounds(int64_t nq, const uint32_t* qperm, const int64_t* 
 hipError_t launch_search_popcount(const homs_ctx* c, int64_t nq, const uint32_t* q_hv,
                                   const uint32_t* qperm, const int64_t* lo, const int64_t* hi,
                                   const int64_t* tile_lo, const int64_t* tile_hi,
-                                  const TilePlan& plan, uint64_t* keys, hipStream_t s)
+                                  uint64_t* keys, hipStream_t s)
 {
-    (void)plan;
     const int64_t n_tiles = (nq + kTile - 1) / kTile;
     if (n_tiles <= 0 || c->lib.n <= 0) return hipSuccess;
     // enough (tile, chunk) items to fill the chip evenly (2,001 queries,
