@@ -281,19 +281,16 @@ __device__ __forceinline__ U4 at_least(const U4 (&c)[P], uint32_t t)
     return r;
 }
 
+// adds the peaks [a, b) to the counters and the number of those in range to n_ok
 template <int P>
-__device__ __forceinline__ U4 encode_one(const uint4* __restrict__ id, const uint4* __restrict__ lv,
-                                         uint32_t w4, uint32_t lane, int64_t a, int64_t b,
-                                         const int32_t* __restrict__ bin,
-                                         const uint8_t* __restrict__ level, int64_t n_bins,
-                                         uint32_t n_levels, uint32_t* __restrict__ err)
+__device__ __forceinline__ void count_peaks(U4 (&c)[P], uint32_t& n_ok,
+                                            const uint4* __restrict__ id,
+                                            const uint4* __restrict__ lv, uint32_t w4,
+                                            uint32_t lane, int64_t a, int64_t b,
+                                            const int32_t* __restrict__ bin,
+                                            const uint8_t* __restrict__ level, int64_t n_bins,
+                                            uint32_t n_levels, uint32_t* __restrict__ err)
 {
-    U4 c[P];
-#pragma unroll
-    for (int k = 0; k < P; ++k)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) c[k].v[e] = 0u;
-    uint32_t n_ok = 0;
     bool bad = false;
     // one group of eight peaks from p on; with `partial`, the slots from b on
     // re-read peak b - 1 and are masked off. A peak out of range adds nothing
@@ -324,6 +321,28 @@ __device__ __forceinline__ U4 encode_one(const uint4* __restrict__ id, const uin
     for (; p + 8 <= b; p += 8) group(p, false);
     if (p < b) group(p, true);
     if (bad && lane == 0) atomicOr(err, kErrRange);
+}
+
+template <int P>
+__device__ __forceinline__ void clear(U4 (&c)[P])
+{
+#pragma unroll
+    for (int k = 0; k < P; ++k)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) c[k].v[e] = 0u;
+}
+
+template <int P>
+__device__ __forceinline__ U4 encode_one(const uint4* __restrict__ id, const uint4* __restrict__ lv,
+                                         uint32_t w4, uint32_t lane, int64_t a, int64_t b,
+                                         const int32_t* __restrict__ bin,
+                                         const uint8_t* __restrict__ level, int64_t n_bins,
+                                         uint32_t n_levels, uint32_t* __restrict__ err)
+{
+    U4 c[P];
+    clear<P>(c);
+    uint32_t n_ok = 0;
+    count_peaks<P>(c, n_ok, id, lv, w4, lane, a, b, bin, level, n_bins, n_levels, err);
     return at_least<P>(c, (n_ok + 1u) / 2u);
 }
 
@@ -355,10 +374,7 @@ __device__ __forceinline__ U4 encode_one_lsh(const uint4* __restrict__ id, uint3
                                              uint32_t n_levels, uint32_t* __restrict__ err)
 {
     U4 c[P];
-#pragma unroll
-    for (int k = 0; k < P; ++k)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) c[k].v[e] = 0u;
+    clear<P>(c);
     uint32_t W = 0;
     for (int64_t p = a; p < b; ++p) {
         const int32_t bi = bin[p];
@@ -449,6 +465,76 @@ __global__ __launch_bounds__(256) void encode_kernel(EncodeArgs x)
     }
 }
 
+// Few spectra: a workgroup each. Its groups of D/128 lanes take a share of the
+// peaks each and add their counters up in LDS, in a tree: a share is a chain
+// of one or two rounds of (bin, row) loads where a whole spectrum is six, and
+// the chains are what a call of few spectra takes. One launch for all size
+// classes (spectra of 256 peaks and more by the first group alone).
+// Measured per call (top 50, then 150 peaks; the three launches by size class
+// in brackets): 64 spectra at D = 8,192 8.5 (13.8) and 8.9 (33.7) us, 512 8.4
+// (15.0) and 13.3 (50.7), 1,024 15.7 (17.6) and 24.4 (52.9); 2,048 27.8 (22.0)
+// and 40.1 (60.3); at D = 2,048 1,024 11.3 (14.0) and 14.5 (36.1).
+constexpr int kFewPlanes = 8;
+constexpr int64_t kFewSpectra = 1024;
+__global__ __launch_bounds__(256) void encode_few_kernel(EncodeArgs x)
+{
+    __shared__ uint4 s_c[kFewPlanes][256];
+    __shared__ uint32_t s_ok[256];
+    const int64_t s = blockIdx.x;
+    const uint32_t t = threadIdx.x, sub = t / x.w4, lane = t - sub * x.w4;
+    const int64_t a = x.off[s], b = x.off[s + 1], np = b - a;
+    const int64_t row = x.slot ? (int64_t)x.slot[s] : s;
+    U4 r;
+    if (np >= 256) {  // uniform
+        if (sub != 0) return;
+        r = np < 65536 ? encode_one<16>(x.id, x.lv, x.w4, lane, a, b, x.bin, x.level, x.n_bins,
+                                        x.n_levels, x.err)
+                       : encode_one<32>(x.id, x.lv, x.w4, lane, a, b, x.bin, x.level, x.n_bins,
+                                        x.n_levels, x.err);
+    } else {
+        const int64_t share = (np + x.per_block - 1) / x.per_block;
+        const int64_t p0 = min(a + (int64_t)sub * share, b), p1 = min(p0 + share, b);
+        U4 c[kFewPlanes];
+        clear<kFewPlanes>(c);
+        uint32_t n_ok = 0;
+        count_peaks<kFewPlanes>(c, n_ok, x.id, x.lv, x.w4, lane, p0, p1, x.bin, x.level, x.n_bins,
+                                x.n_levels, x.err);
+        for (uint32_t m = x.per_block; m > 1; m = (m + 1) / 2) {  // groups left
+            const uint32_t h = (m + 1) / 2;
+            if (sub >= h && sub < m) {
+#pragma unroll
+                for (int k = 0; k < kFewPlanes; ++k)
+                    s_c[k][t] = make_uint4(c[k].v[0], c[k].v[1], c[k].v[2], c[k].v[3]);
+                s_ok[t] = n_ok;
+            }
+            __syncthreads();
+            if (sub + h < m) {
+                const uint32_t o = t + h * x.w4;
+                U4 carry;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) carry.v[e] = 0u;
+#pragma unroll
+                for (int k = 0; k < kFewPlanes; ++k) {
+                    const uint4 y4 = s_c[k][o];
+                    const uint32_t y[4] = {y4.x, y4.y, y4.z, y4.w};
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const uint32_t v = c[k].v[e] ^ y[e];
+                        const uint32_t up = (c[k].v[e] & y[e]) | (v & carry.v[e]);
+                        c[k].v[e] = v ^ carry.v[e];
+                        carry.v[e] = up;
+                    }
+                }
+                n_ok += s_ok[o];
+            }
+            // the groups that wrote are done, those that read write elsewhere
+        }
+        if (sub != 0) return;
+        r = at_least<kFewPlanes>(c, (n_ok + 1u) / 2u);
+    }
+    x.out[(size_t)row * x.w4 + lane] = make_uint4(r.v[0], r.v[1], r.v[2], r.v[3]);
+}
+
 }  // namespace
 
 bool step_encode_takes(const homs_params& p)
@@ -494,6 +580,10 @@ hipError_t launch_encode(const homs_ctx* c, int64_t n, const int64_t* off, const
         go(encode_kernel<0, true>, near);
         go(encode_kernel<1, true>, far);
         go(encode_kernel<2, true>, far);
+        return hipGetLastError();
+    }
+    if (!step && n <= kFewSpectra) {
+        go(encode_few_kernel, 1);
         return hipGetLastError();
     }
     if (!step) go(encode_kernel<0, false>, near);
