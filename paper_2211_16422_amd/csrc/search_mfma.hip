@@ -400,12 +400,12 @@ __global__ __launch_bounds__(256) void fp4_row_consts_kernel(int64_t n, int64_t 
   if ((threadIdx.x & 63) == 0) rowk[r] = (float)s;
 }
 
-// Library rows per workgroup: the largest power of two up to kMfChunk (the
-// stream kernel: kStreamChunk), and at least 256, that makes `items` (tile,
-// chunk) items, of which a window's share holds candidates; fewer leave
-// compute units idle (16,003 queries, 600,002 rows, D = 8,192, 8 x 4 patches:
-// 8.19 ms with 16,384 items, 7.89 ms with 24,576, 7.91 ms with 49,152).
-constexpr int64_t kMfChunk = 2048, kStreamChunk = 8192;
+// Library rows per workgroup: the largest power of two up to `most`, and at
+// least 256, that makes `items` (tile, chunk) items, of which a window's share
+// holds candidates; fewer leave compute units idle (16,003 queries, 600,002
+// rows, D = 8,192, 8 x 4 patches: 8.19 ms with 16,384 items, 7.89 ms with
+// 24,576, 7.91 ms with 49,152).
+constexpr int64_t kMfChunk = 2048;
 constexpr int64_t kMfItems = 24576;
 constexpr int64_t kShortGrid = 1024;  // workgroups of a call of short windows (of kXcds rounds)
 int64_t chunk_rows(int64_t n_tiles, int64_t n, int64_t most, int64_t items)
@@ -413,6 +413,26 @@ int64_t chunk_rows(int64_t n_tiles, int64_t n, int64_t most, int64_t items)
     int64_t chunk = most;
     while (chunk > 256 && n_tiles * ((n + chunk - 1) / chunk) < items) chunk /= 2;
     return chunk;
+}
+
+// The stream kernel's rows per workgroup (a multiple of its 32-row blocks).
+// 512 of its workgroups run at once. Up to four tiles, whose windows cover most
+// of the library, they are made to fit that many one or two rounds: a
+// workgroup starts by filling LDS with its queries, and a round that is
+// nearly empty costs as much as a full one (400,000 rows, D = 8,192, against
+// powers of two: 64 queries 0.135 against 0.167 ms, 16 0.113 against 0.131,
+// 200 0.30 against 0.40). More tiles cover less of the library each, and
+// more, smaller items even that out (1,000 queries 0.557 ms with 1,024 rows,
+// 0.585 with 512; of 120,000 rows 0.223 with 512, 0.247 with 256 and 0.274
+// with 1,600).
+int64_t stream_chunk(int64_t n_tiles, int64_t n)
+{
+    if (n_tiles <= 4) {
+        const int64_t wgs = n_tiles == 1 ? 512 : 1024;
+        const int64_t rows = (n * n_tiles + wgs - 1) / wgs;
+        return std::min<int64_t>(1600, std::max<int64_t>(256, (rows + 31) / 32 * 32));
+    }
+    return n_tiles < 32 ? chunk_rows(n_tiles, n, 2048, 3072) : chunk_rows(n_tiles, n, 8192, 8192);
 }
 
 }  // namespace
@@ -462,8 +482,7 @@ hipError_t launch_search_mfma(const homs_ctx* c, int fmt, int64_t nq, const uint
     const int64_t n_tiles = (nq + tile - 1) / tile;
     const bool f4 = fmt == 2;
     if (tile != mfd::kQueries) {
-        const int64_t ch =
-            chunk_rows(n_tiles, c->lib.n, kStreamChunk, n_tiles < 16 ? 4096 : 8192);
+        const int64_t ch = stream_chunk(n_tiles, c->lib.n);
         const int64_t wgs = ((c->lib.n + ch - 1) / ch + kXcds - 1) / kXcds * kXcds * n_tiles;
         if (wgs > 0x7FFFFFFF) return hipErrorInvalidConfiguration;
         const size_t lds = (size_t)tile * (c->words * 4 + 16);
