@@ -22,6 +22,8 @@
 // of lane l holds row 8 (r / 4) + 4 (l / 32) + r % 4, column l % 32.
 #pragma once
 
+#include <type_traits>
+
 #include "internal.h"
 
 namespace homs {
@@ -96,11 +98,15 @@ struct Side {
             }
         }
     }
-    // stage s of the operand rows from row0 on into the LDS bytes at `lds`
-    __device__ __forceinline__ void issue(const Op& op, int row0, int s, uint32_t lds) const
+    // bytes from one stage of a row to the next
+    static constexpr uint32_t kStep = Op::kBits ? KS / 8 : kRow;
+    __device__ __forceinline__ static const char* start(const Op& op, int row0)
     {
-        const char* base = (const char*)(op.p + (size_t)row0 * op.ld) +
-                           (size_t)s * (Op::kBits ? KS / 8 : kRow);
+        return (const char*)(op.p + (size_t)row0 * op.ld);
+    }
+    // the stage at `base` (wave-uniform) into the LDS bytes at `lds`
+    __device__ __forceinline__ void issue(const char* base, uint32_t lds) const
+    {
 #pragma unroll
         for (int x = 0; x < kPerWave; ++x) {
             const uint32_t m0 = __builtin_amdgcn_readfirstlane(lds + dst[x]);
@@ -142,6 +148,33 @@ __device__ __forceinline__ bf16x8 expand8(uint32_t b, uint32_t sel, uint32_t one
 template <class Op, int R, int KS, int T>
 struct Reader {
     uint32_t words[T];
+    typename std::conditional<Op::kBits, uint32_t, bf16x8>::type all[KS / (Op::kBits ? 32 : 16)][T];
+    // a whole stage's operands (fetch), then those of one k step (take)
+    __device__ __forceinline__ void fetch(const uint8_t* lds, int row, int h)
+    {
+#pragma unroll
+        for (int x = 0; x < KS / (Op::kBits ? 32 : 16); ++x)
+#pragma unroll
+            for (int i = 0; i < T; ++i) {
+                if constexpr (Op::kBits) {
+                    all[x][i] = *(const uint32_t*)(lds + (x * R + row + i * 32) * 4) >> (8 * h);
+                } else {
+                    using S = Side<Op, R, KS, 1>;
+                    const int piece = (2 * x + h) ^ ((row / S::kRPB) % S::kP);
+                    all[x][i] = *(const bf16x8*)(lds + (row + i * 32) * S::kRow + piece * 16);
+                }
+            }
+    }
+    __device__ __forceinline__ void take(int kk, uint32_t sel, uint32_t one, bf16x8 (&out)[T])
+    {
+#pragma unroll
+        for (int i = 0; i < T; ++i) {
+            if constexpr (Op::kBits)
+                out[i] = expand8((kk & 1) ? all[kk >> 1][i] >> 16 : all[kk >> 1][i], sel, one);
+            else
+                out[i] = all[kk][i];
+        }
+    }
     // row: this lane's row of tile 0 (tiles are 32 rows apart)
     __device__ __forceinline__ void read(const uint8_t* lds, int row, int kk, int h, uint32_t sel,
                                          uint32_t one, bf16x8 (&out)[T])
@@ -213,12 +246,18 @@ __global__ __launch_bounds__(64 * WM * WN, (TR * TC > 4 ? 2 : 3)) void gemm_nt_k
     if constexpr (OpA::kBits || OpB::kBits) asm volatile("" : "+v"(sel), "+v"(one));
 
     const int nk = K / KS;
-    // stages past the end re-read the last one into a buffer that is not read
-    auto issue = [&](int s) {
-        const int from = min(s, nk - 1);
-        const uint32_t to = (uint32_t)(uintptr_t)&lds[s % kBufs][0];
-        sa.issue(A, m0, from, to);
-        sb.issue(B, n0, from, to + SideA::kBytes);
+    // The next stage into buffer `to`; stages past the end re-read the last one
+    // into a buffer that is not read.
+    const char *fa = SideA::start(A, m0), *fb = SideB::start(B, n0);
+    int ahead = nk - 1;  // stages after the one at fa, fb
+    auto issue = [&](int to) {
+        const uint32_t at = (uint32_t)(uintptr_t)&lds[to][0];
+        sa.issue(fa, at);
+        sb.issue(fb, at + SideA::kBytes);
+        const bool more = ahead > 0;
+        fa += more ? SideA::kStep : 0;
+        fb += more ? SideB::kStep : 0;
+        --ahead;
     };
     f32x16 acc[TR][TC];
 #pragma unroll
@@ -229,19 +268,37 @@ __global__ __launch_bounds__(64 * WM * WN, (TR * TC > 4 ? 2 : 3)) void gemm_nt_k
     const int rowA = wr * TR * 32 + (l & 31), rowB = wn * TC * 32 + (l & 31);
     Reader<OpA, kTM, KS, TR> ra;
     Reader<OpB, kTN, KS, TC> rb;
-    issue(0);
-    issue(1);
-    for (int s = 0; s < nk; ++s) {
-        __builtin_amdgcn_s_waitcnt(waitcnt_vm(kLoads));  // this wave's loads of stage s
-        __syncthreads();  // everyone's; stage s - 1 is fully read
-        issue(s + 2);
-        const uint8_t* pa = &lds[s % kBufs][0];
+    // A stage, in buffer `b` (a constant: the loop is unrolled over the buffers,
+    // so that no address is worked out per stage; with one wave per SIMD all
+    // that a stage does besides its matrix instructions adds to its time.
+    // N = 1,024, K = 8,192, bits: 300 rows 51.6 -> 44.9 us, 2,048 rows 61 ->
+    // 55 us with the reads below, 8,000 rows 154 -> 146 us in all; neither
+    // more buffers (6) nor k split over two sets of waves gave anything)
+    auto stage = [&](auto buf) {
+        constexpr int b = decltype(buf)::value;
+        __builtin_amdgcn_s_waitcnt(waitcnt_vm(kLoads));  // this wave's loads of the stage
+        __syncthreads();  // everyone's; the stage before is fully read
+        issue((b + 2) % kBufs);
+        const uint8_t* pa = &lds[b][0];
         const uint8_t* pb = pa + SideA::kBytes;
+        // few matrix instructions a stage: all its LDS reads first, so that
+        // their latency is waited for once
+        constexpr bool kFirst = TR * TC <= 2;
+        if constexpr (kFirst) {
+            ra.fetch(pa, rowA, h);
+            rb.fetch(pb, rowB, h);
+            __builtin_amdgcn_sched_barrier(0);
+        }
 #pragma unroll
         for (int kk = 0; kk < KS / 16; ++kk) {
             bf16x8 av[TR], bv[TC];
-            ra.read(pa, rowA, kk, h, sel, one, av);
-            rb.read(pb, rowB, kk, h, sel, one, bv);
+            if constexpr (kFirst) {
+                ra.take(kk, sel, one, av);
+                rb.take(kk, sel, one, bv);
+            } else {
+                ra.read(pa, rowA, kk, h, sel, one, av);
+                rb.read(pb, rowB, kk, h, sel, one, bv);
+            }
 #pragma unroll
             for (int i = 0; i < TR; ++i)
 #pragma unroll
@@ -249,6 +306,13 @@ __global__ __launch_bounds__(64 * WM * WN, (TR * TC > 4 ? 2 : 3)) void gemm_nt_k
                     acc[i][j] =
                         __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[i], bv[j], acc[i][j], 0, 0, 0);
         }
+    };
+    issue(0);
+    issue(1);
+    for (int s = 0; s < nk; s += 3) {
+        stage(std::integral_constant<int, 0>{});
+        if (s + 1 < nk) stage(std::integral_constant<int, 1>{});
+        if (s + 2 < nk) stage(std::integral_constant<int, 2>{});
     }
     __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));  // the re-reads land before the LDS is released
 
