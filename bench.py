@@ -55,8 +55,8 @@ HBM_PEAK_GBS = 8000.0
 # from rocprofv3 FETCH_SIZE and WRITE_SIZE runs scaled by a 1 GiB copy kernel
 # (profiles/search_kernels_large.md). Keyed by engine and the hash of the
 # kernel's sources: valid only while the source is the one measured.
-MEASURED_TRAFFIC = {("popcount", "8a0818167cd6a169"): 4.868e12,
-                    ("mfma_fp4", "6cc7539ab6528dd9"): 2.5363e+11}
+MEASURED_TRAFFIC = {("popcount", "5f06b7878b874d33"): 5.35e12,
+                    ("mfma_fp4", "f7d9e0e92fa14b13"): 1.5434e+11}
 
 ENGINE_SOURCES = {"popcount": ("search_popc.hip", "popcount_tile.h"),
                   "mfma_fp8": ("search_mfma.hip", "mfma_direct.h"),

@@ -47,8 +47,9 @@
 // 86k; with the expansions spread between the matrix instructions (about three
 // after each, which issue in its shadow), the operands read in a group's last
 // step and the barrier before that step it takes 79k to 81k: 164.8 -> 159.1 ms
-// for 100,000 queries with +-500 Da windows of a library of 1,000,000 rows,
-// 17.8 -> 15.3 ms in fp8 for 16,000 queries of 300,000 rows.
+// for 100,000 queries with +-500 Da windows of a library of 2,000,000 rows,
+// 17.8 -> 15.3 ms in fp8 for 16,000 queries of 600,000 rows, 66.1 -> 63.0 in
+// int8 for 40,000 of 1,000,000 (each then again with the work map's share).
 #pragma once
 
 #include <type_traits>
@@ -407,21 +408,26 @@ __device__ __forceinline__ void tile_rows_staged(uint32_t words, int64_t nq,
         v8i bnext[TQ];
 #pragma unroll
         for (int i = 0; i < TR; ++i) {
+          if constexpr (F == kFmtI8) {
+            // bytes 0-15 and 16-31 of each lane: two K = 32 halves of the same
+            // 64 components, split alike on both operands; one half of every
+            // query tile before the other, so that no instruction waits for
+            // the one right before it
 #pragma unroll
-          for (int j = 0; j < TQ; ++j) {
-            if constexpr (F == kFmtI8) {
-              // bytes 0-15 and 16-31 of each lane: two K = 32 halves of the
-              // same 64 components, split alike on both operands
-              const v4i a0 = {acur[0], acur[1], acur[2], acur[3]};
-              const v4i a1 = {acur[4], acur[5], acur[6], acur[7]};
-              const v4i b0 = {bcur[j][0], bcur[j][1], bcur[j][2], bcur[j][3]};
-              const v4i b1 = {bcur[j][4], bcur[j][5], bcur[j][6], bcur[j][7]};
-              acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a0, b0, acc[i][j], 0, 0, 0);
-              acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a1, b1, acc[i][j], 0, 0, 0);
-            } else {
+            for (int x = 0; x < 2; ++x) {
+              const v4i a4 = {acur[4 * x], acur[4 * x + 1], acur[4 * x + 2], acur[4 * x + 3]};
+#pragma unroll
+              for (int j = 0; j < TQ; ++j) {
+                const v4i b4 = {bcur[j][4 * x], bcur[j][4 * x + 1], bcur[j][4 * x + 2],
+                                bcur[j][4 * x + 3]};
+                acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a4, b4, acc[i][j], 0, 0, 0);
+              }
+            }
+          } else {
+#pragma unroll
+            for (int j = 0; j < TQ; ++j)
               acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(acur, bcur[j], acc[i][j],
                                                                            F, F, 0, 0, 0, 0);
-            }
           }
           acur = i + 1 < TR ? expand(ca[i + 1], st) : expand(ca[0], (st + 1) & 3);
           if (st == 3 && i + 1 < TR) read_a(i + 1, gn ? S : Sn, gn);
@@ -430,9 +436,10 @@ __device__ __forceinline__ void tile_rows_staged(uint32_t words, int64_t nq,
 #pragma unroll
         for (int j = 0; j < TQ; ++j) bcur[j] = bnext[j];
 #pragma unroll
-        for (int m = 0; m < TR * TQ; ++m) {
-          __builtin_amdgcn_sched_group_barrier(0x008, F == kFmtI8 ? 2 : 1, 0);  // matrix
-          __builtin_amdgcn_sched_group_barrier(0x002, F == kFmtF4 ? 3 : 12, 0);  // vector
+        for (int m = 0; m < (F == kFmtI8 ? 2 : 1) * TR * TQ; ++m) {
+          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // matrix
+          __builtin_amdgcn_sched_group_barrier(  // vector
+              0x002, F == kFmtF4 ? 3 : F == kFmtI8 ? 6 : 12, 0);
         }
         __builtin_amdgcn_sched_barrier(0);
       }

@@ -21,8 +21,8 @@
 // Data movement (mfma_direct.h): the packed bits of a block's rows and of the
 // tile's queries move into LDS in stages of 1,024 components by direct
 // global-to-LDS loads, one stage ahead of their use; each wave reads its
-// operand words from LDS and expands them in registers right before the
-// matrix instructions, with one shift and one bit insert per 4 components
+// operand words from LDS and expands them in registers between the matrix
+// instructions of the step before, with one shift and one bit insert per 4 components
 // (int8 +-64, fp8 +-1.0) or per 8 (fp4, asymmetric on the library side).
 //
 // Epilogue per block: distance = (Q - dot) / 2 (Q = D, or the fp4 form's
