@@ -749,7 +749,9 @@ __global__ __launch_bounds__(64 * kWaves) void preprocess_top_kernel(
     }
 }
 
-// one wave per spectrum, grid-stride
+// Four spectra a wave, so that their loads are in flight together (400,001
+// spectra of 46 entries: one a wave 95 us, so 77); grid-stride.
+constexpr int kCompact = 4;
 __global__ void compact_stage_kernel(int64_t n, PrepArgs pa, const int64_t* __restrict__ counts,
                                      const int64_t* __restrict__ out_off,
                                      const int32_t* __restrict__ st_bin,
@@ -759,11 +761,31 @@ __global__ void compact_stage_kernel(int64_t n, PrepArgs pa, const int64_t* __re
     const int l = threadIdx.x & 63;
     const int64_t waves = ((int64_t)gridDim.x * blockDim.x) >> 6;
     const int64_t cap = stage_cap(pa);
-    for (int64_t s = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6; s < n; s += waves) {
-        const int64_t c = counts[s], o = out_off[s];
-        for (int64_t j = l; j < c; j += 64) {
-            out_bin[o + j] = st_bin[s * cap + j];
-            out_level[o + j] = st_level[s * cap + j];
+    for (int64_t s = (((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6) * kCompact; s < n;
+         s += waves * kCompact) {
+        int64_t c[kCompact], o[kCompact], most = 0;
+#pragma unroll
+        for (int k = 0; k < kCompact; ++k) {
+            c[k] = s + k < n ? counts[s + k] : 0;
+            o[k] = s + k < n ? out_off[s + k] : 0;
+        }
+#pragma unroll
+        for (int k = 0; k < kCompact; ++k) most = max(most, c[k]);
+        for (int64_t j = l; j < most; j += 64) {
+            int32_t bin[kCompact];
+            uint8_t level[kCompact];
+#pragma unroll
+            for (int k = 0; k < kCompact; ++k)
+                if (j < c[k]) {
+                    bin[k] = st_bin[(s + k) * cap + j];
+                    level[k] = st_level[(s + k) * cap + j];
+                }
+#pragma unroll
+            for (int k = 0; k < kCompact; ++k)
+                if (j < c[k]) {
+                    out_bin[o[k] + j] = bin[k];
+                    out_level[o[k] + j] = level[k];
+                }
         }
     }
 }
@@ -831,7 +853,7 @@ hipError_t launch_preprocess_device(const homs_ctx* c, int64_t n, const int64_t*
         e = exclusive_scan<int64_t>(counts, out_off, n, temp, s);
         if (e != hipSuccess) return e;
         offsets_tail_kernel<<<1, 1, 0, s>>>(n, counts, out_off);
-        const int64_t cgrid64 = (n + 3) / 4;
+        const int64_t cgrid64 = (n + 4 * kCompact - 1) / (4 * kCompact);
         compact_stage_kernel<<<(uint32_t)(cgrid64 < 65536 ? cgrid64 : 65536), 256, 0, s>>>(
             n, pa, counts, out_off, st_bin, st_level, out_bin, out_level);
         return hipGetLastError();
