@@ -4,6 +4,7 @@
 #pragma once
 
 #include "internal.h"
+#include "popcount_lines.h"
 
 namespace homs {
 namespace popc {
@@ -77,10 +78,12 @@ __device__ __forceinline__ void popcount_tile_rows(
         // the next block's rows on their way into L2 (one word of each
         // 128-byte line), so that the scalar loads find them there
         uint32_t ahead = 0;
-        if (rb + kRefs < b)
-            for (uint32_t i = threadIdx.x; i < words; i += kTile)
-                ahead ^= lib_hv[(size_t)min(rb + kRefs + i / (words / 32), b - 1u) * words +
-                                i % (words / 32) * 32];
+        const uint32_t next = rb + kRefs;
+        if (next < b) {
+            const uint32_t lines = ahead_lines(min(b - next, (uint32_t)kRefs), words);
+            for (uint32_t i = threadIdx.x; i < lines; i += kTile)
+                ahead ^= lib_hv[ahead_word(next, words, i)];
+        }
 
         // rows past the chunk end re-read its last row; they are masked below
         Slice cur[kGroup];
