@@ -583,13 +583,14 @@ __device__ __forceinline__ void preprocess_wave(int write, int64_t s, int64_t p0
     imax = wave_max(imax);
     const double floor_i = pa.noise_frac * imax;
     // keys of the kept peaks, in the order of their intensities (none is
-    // negative: it would be below the floor); 0: not kept
+    // negative: it would be below the floor); 0: not kept, as a NaN is not: it
+    // is below no floor and its key lies above the maximum's
     auto key_of = [](double x) { return (uint64_t)__double_as_longlong(x == 0.0 ? 0.0 : x) + 1; };
     uint64_t key[P];
     int kept = 0;
 #pragma unroll
     for (int q = 0; q < P; ++q) {
-        const bool keep = ok[q] && !(v[q] < floor_i);
+        const bool keep = ok[q] && !(v[q] < floor_i) && v[q] == v[q];
         key[q] = keep ? key_of(v[q]) : 0ull;
         kept += __popcll(__ballot(keep));
     }
@@ -646,7 +647,8 @@ __device__ __forceinline__ void preprocess_wave(int write, int64_t s, int64_t p0
                 sel[q] = key[q] > t || (key[q] == t && rank[q] < top - above);
         }
     }
-    // one selected peak per lane, in input order
+    // one selected peak per lane, in input order; top_n bounds what is written
+    // whatever the intensities were (infinite ones have a floor of NaN)
     int k = 0;
 #pragma unroll
     for (int q = 0; q < P; ++q) {
@@ -655,11 +657,14 @@ __device__ __forceinline__ void preprocess_wave(int write, int64_t s, int64_t p0
             const int at = k + (int)__builtin_amdgcn_mbcnt_hi(
                                    (uint32_t)(w >> 32),
                                    __builtin_amdgcn_mbcnt_lo((uint32_t)w, 0u));
-            lds.mz[at] = m[q];
-            lds.val[at] = v[q];
+            if (at < top) {
+                lds.mz[at] = m[q];
+                lds.val[at] = v[q];
+            }
         }
         k += __popcll(w);
     }
+    k = min(k, top);
     __builtin_amdgcn_wave_barrier();
     // 4-5. square roots and bins
     const bool have_peak = l < k;
