@@ -51,6 +51,7 @@
 #include "bits.h"
 #include "codebook.h"
 #include "internal.h"
+#include "launch_pieces.h"
 
 namespace homs {
 namespace {
@@ -67,6 +68,7 @@ struct StepArgs {
     const uint16_t* first_off;
     uint32_t classes, slots, alpha, words;
     uint32_t chunk;  // slots per thread of the running XOR (odd: distinct banks)
+    int64_t first;   // spectrum of workgroup 0
     int64_t n, n_bins;
     uint32_t n_levels;
     const int64_t* off;
@@ -86,7 +88,7 @@ __global__ __launch_bounds__(NT) void encode_step_kernel(StepArgs a)
     __shared__ uint32_t s_wave[NW];
     __shared__ uint32_t s_row[kStepSpectra];  // output row, ~0: not this kernel's
     const int t = threadIdx.x, l = t & 63, w = __builtin_amdgcn_readfirstlane(t >> 6);
-    const int64_t s0 = (int64_t)blockIdx.x * kStepSpectra;
+    const int64_t s0 = a.first + (int64_t)blockIdx.x * kStepSpectra;
     for (uint32_t i = t; i < a.chunk * NT; i += NT) s_slot[i] = 0;
     __syncthreads();
 
@@ -557,12 +559,16 @@ hipError_t launch_encode(const homs_ctx* c, int64_t n, const int64_t* off, const
     if (step) {
         const StepEncode& st = c->step;
         const uint32_t chunk = ((st.slots + kStepThreads - 1) / kStepThreads) | 1u;
-        const StepArgs a{st.start, st.source,   st.first_off, st.classes, st.slots, st.alpha,
-                         c->words, chunk,       n,            c->n_bins,  c->p.n_levels,
-                         off,      bin,         level,        slot,       out,      c->d_err};
-        encode_step_kernel<kStepThreads>
-            <<<(uint32_t)((n + kStepSpectra - 1) / kStepSpectra), kStepThreads,
-               (size_t)chunk * kStepThreads * 4, s>>>(a);
+        in_pieces((n + kStepSpectra - 1) / kStepSpectra, kStepThreads,
+                  [&](int64_t first, int64_t count) {
+            const StepArgs a{st.start, st.source, st.first_off, st.classes,
+                             st.slots, st.alpha,  c->words,     chunk,
+                             first * kStepSpectra, n, c->n_bins, c->p.n_levels,
+                             off,      bin,       level,        slot,
+                             out,      c->d_err};
+            encode_step_kernel<kStepThreads>
+                <<<(uint32_t)count, kStepThreads, (size_t)chunk * kStepThreads * 4, s>>>(a);
+        });
     }
     const uint32_t w4 = c->words / 4;  // lanes per spectrum
     const uint32_t per_block = 256u / w4;

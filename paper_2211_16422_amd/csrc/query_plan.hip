@@ -19,6 +19,7 @@
 #include <algorithm>
 
 #include "internal.h"
+#include "launch_pieces.h"
 #include "window_search.h"
 
 namespace homs {
@@ -307,13 +308,13 @@ __device__ __forceinline__ uint64_t scan_window(uint32_t words, const uint32_t* 
 
 // one wave per kPerWave places of the order (of one tile)
 constexpr int kPerWave = 2;
-__global__ __launch_bounds__(kThreads) void finish_kernel(PlanArgs a,
+__global__ __launch_bounds__(kThreads) void finish_kernel(PlanArgs a, int64_t first,
     const uint32_t* __restrict__ q_hv, const uint32_t* __restrict__ lib_hv,
     const uint32_t* __restrict__ lib_orig, int64_t* __restrict__ out_idx,
     int32_t* __restrict__ out_dist)
 {
     const int64_t p0 =
-        ((int64_t)blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6)) * kPerWave;
+        ((first + blockIdx.x) * (kThreads / 64) + (threadIdx.x >> 6)) * kPerWave;
     const int l = threadIdx.x & 63;
     if (p0 >= a.nq) return;
     const int n = (int)min((int64_t)kPerWave, a.nq - p0);
@@ -413,8 +414,10 @@ hipError_t launch_finish(const homs_ctx* c, int64_t nq, const uint32_t* q_hv, in
     a.words = c->words;
     a.w = w;
     const int64_t per = kPerWave * (kThreads / 64);
-    finish_kernel<<<(uint32_t)((nq + per - 1) / per), kThreads, 0, s>>>(
-        a, q_hv, c->lib.hv, c->lib.orig, out_idx, out_dist);
+    in_pieces((nq + per - 1) / per, kThreads, [&](int64_t first, int64_t count) {
+        finish_kernel<<<(uint32_t)count, kThreads, 0, s>>>(a, first, q_hv, c->lib.hv, c->lib.orig,
+                                                           out_idx, out_dist);
+    });
     return hipGetLastError();
 }
 

@@ -33,6 +33,7 @@
 #include <algorithm>
 
 #include "internal.h"
+#include "launch_pieces.h"
 #include "mfma_direct.h"
 #include "window_search.h"
 
@@ -58,6 +59,8 @@ struct WorkMap {
   uint32_t patch_tiles, patch_chunks;         // items of a patch
   uint32_t chunk_patches, patches;            // patches along the library, in all
   uint32_t items;                             // kXcds rounds of whole patches
+  uint32_t first;                             // item of workgroup 0
+  bool listed;                                // the workgroups list their items
 };
 
 // wave layout of the one-shot kernels
@@ -89,13 +92,14 @@ __global__ __launch_bounds__(DirectLayout::kThreads, 1) void mfma_direct_kernel(
     *a = max(c0, tlo[*tile]);
     *b = min(c0 + map.chunk, thi[*tile]);
   };
-  // Item blockIdx.x, + gridDim.x, ...: one where the grid covers them all;
-  // otherwise each thread looks at one, and those with candidates are listed.
+  // One item per workgroup, or (listed) items blockIdx.x, + gridDim.x, ...: each
+  // thread looks at one, and those with candidates are listed.
   __shared__ uint32_t s_items[DirectLayout::kThreads], s_n;
-  for (uint64_t i0 = blockIdx.x; i0 < map.items;
-       i0 += (uint64_t)gridDim.x * DirectLayout::kThreads) {
+  const uint32_t mine = map.first + blockIdx.x;
+  const uint64_t end = map.listed ? map.items : (uint64_t)mine + 1;
+  for (uint64_t i0 = mine; i0 < end; i0 += (uint64_t)gridDim.x * DirectLayout::kThreads) {
     uint32_t n = 1;
-    if (gridDim.x < map.items) {
+    if (map.listed) {
       if (threadIdx.x == 0) s_n = 0;
       __syncthreads();
       const uint64_t item = i0 + (uint64_t)threadIdx.x * gridDim.x;
@@ -109,8 +113,7 @@ __global__ __launch_bounds__(DirectLayout::kThreads, 1) void mfma_direct_kernel(
     for (uint32_t k = 0; k < n; ++k) {
       uint32_t tile;
       int64_t a, b;
-      rows_of(gridDim.x < map.items ? __builtin_amdgcn_readfirstlane(s_items[k]) : blockIdx.x,
-              &tile, &a, &b);
+      rows_of(map.listed ? __builtin_amdgcn_readfirstlane(s_items[k]) : mine, &tile, &a, &b);
       if (a < b)
         mfd::tile_rows<F, DirectLayout>(words, nq, q_hv, qperm, lo, hi, tile, (uint32_t)a,
                                         (uint32_t)b, lib, orig, qoff, rowk, keys);
@@ -353,13 +356,14 @@ __global__ __launch_bounds__(kStreamThreads, 4) void mfma_stream_kernel(uint32_t
     const int64_t* __restrict__ tlo, const int64_t* __restrict__ thi,
     const uint32_t* __restrict__ lib, const uint32_t* __restrict__ orig,
     const int32_t* __restrict__ qoff, const float* __restrict__ rowk,
-    uint64_t* __restrict__ keys, uint32_t n_tiles, uint32_t chunk)
+    uint64_t* __restrict__ keys, uint32_t n_tiles, uint32_t round0, uint32_t chunk)
 {
   // XCD x (workgroup i runs on XCD i mod 8) takes chunks x, x + 8, ... and,
-  // chunk after chunk, every tile: a chunk's rows come into one L2 once
+  // chunk after chunk, every tile: a chunk's rows come into one L2 once (this
+  // launch: from round round0 of eight chunks on)
   const uint32_t wg = blockIdx.x, slot = wg / kXcds;
   const uint32_t tile = slot % n_tiles;
-  const int64_t c0 = (int64_t)(slot / n_tiles * kXcds + wg % kXcds) * chunk;
+  const int64_t c0 = ((int64_t)(round0 + slot / n_tiles) * kXcds + wg % kXcds) * chunk;
   const int64_t a = max(c0, tlo[tile]), b = min(c0 + chunk, thi[tile]);
   if (a >= b) return;
   if (words % 32 == 0)
@@ -505,14 +509,16 @@ hipError_t launch_search_mfma(const homs_ctx* c, int fmt, int64_t nq, const uint
     const bool f4 = fmt == 2;
     if (tile != mfd::kQueries) {
         const int64_t ch = stream_chunk(n_tiles, c->lib.n);
-        const int64_t wgs = ((c->lib.n + ch - 1) / ch + kXcds - 1) / kXcds * kXcds * n_tiles;
-        if (wgs > 0x7FFFFFFF) return hipErrorInvalidConfiguration;
+        const int64_t n_rounds = ((c->lib.n + ch - 1) / ch + kXcds - 1) / kXcds;
         const size_t lds = (size_t)tile * (c->words * 4 + 16);
-        auto go = [&](auto kern) {
-            kern<<<(uint32_t)wgs, kStreamThreads, lds, s>>>(
-                c->words, nq, q_hv, qperm, lo, hi, tile_lo, tile_hi, c->lib.hv, c->lib.orig,
-                f4 ? qoff : nullptr, f4 ? c->lib.rowk : nullptr, keys, (uint32_t)n_tiles,
-                (uint32_t)ch);
+        auto go = [&](auto kern) {  // a few tiles: a piece holds them all
+            in_pieces(n_tiles, n_rounds, kStreamThreads,
+                      [&](int64_t, int64_t, int64_t r, int64_t rounds) {
+                kern<<<(uint32_t)(n_tiles * rounds * kXcds), kStreamThreads, lds, s>>>(
+                    c->words, nq, q_hv, qperm, lo, hi, tile_lo, tile_hi, c->lib.hv, c->lib.orig,
+                    f4 ? qoff : nullptr, f4 ? c->lib.rowk : nullptr, keys, (uint32_t)n_tiles,
+                    (uint32_t)r, (uint32_t)ch);
+            });
         };
         if (tile == 32) {
             if (fmt == 0) go(mfma_stream_kernel<mfd::kFmtI8, 1>);
@@ -548,12 +554,15 @@ hipError_t launch_search_mfma(const homs_ctx* c, int fmt, int64_t nq, const uint
     // workgroups first list their items with candidates, one item a thread,
     // passes over them in 5 us; where most items hold work, one workgroup each
     // is the better balanced.
-    const uint32_t grid =
-        (uint32_t)(short_windows ? std::min<int64_t>(blocks, kShortGrid) : blocks);
+    m.listed = short_windows && blocks > kShortGrid;
     auto go = [&](auto kern) {
-        kern<<<grid, DirectLayout::kThreads, 0, s>>>(
-            c->words, nq, q_hv, qperm, lo, hi, tile_lo, tile_hi, c->lib.hv, c->lib.orig,
-            f4 ? qoff : nullptr, f4 ? c->lib.rowk : nullptr, keys, m);
+        in_pieces(m.listed ? kShortGrid : blocks, DirectLayout::kThreads,
+                  [&](int64_t first, int64_t count) {
+            m.first = (uint32_t)first;
+            kern<<<(uint32_t)count, DirectLayout::kThreads, 0, s>>>(
+                c->words, nq, q_hv, qperm, lo, hi, tile_lo, tile_hi, c->lib.hv, c->lib.orig,
+                f4 ? qoff : nullptr, f4 ? c->lib.rowk : nullptr, keys, m);
+        });
     };
     if (fmt == 0) go(mfma_direct_kernel<mfd::kFmtI8>);
     else if (fmt == 1) go(mfma_direct_kernel<mfd::kFmtF8>);

@@ -29,6 +29,7 @@
 // lexicographic minimum of (distance, library index) over rows inside its
 // own window [lo, hi); the lane's minimum is merged into the query's 64-bit
 // key (distance << 32 | library index) with one global atomicMin.
+#include "launch_pieces.h"
 #include "popcount_tile.h"
 
 namespace homs {
@@ -41,15 +42,16 @@ __global__ __launch_bounds__(kTile) void search_popcount_kernel(
     const uint32_t* __restrict__ qperm, const int64_t* __restrict__ lo,
     const int64_t* __restrict__ hi, const int64_t* __restrict__ tile_lo,
     const int64_t* __restrict__ tile_hi, const uint32_t* __restrict__ lib_hv,
-    const uint32_t* __restrict__ lib_orig, uint32_t n_tiles, int64_t chunk,
-    uint64_t* __restrict__ keys)
+    const uint32_t* __restrict__ lib_orig, uint32_t tile0, uint32_t n_tiles, uint32_t round0,
+    int64_t chunk, uint64_t* __restrict__ keys)
 {
     // workgroup i runs on XCD i mod 8, which takes chunks c = i mod 8 and,
     // chunk after chunk, every tile, so that a chunk's rows come into one L2
-    // once and serve all the tiles there
+    // once and serve all the tiles there; this launch: n_tiles tiles from tile0
+    // on, rounds of eight chunks from round0 on
     const uint32_t wg = blockIdx.x;
-    const uint32_t tile = (wg / 8) % n_tiles;
-    const int64_t c0 = (int64_t)((wg / 8) / n_tiles * 8 + wg % 8) * chunk;
+    const uint32_t tile = tile0 + (wg / 8) % n_tiles;
+    const int64_t c0 = ((int64_t)(round0 + (wg / 8) / n_tiles) * 8 + wg % 8) * chunk;
     const int64_t a = max(c0, tile_lo[tile]), b = min(c0 + chunk, tile_hi[tile]);
     if (a >= b) return;  // the chunk holds none of the tile's candidates
     popcount_tile_rows(words, nq, q_hv, qperm, lo, hi, tile, (uint32_t)a, (uint32_t)b, lib_hv,
@@ -114,11 +116,12 @@ hipError_t launch_search_popcount(const homs_ctx* c, int64_t nq, const uint32_t*
     int64_t chunk = kChunk;
     while (chunk > 64 && n_tiles * ((c->lib.n + chunk - 1) / chunk) < 16384) chunk /= 2;
     // whole rounds of 8 chunks, so every XCD's sequence is complete
-    const int64_t blocks = ((c->lib.n + chunk - 1) / chunk + 7) / 8 * 8 * n_tiles;
-    if (blocks > 0x7FFFFFFF) return hipErrorInvalidConfiguration;
-    search_popcount_kernel<<<(uint32_t)blocks, kTile, 0, s>>>(
-        c->words, nq, q_hv, qperm, lo, hi, tile_lo, tile_hi, c->lib.hv, c->lib.orig,
-        (uint32_t)n_tiles, chunk, keys);
+    const int64_t n_rounds = ((c->lib.n + chunk - 1) / chunk + 7) / 8;
+    in_pieces(n_tiles, n_rounds, kTile, [&](int64_t t, int64_t tiles, int64_t r, int64_t rounds) {
+        search_popcount_kernel<<<(uint32_t)(tiles * rounds * 8), kTile, 0, s>>>(
+            c->words, nq, q_hv, qperm, lo, hi, tile_lo, tile_hi, c->lib.hv, c->lib.orig,
+            (uint32_t)t, (uint32_t)tiles, (uint32_t)r, chunk, keys);
+    });
     return hipGetLastError();
 }
 
