@@ -710,7 +710,7 @@ homs_status run_search(homs_ctx* c, int64_t nq, const uint32_t* d_q_hv, const do
     hipEvent_t e1 = mark();
     if (engine == HOMS_ENGINE_POPCOUNT)
         HIP_TRY(c, homs::launch_search_popcount(c, nq, d_q_hv, w.qperm, w.lo, w.hi, w.tile_lo,
-                                                w.tile_hi, w.keys, s),
+                                                w.tile_hi, w.keys, win->kind, win->value, s),
                 "search kernel");
     else
         HIP_TRY(c, homs::launch_search_mfma(c, engine == HOMS_ENGINE_MFMA_I8   ? 0
@@ -718,10 +718,7 @@ homs_status run_search(homs_ctx* c, int64_t nq, const uint32_t* d_q_hv, const do
                                                                                : 2,
                                             nq, d_q_hv,
                                             w.qperm, w.lo, w.hi, w.tile_lo, w.tile_hi, w.qoff,
-                                            w.keys,
-                                            win->value <= (win->kind == HOMS_TOL_PPM ? 1000.0
-                                                                                     : 1.0),
-                                            s),
+                                            w.keys, win->kind, win->value, s),
                 "MFMA search kernel");
     hipEvent_t e2 = mark();
     HIP_TRY(c, homs::launch_finish(c, nq, d_q_hv, tile, w, d_out_idx, d_out_dist, s),

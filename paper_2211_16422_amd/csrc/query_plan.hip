@@ -19,7 +19,6 @@
 #include <algorithm>
 
 #include "internal.h"
-#include "launch_pieces.h"
 #include "window_search.h"
 
 namespace homs {
@@ -42,18 +41,39 @@ inline uint32_t blocks_for(int64_t n) { return (uint32_t)((n + kThreads - 1) / k
 // tiles: 100,000 queries over 2M rows, scan 1.76 ms at +-50 ppm against 2.25 ms
 // of tiles at 75 and 100 (windows of 1/36 of the union at the crossing);
 // fp8 there 6.0 / 10.8 ms at 200 / 400 ppm against 5.1 / 5.3; small tiles:
-// 2,000 queries, scan 0.43 / 1.55 ms at 200 / 1,000 ppm against 0.70; popcount:
-// 30,000 queries over 400,000 rows, scan 0.53 / 1.38 ms at 200 / 800 ppm
-// against 7.5.
-int64_t narrow_ratio(int32_t engine, int tile)
+// 2,000 queries, scan 0.43 / 1.55 ms at 200 / 1,000 ppm against 0.70. At D = 512
+// 9,000 queries over 2,000,000 rows cross at windows of 1/30 of the union (fp4:
+// 500 rows 0.16 ms by scan and 0.40 by tiles, 2,400 rows 0.72 and 0.52), at D =
+// 32,768 over 300,000 rows fp8 at more than 1/18 (500 rows 3.0 and 2.1 ms).
+// Popcount: windows of 1/3.8 of the union, 20,000 queries over 400,000 rows, 5.2
+// ms by scan and 6.5 by tiles; of 1/3, 100,000 over 200,000 rows at D = 32,768,
+// 19.6 by scan, 16.8 by tiles and 21.3 half by half (a call waits for both).
+int64_t narrow_ratio10(int32_t engine, int tile)  // in tenths
 {
-    if (engine == HOMS_ENGINE_POPCOUNT) return 3;
-    if (engine == HOMS_ENGINE_MFMA_F4) return tile == 256 ? 36 : 92;
-    return tile == 256 ? 18 : 48;
+    if (engine == HOMS_ENGINE_POPCOUNT) return 26;
+    if (engine == HOMS_ENGINE_MFMA_F4) return tile == 256 ? 360 : 920;
+    return tile == 256 ? 180 : 480;
 }
-// largest window of a narrow tile: few queries are few waves, which a tile
-// kernel's chunks would beat on long windows
-int64_t narrow_max(int64_t nq) { return std::min<int64_t>(2048, 64 + nq / 4); }
+// Largest window of a narrow tile: few queries are few waves, which a tile
+// kernel's chunks would beat on long windows (a wave scans its two queries of
+// 1,800 rows of D = 8,192 for 0.9 ms: over 2,000,000 rows 9,000 queries fp4 2.6 ms
+// and 16,000 fp8 4.9 where a few tiles were narrow, 1.8 and 3.9 by tiles). Many queries are bound by the
+// rows they fetch, 8 pairs a ns at D = 8,192 and 50 at D = 512, where a popcount
+// tile does ten times as many but waits for its chains of loads: a scan of so
+// many pairs takes as long as those (100,000 queries, 2,000,000 rows, D = 8,192:
+// windows of 500 rows 6.4 ms by scan and 11 by tiles, of 1,200 rows 15.7 and
+// 10.9; D = 512, 400,000 rows: of 150 rows 0.38 and 0.49, of 500 rows 1.02 and
+// 0.65).
+int64_t narrow_max(int64_t nq, int32_t engine, uint32_t words, int tile)
+{
+    const int64_t most = engine == HOMS_ENGINE_POPCOUNT || tile != 256 || words < 128 ? 2048
+                         : engine == HOMS_ENGINE_MFMA_F4                              ? 1024
+                                                                                      : 1536;
+    const int64_t rows = std::min<int64_t>(most, 64 + nq / 4);
+    if (engine != HOMS_ENGINE_POPCOUNT) return rows;
+    const int64_t pairs = std::min<int64_t>(60000000, 14000000 + 750000 * (int64_t)words);
+    return std::min(rows, std::max<int64_t>(1, pairs / nq));
+}
 
 struct PlanArgs {
     int64_t nq;
@@ -66,7 +86,7 @@ struct PlanArgs {
     const uint32_t* charge_first;
     int64_t nlib;
     int tile;
-    int64_t narrow_ratio, narrow_max;
+    int64_t narrow_ratio10, narrow_max;
     uint32_t words;
     const uint32_t* q_hv;  // rows of the fp4 query constants (NULL: not wanted)
     QueryPlan w;
@@ -120,7 +140,7 @@ __device__ __forceinline__ void tile_shape(const PlanArgs& a, int64_t t, At at)
     }
     if (l == 0) {
         // a narrow tile keeps no rows for the tile kernels
-        const bool narrow = big <= a.narrow_max && sum * a.narrow_ratio <= (mx - mn) * a.tile;
+        const bool narrow = big <= a.narrow_max && sum * a.narrow_ratio10 <= 10 * (mx - mn) * a.tile;
         a.w.tile_narrow[t] = narrow || mx == 0 ? 1 : 0;
         a.w.tile_lo[t] = narrow || mx == 0 ? 0 : mn;
         a.w.tile_hi[t] = narrow ? 0 : mx;
@@ -308,13 +328,14 @@ __device__ __forceinline__ uint64_t scan_window(uint32_t words, const uint32_t* 
 
 // one wave per kPerWave places of the order (of one tile)
 constexpr int kPerWave = 2;
-__global__ __launch_bounds__(kThreads) void finish_kernel(PlanArgs a, int64_t first,
+constexpr int64_t kPieceQueries = (int64_t)1 << 26;  // of one launch
+__global__ __launch_bounds__(kThreads) void finish_kernel(PlanArgs a,
     const uint32_t* __restrict__ q_hv, const uint32_t* __restrict__ lib_hv,
     const uint32_t* __restrict__ lib_orig, int64_t* __restrict__ out_idx,
     int32_t* __restrict__ out_dist)
 {
     const int64_t p0 =
-        ((first + blockIdx.x) * (kThreads / 64) + (threadIdx.x >> 6)) * kPerWave;
+        ((int64_t)blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6)) * kPerWave;
     const int l = threadIdx.x & 63;
     if (p0 >= a.nq) return;
     const int n = (int)min((int64_t)kPerWave, a.nq - p0);
@@ -385,7 +406,8 @@ hipError_t launch_query_plan(const homs_ctx* c, int64_t nq, const double* q_pmz,
                      kind,        value,
                      c->lib.pmz,  c->lib.charge_first,
                      c->lib.n,    tile,
-                     narrow_ratio(engine, tile), narrow_max(nq),
+                     narrow_ratio10(engine, tile),
+                     narrow_max(nq, engine, c->words, tile),
                      c->words,    q_hv,
                      w};
     if (nq <= kSmallPlan) {
@@ -409,15 +431,20 @@ hipError_t launch_finish(const homs_ctx* c, int64_t nq, const uint32_t* q_hv, in
 {
     if (nq <= 0) return hipSuccess;
     PlanArgs a{};
-    a.nq = nq;
     a.tile = tile;
     a.words = c->words;
     a.w = w;
     const int64_t per = kPerWave * (kThreads / 64);
-    in_pieces((nq + per - 1) / per, kThreads, [&](int64_t first, int64_t count) {
-        finish_kernel<<<(uint32_t)count, kThreads, 0, s>>>(a, first, q_hv, c->lib.hv, c->lib.orig,
-                                                           out_idx, out_dist);
-    });
+    // 32 threads a query: a grid holds less than 2^32. Each launch takes whole
+    // tiles of the order.
+    static_assert(kPieceQueries % 256 == 0 && kPieceQueries * 32 < (int64_t)1 << 32, "");
+    for (int64_t p = 0; p < nq; p += kPieceQueries) {
+        a.nq = std::min(kPieceQueries, nq - p);
+        a.w.qperm = w.qperm + p;
+        a.w.tile_narrow = w.tile_narrow + p / tile;
+        finish_kernel<<<(uint32_t)((a.nq + per - 1) / per), kThreads, 0, s>>>(
+            a, q_hv, c->lib.hv, c->lib.orig, out_idx, out_dist);
+    }
     return hipGetLastError();
 }
 

@@ -31,6 +31,7 @@
 // index); lanes l and l+32 hold the same query columns and are merged with a
 // shuffle before one atomicMin per query.
 #include <algorithm>
+#include <cmath>
 
 #include "internal.h"
 #include "launch_pieces.h"
@@ -431,11 +432,10 @@ __global__ __launch_bounds__(256) void fp4_row_consts_kernel(int64_t n, int64_t 
 // 24,576, 7.91 ms with 49,152).
 constexpr int64_t kMfChunk = 2048;
 constexpr int64_t kMfItems = 24576;
-constexpr int64_t kShortGrid = 1024;  // workgroups of a call of short windows (of kXcds rounds)
-int64_t chunk_rows(int64_t n_tiles, int64_t n, int64_t most, int64_t items)
+int64_t chunk_rows(int64_t n_tiles, int64_t n, int64_t most, int64_t items, int64_t least = 256)
 {
     int64_t chunk = most;
-    while (chunk > 256 && n_tiles * ((n + chunk - 1) / chunk) < items) chunk /= 2;
+    while (chunk > least && n_tiles * ((n + chunk - 1) / chunk) < items) chunk /= 2;
     return chunk;
 }
 
@@ -501,7 +501,7 @@ hipError_t launch_fp4_query_offsets(const homs_ctx* c, int64_t nq, const uint32_
 hipError_t launch_search_mfma(const homs_ctx* c, int fmt, int64_t nq, const uint32_t* q_hv,
                               const uint32_t* qperm, const int64_t* lo, const int64_t* hi,
                               const int64_t* tile_lo, const int64_t* tile_hi, const int32_t* qoff,
-                              uint64_t* keys, bool short_windows, hipStream_t s)
+                              uint64_t* keys, int32_t kind, double value, hipStream_t s)
 {
     if (nq <= 0 || c->lib.n <= 0) return hipSuccess;
     const int tile = search_mfma_tile(c, nq);
@@ -531,7 +531,10 @@ hipError_t launch_search_mfma(const homs_ctx* c, int fmt, int64_t nq, const uint
         }
         return hipGetLastError();
     }
-    const int64_t chunk = chunk_rows(n_tiles, c->lib.n, kMfChunk, kMfItems);
+    // a block of short rows is done before its queries are loaded (D = 512, 6,000
+    // queries of 400,000 rows, +-500 Da: 0.71 ms with 256-row chunks, 0.55 so)
+    const int64_t chunk = chunk_rows(n_tiles, c->lib.n, kMfChunk, kMfItems,
+                                     std::max<int64_t>(256, 16384 / c->words));
     const int64_t n_chunks = (c->lib.n + chunk - 1) / chunk;
     WorkMap m;
     m.n_tiles = (uint32_t)n_tiles;
@@ -541,6 +544,14 @@ hipError_t launch_search_mfma(const homs_ctx* c, int fmt, int64_t nq, const uint
     m.patch_chunks = n_tiles * n_chunks >= 32 * 64 ? 4 : 1;
     const int64_t tile_groups = (n_tiles + m.patch_tiles - 1) / m.patch_tiles;
     m.chunk_patches = (uint32_t)((n_chunks + m.patch_chunks - 1) / m.patch_chunks);
+    // Short windows lie along a diagonal: a group of tiles has its candidates in
+    // a patch or two, `step` patches further along the library than the group
+    // before, chunk_patches + step patches on in the sequence dealt to the XCDs.
+    // An even distance would leave half of the XCDs idle (100,000 queries of
+    // 400,000 rows, +-3.3 Da: 1.85 ms; 1.23 with one empty patch more a group).
+    const double step = ((double)n_chunks / m.patch_chunks) / ((double)n_tiles / m.patch_tiles);
+    const double turn = std::fmod(m.chunk_patches + step, 2.0);
+    if (step < 4.0 && (turn < 0.2 || turn > 1.8)) m.chunk_patches += 1;
     const int64_t patches = tile_groups * m.chunk_patches;
     // whole rounds of kXcds patches, so every XCD's sequence is complete
     const int64_t blocks =
@@ -553,10 +564,16 @@ hipError_t launch_search_mfma(const homs_ctx* c, int fmt, int64_t nq, const uint
     // 1,000,000 rows: 39,000 items, 84 us of nothing else). A fixed grid whose
     // workgroups first list their items with candidates, one item a thread,
     // passes over them in 5 us; where most items hold work, one workgroup each
-    // is the better balanced.
-    m.listed = short_windows && blocks > kShortGrid;
+    // is the better balanced. 100,000 queries of 2,000,000 rows, D = 8,192, 4,096
+    // and 65,536 workgroups and one for each of the 382,000 items: +-0.66 Da 2.4,
+    // 2.6 and 3.8 ms, +-2.75 Da 3.2, 3.5 and 4.6, +-16.5 Da 9.3, 9.5 and 10.2,
+    // +-500 Da 170.5, 157.8 and 155.0; D = 512, +-2.75 Da 0.78, 1.06 and 2.28.
+    const double da = kind == HOMS_TOL_PPM ? value / 1000.0 : value;  // near 1,000 Da
+    const int64_t most_groups =
+        da > 25.0 ? INT64_MAX : da > 1.0 ? 65536 : da > 0.1 && blocks > 65536 ? 4096 : 1024;
+    m.listed = blocks > most_groups;
     auto go = [&](auto kern) {
-        in_pieces(m.listed ? kShortGrid : blocks, DirectLayout::kThreads,
+        in_pieces(m.listed ? most_groups : blocks, DirectLayout::kThreads,
                   [&](int64_t first, int64_t count) {
             m.first = (uint32_t)first;
             kern<<<(uint32_t)count, DirectLayout::kThreads, 0, s>>>(

@@ -107,13 +107,20 @@ hipError_t launch_tile_bounds(int64_t nq, const uint32_t* qperm, const int64_t* 
 hipError_t launch_search_popcount(const homs_ctx* c, int64_t nq, const uint32_t* q_hv,
                                   const uint32_t* qperm, const int64_t* lo, const int64_t* hi,
                                   const int64_t* tile_lo, const int64_t* tile_hi,
-                                  uint64_t* keys, hipStream_t s)
+                                  uint64_t* keys, int32_t kind, double value, hipStream_t s)
 {
     const int64_t n_tiles = (nq + kTile - 1) / kTile;
     if (n_tiles <= 0 || c->lib.n <= 0) return hipSuccess;
-    // enough (tile, chunk) items to fill the chip evenly (2,001 queries,
-    // 200,000 rows, D = 8,192: 4.03 ms with 2,048-row chunks, 3.11 ms so)
-    int64_t chunk = kChunk;
+    // Enough (tile, chunk) items to fill the chip evenly (2,001 queries,
+    // 200,000 rows, D = 8,192: 4.03 ms with 2,048-row chunks, 3.11 ms so). A
+    // chunk is a chain of scalar loads (2,048 rows of D = 8,192: 7 ms), which
+    // windows of a few thousand rows wait for (9,000 queries +-2.75 Da of
+    // 2,000,000 rows 12.3 ms with chunks of 2,048 rows, 10.0 with 1,024). The
+    // shortest windows are scanned instead and leave hardly an item here, but
+    // each workgroup costs its dispatch (6,000 queries +-5 ppm of 2,000,000 rows,
+    // D = 2,048: 41 us in all, 63 with chunks of 512 rows).
+    const double da = kind == HOMS_TOL_PPM ? value / 1000.0 : value;  // near 1,000 Da
+    int64_t chunk = da <= 0.15 ? kChunk : kChunk / 2;
     while (chunk > 64 && n_tiles * ((c->lib.n + chunk - 1) / chunk) < 16384) chunk /= 2;
     // whole rounds of 8 chunks, so every XCD's sequence is complete
     const int64_t n_rounds = ((c->lib.n + chunk - 1) / chunk + 7) / 8;
