@@ -26,7 +26,6 @@
 //   window bounds -> bucket histogram (and key reset) -> scan -> scatter
 //   (counting sort by (wide/narrow, charge, precursor bucket)) -> tiles ->
 //   plan -> persistent search -> finalize.
-#include <algorithm>
 
 #include "mfma_direct.h"
 #include "popcount_tile.h"
@@ -132,7 +131,7 @@ __global__ void scatter_kernel(int64_t nq, const uint32_t* __restrict__ bucket,
     order[pos] = (uint32_t)q;
 }
 
-constexpr uint32_t kXcds = 8, kComputeUnits = 256;
+constexpr uint32_t kXcds = 8;
 constexpr int64_t kPatchTiles = 8;
 constexpr uint32_t kPatchChunks = 4;
 constexpr uint32_t kPatchItems = (uint32_t)kPatchTiles * kPatchChunks;
@@ -373,18 +372,17 @@ hipError_t launch_search_batched(const homs_ctx* c, const BatchedConfig& cfg, vo
                                                                       max_tiles, tile_lo, tile_hi);
     plan_kernel<<<1, 1024, 0, s>>>(nq, hist, cfg.chunk_rows, cfg.narrow_group, tile_lo, tile_hi,
                                    group, plan);
-    // a compute unit holds one workgroup of the matrix-core tiles: more would
-    // start when the queues are empty
-    const uint32_t mf_grid = std::min<uint32_t>(cfg.grid, kComputeUnits);
+    // (a compute unit holds one workgroup of the matrix-core tiles: those beyond
+    // 256 start when the queues are nearly empty)
     if (cfg.engine == HOMS_ENGINE_MFMA_F8) {
-        persistent_search_kernel<HOMS_ENGINE_MFMA_F8><<<mf_grid, mfd::kThreads, 0, s>>>(
+        persistent_search_kernel<HOMS_ENGINE_MFMA_F8><<<cfg.grid, mfd::kThreads, 0, s>>>(
             c->words, q_hv, order, lo, hi, nq, tile_lo, tile_hi, group,
             cfg.chunk_rows, cfg.narrow_group, plan, c->lib.hv, c->lib.orig, nullptr, nullptr,
             keys);
     } else if (cfg.engine == HOMS_ENGINE_MFMA_F4) {
         e = launch_fp4_query_offsets(c, nq, q_hv, qoff, s);
         if (e != hipSuccess) return e;
-        persistent_search_kernel<HOMS_ENGINE_MFMA_F4><<<mf_grid, mfd::kThreads, 0, s>>>(
+        persistent_search_kernel<HOMS_ENGINE_MFMA_F4><<<cfg.grid, mfd::kThreads, 0, s>>>(
             c->words, q_hv, order, lo, hi, nq, tile_lo, tile_hi, group,
             cfg.chunk_rows, cfg.narrow_group, plan, c->lib.hv, c->lib.orig, qoff, c->lib.rowk,
             keys);
