@@ -406,11 +406,13 @@ homs_status homs_device_errors(homs_ctx *ctx, uint32_t *flags, void *stream);
  * encode call records HIP events on its stream around its main kernels;
  * homs_profile_read waits for those events, returns the accumulated times
  * and launch counts since the last read, and resets them.
- *  search_ms/search_launches: the Hamming search kernel (any engine);
+ *  search_ms/search_launches: the Hamming search of a call (any engine), from
+ *           its search kernel to the result kernel, which scans the windows of
+ *           few rows and writes the answers (a cascade counts two);
  *  encode_ms/encode_launches: the encode kernels of homs_encode_queries and
  *           homs_encode_library (and the device preprocessing kernels);
- *  prep_ms: window, ordering and result kernels around the search kernel
- *           (and the query embedding of homs_search_learned), and the
+ *  prep_ms: window and ordering kernels before the search (and the query
+ *           embedding and the result kernel of homs_search_learned), and the
  *           library sort of homs_encode_library;
  *  score_ms/score_launches: the matrix-core scoring kernels of
  *           homs_search_learned (two scoring launches and the threshold
