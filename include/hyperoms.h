@@ -231,8 +231,13 @@ homs_status homs_encode_queries(homs_ctx *ctx, int64_t n, const int64_t *d_offse
  * contiguous range. Library index = position in the input (references and
  * decoys as the caller orders them); 0 <= n < 2^31.
  * In: CSR as for homs_encode_queries; d_pmz[n] float64; d_charge[n] int8.
- * Replaces any previous library. Synchronous (waits for `stream`); returns
- * HOMS_E_INVALID if a bin or level was out of range.
+ * Replaces any previous library, in its buffers where they fit the new one with
+ * at most a quarter to spare (else they are freed before new ones are
+ * allocated); n = 0 frees them. The sort's scratch is part of the context's
+ * workspace up to 64 MiB (some 3.3 million spectra) and beyond that freed before
+ * the call returns. Synchronous (waits for `stream` and for the device's other
+ * work, which may still read the previous library); returns HOMS_E_INVALID if a
+ * bin or level was out of range.
  */
 homs_status homs_encode_library(homs_ctx *ctx, int64_t n, const int64_t *d_offsets,
                                 const int32_t *d_bin, const uint8_t *d_level,

@@ -168,13 +168,13 @@ void free_library(homs::Library& L)
 
 inline size_t al(size_t x) { return (x + 255) & ~(size_t)255; }
 
-// A library of n rows in L's buffers where they fit it without keeping more
-// than four times its size, else in new ones (L's are freed first). The pads
-// of orig and rowk, which the matrix-core epilogue reads past the last row,
-// are left to the caller.
+// A library of n rows in L's buffers where they fit it with at most a quarter
+// to spare, else in new ones (L's are freed first). The pads of orig and rowk,
+// which the matrix-core epilogue reads past the last row, are left to the
+// caller.
 hipError_t place_library(homs::Library& L, int64_t n, uint32_t words)
 {
-    if (L.cap < n || L.cap / 4 > n) {
+    if (L.cap < n || L.cap - n > n / 4) {
         free_library(L);
         const size_t pad = (size_t)homs::search_mfma_row_pad();
         hipError_t e = homs::dev_malloc(&L.hv, (size_t)n * words * 4);
@@ -205,6 +205,10 @@ hipError_t place_library(homs::Library& L, int64_t n, uint32_t words)
 }
 
 void drop_graph(homs_ctx* c);
+
+// Library sorts that need no more scratch than this (some 3.3 million rows)
+// take it from the workspace and may grow it.
+constexpr size_t kKeptSortScratch = (size_t)64 << 20;
 
 // Grows the context's workspace to at least `bytes` (synchronising first).
 homs_status ensure_workspace(homs_ctx* c, size_t bytes, hipStream_t s)
@@ -585,12 +589,24 @@ homs_status homs_encode_library(homs_ctx* c, int64_t n, const int64_t* d_offsets
     }
     hipError_t e = place_library(L, n, c->words);
     if (e != hipSuccess) return hip_fail(c, e, "encode_library");
+    // the sort's scratch: the workspace, unless it would have to grow beyond what
+    // may stay with the context; then memory of its own, freed before returning
     const size_t tmp_bytes = homs::library_sort_temp_bytes(n);
-    if (homs_status st = ensure_workspace(c, tmp_bytes, s)) {
-        free_library(L);
-        return st;
+    void *tmp = nullptr, *own_tmp = nullptr;
+    if (tmp_bytes <= std::max(c->ws.bytes, kKeptSortScratch)) {
+        if (homs_status st = ensure_workspace(c, tmp_bytes, s)) {
+            free_library(L);
+            return st;
+        }
+        tmp = c->ws.ptr;
+    } else {
+        e = homs::dev_malloc(&own_tmp, tmp_bytes);
+        if (e != hipSuccess) {
+            free_library(L);
+            return hip_fail(c, e, "encode_library");
+        }
+        tmp = own_tmp;
     }
-    void* tmp = c->ws.ptr;
     const size_t orig_pad = (size_t)homs::search_mfma_row_pad();
     e = hipMemsetAsync(L.orig + n, 0, orig_pad * 4, s);
     if (e == hipSuccess) e = hipMemsetAsync(c->d_err, 0, 4, s);
@@ -607,6 +623,7 @@ homs_status homs_encode_library(homs_ctx* c, int64_t n, const int64_t* d_offsets
     uint32_t flags = 0;
     if (e == hipSuccess) e = hipMemcpyAsync(&flags, c->d_err, 4, hipMemcpyDeviceToHost, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
+    if (own_tmp) (void)hipFree(own_tmp);
     if (e != hipSuccess) {
         free_library(L);
         return hip_fail(c, e, "encode_library");
