@@ -95,7 +95,8 @@ __global__ __launch_bounds__(NT) void encode_step_kernel(StepArgs a)
     for (int s = w; s < kStepSpectra; s += NW) {
         const int64_t sp = s0 + s;
         const int64_t b0 = sp < a.n ? a.off[sp] : 0;
-        const int64_t np = sp < a.n ? a.off[sp + 1] - b0 : -1;
+        // (offsets that descend hold no peaks, here as on the general path)
+        const int64_t np = sp < a.n ? max(a.off[sp + 1] - b0, (int64_t)0) : -1;
         if (l == 0)
             s_row[s] = np < 0 || np > kStepPeaks ? ~0u : a.slot ? a.slot[sp] : (uint32_t)sp;
         if (np < 0 || np > kStepPeaks) continue;  // wave-uniform
