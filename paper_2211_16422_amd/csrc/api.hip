@@ -251,7 +251,8 @@ hipError_t scratch_address(int device, void** out)
     return hipSuccess;
 }
 
-// Per-call search scratch carved out of the workspace.
+// Per-call scratch of the shortlist search and the debug distances, carved out
+// of the workspace.
 struct SearchScratch {
     int64_t* lo;
     int64_t* hi;
@@ -260,23 +261,17 @@ struct SearchScratch {
     uint64_t* qk_b;
     uint32_t* qp_a;
     uint32_t* qp_b;
-    int64_t* tile_lo;
-    int64_t* tile_hi;
-    int32_t* qoff;  // per-query constants of the fp4 engine
     void* sort_tmp;
     size_t sort_bytes;
 };
 
-size_t search_scratch_bytes(int64_t nq, int tile)
+size_t search_scratch_bytes(int64_t nq)
 {
-    const int64_t nt = (nq + tile - 1) / tile;
-    return 2 * al(nq * 8) + al(nq * 8) + 2 * al(nq * 8) + 2 * al(nq * 4) + 2 * al(nt * 8) +
-           al(nq * 4) + homs::query_sort_temp_bytes(nq);
+    return 5 * al(nq * 8) + 2 * al(nq * 4) + homs::query_sort_temp_bytes(nq);
 }
 
-SearchScratch carve(void* base, int64_t nq, int tile)
+SearchScratch carve(void* base, int64_t nq)
 {
-    const int64_t nt = (nq + tile - 1) / tile;
     char* p = (char*)base;
     SearchScratch s{};
     s.lo = (int64_t*)p;
@@ -292,12 +287,6 @@ SearchScratch carve(void* base, int64_t nq, int tile)
     s.qp_a = (uint32_t*)p;
     p += al(nq * 4);
     s.qp_b = (uint32_t*)p;
-    p += al(nq * 4);
-    s.tile_lo = (int64_t*)p;
-    p += al(nt * 8);
-    s.tile_hi = (int64_t*)p;
-    p += al(nt * 8);
-    s.qoff = (int32_t*)p;
     p += al(nq * 4);
     s.sort_tmp = p;
     s.sort_bytes = homs::query_sort_temp_bytes(nq);
@@ -1131,9 +1120,8 @@ homs_status homs_debug_distances(homs_ctx* c, int64_t nq, const uint32_t* d_q_hv
         return fail(c, HOMS_E_INVALID, "NULL device pointer");
     DeviceGuard g(c->device);
     hipStream_t s = (hipStream_t)stream;
-    const int tile = homs::search_popcount_tile();
-    if (homs_status st = ensure_workspace(c, search_scratch_bytes(nq, tile), s)) return st;
-    SearchScratch w = carve(c->ws.ptr, nq, tile);
+    if (homs_status st = ensure_workspace(c, search_scratch_bytes(nq), s)) return st;
+    SearchScratch w = carve(c->ws.ptr, nq);
     HIP_TRY(c, homs::launch_window_bounds(c, nq, d_q_pmz, d_q_charge, win->kind, win->value,
                                           nullptr, nullptr, w.lo, w.hi, s),
             "window kernel");
@@ -1507,15 +1495,14 @@ homs_status homs_search_learned(homs_ctx* c, homs_model* m, int64_t nq, const ui
     if (!aligned16(d_q_hv)) return fail(c, HOMS_E_INVALID, "d_q_hv must be 16-byte aligned");
     DeviceGuard g(c->device);
     hipStream_t s = (hipStream_t)stream;
-    const int tile = homs::search_popcount_tile();
     homs::LearnedScratchPlan plan;
-    const size_t base = search_scratch_bytes(nq, tile);
+    const size_t base = search_scratch_bytes(nq);
     const size_t extra = al(homs::fallback_scratch_bytes(nq)) + al(nq * (size_t)m->E * 2) +
                          al(nq * (size_t)m->E) +
                          (d_out_shortlist ? 0 : al(nq * (size_t)k * 8)) +
                          homs::learned_scratch_bytes(nq, m->E, &plan);
     if (homs_status st = ensure_workspace(c, base + extra, s)) return st;
-    SearchScratch w = carve(c->ws.ptr, nq, tile);
+    SearchScratch w = carve(c->ws.ptr, nq);
     char* p = (char*)c->ws.ptr + base;
     void* fb_scratch = p;
     p += al(homs::fallback_scratch_bytes(nq));
