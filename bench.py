@@ -55,7 +55,7 @@ HBM_PEAK_GBS = 8000.0
 # from rocprofv3 FETCH_SIZE and WRITE_SIZE runs scaled by a 1 GiB copy kernel
 # (profiles/search_kernels_large.md). Keyed by engine and the hash of the
 # kernel's sources: valid only while the source is the one measured.
-MEASURED_TRAFFIC = {("popcount", "bcb30796aa58dbe6"): 4.847e12,
+MEASURED_TRAFFIC = {("popcount", "0c99122d4f5e8859"): 4.697e12,
                     ("mfma_fp4", "ade4964d0b2b576d"): 1.5306e+11}
 
 ENGINE_SOURCES = {"popcount": ("search_popc.hip", "popcount_tile.h"),

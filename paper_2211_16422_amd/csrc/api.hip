@@ -716,7 +716,7 @@ homs_status run_search(homs_ctx* c, int64_t nq, const uint32_t* d_q_hv, const do
     hipEvent_t e1 = mark();
     if (engine == HOMS_ENGINE_POPCOUNT)
         HIP_TRY(c, homs::launch_search_popcount(c, nq, d_q_hv, w.qperm, w.lo, w.hi, w.tile_lo,
-                                                w.tile_hi, w.keys, win->kind, win->value, s),
+                                                w.tile_hi, w.keys, s),
                 "search kernel");
     else
         HIP_TRY(c, homs::launch_search_mfma(c, engine == HOMS_ENGINE_MFMA_I8   ? 0

@@ -186,14 +186,14 @@ hipError_t launch_query_plan(const homs_ctx* c, int64_t nq, const double* q_pmz,
 hipError_t launch_finish(const homs_ctx* c, int64_t nq, const uint32_t* q_hv, int tile,
                          const QueryPlan& w, int64_t* out_idx, int32_t* out_dist, hipStream_t s);
 
-// search_popc.hip (kind, value: the tolerance of the windows)
+// search_popc.hip
 hipError_t launch_tile_bounds(int64_t nq, const uint32_t* qperm, const int64_t* lo,
                               const int64_t* hi, int tile, int64_t* tile_lo, int64_t* tile_hi,
                               hipStream_t s);
 hipError_t launch_search_popcount(const homs_ctx* c, int64_t nq, const uint32_t* q_hv,
                                   const uint32_t* qperm, const int64_t* lo, const int64_t* hi,
                                   const int64_t* tile_lo, const int64_t* tile_hi,
-                                  uint64_t* keys, int32_t kind, double value, hipStream_t s);
+                                  uint64_t* keys, hipStream_t s);
 int search_popcount_tile();
 
 // search_batched.hip
@@ -207,7 +207,8 @@ hipError_t launch_search_batched(const homs_ctx* c, const BatchedConfig& cfg, vo
 // search_mfma.hip (fmt 0: int8, 1: fp8 e4m3, 2: fp4 e2m1)
 int search_mfma_tile(const homs_ctx* c, int64_t nq);  // queries per tile, by the call's size
 int64_t search_mfma_row_pad();  // rows of padding the library's orig array needs
-// qoff: the fp4 form's per-query constants (unused by the others);
+// qoff: the fp4 form's per-query constants (unused by the others); kind, value:
+// the tolerance of the windows
 hipError_t launch_search_mfma(const homs_ctx* c, int fmt, int64_t nq, const uint32_t* q_hv,
                               const uint32_t* qperm, const int64_t* lo, const int64_t* hi,
                               const int64_t* tile_lo, const int64_t* tile_hi, const int32_t* qoff,

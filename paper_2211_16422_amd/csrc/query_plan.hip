@@ -36,7 +36,8 @@ inline uint32_t blocks_for(int64_t n) { return (uint32_t)((n + kThreads - 1) / k
 // searches of a few dozen candidates), finish_kernel scans each window on its
 // own instead, one wave per two queries, with XOR and population counts (the
 // same distances). A tile is narrow when ratio x the sum of its windows is at
-// most union x tile, and its largest window leaves the waves evenly loaded.
+// most union x tile, and its windows leave the waves evenly loaded and are not
+// too many pairs.
 // The ratios are where both ways took the same time (D = 8,192): fp4, 256-query
 // tiles: 100,000 queries over 2M rows, scan 1.76 ms at +-50 ppm against 2.25 ms
 // of tiles at 75 and 100 (windows of 1/36 of the union at the crossing);
@@ -45,34 +46,50 @@ inline uint32_t blocks_for(int64_t n) { return (uint32_t)((n + kThreads - 1) / k
 // 9,000 queries over 2,000,000 rows cross at windows of 1/30 of the union (fp4:
 // 500 rows 0.16 ms by scan and 0.40 by tiles, 2,400 rows 0.72 and 0.52), at D =
 // 32,768 over 300,000 rows fp8 at more than 1/18 (500 rows 3.0 and 2.1 ms).
-// Popcount: windows of 1/3.8 of the union, 20,000 queries over 400,000 rows, 5.2
-// ms by scan and 6.5 by tiles; of 1/3, 100,000 over 200,000 rows at D = 32,768,
-// 19.6 by scan, 16.8 by tiles and 21.3 half by half (a call waits for both).
+// Popcount crosses at the shares and numbers of pairs below; windows above 1/3 of
+// the union are never the faster by scan (D = 8,192, 100,000 queries over 400,000
+// rows: 400 rows 4.8 ms by scan and 2.8 by tiles).
 int64_t narrow_ratio10(int32_t engine, int tile)  // in tenths
 {
-    if (engine == HOMS_ENGINE_POPCOUNT) return 26;
+    if (engine == HOMS_ENGINE_POPCOUNT) return 30;
     if (engine == HOMS_ENGINE_MFMA_F4) return tile == 256 ? 360 : 920;
     return tile == 256 ? 180 : 480;
 }
 // Largest window of a narrow tile: few queries are few waves, which a tile
 // kernel's chunks would beat on long windows (a wave scans its two queries of
-// 1,800 rows of D = 8,192 for 0.9 ms: over 2,000,000 rows 9,000 queries fp4 2.6 ms
-// and 16,000 fp8 4.9 where a few tiles were narrow, 1.8 and 3.9 by tiles). Many queries are bound by the
-// rows they fetch, 8 pairs a ns at D = 8,192 and 50 at D = 512, where a popcount
-// tile does ten times as many but waits for its chains of loads: a scan of so
-// many pairs takes as long as those (100,000 queries, 2,000,000 rows, D = 8,192:
-// windows of 500 rows 6.4 ms by scan and 11 by tiles, of 1,200 rows 15.7 and
-// 10.9; D = 512, 400,000 rows: of 150 rows 0.38 and 0.49, of 500 rows 1.02 and
-// 0.65).
-int64_t narrow_max(int64_t nq, int32_t engine, uint32_t words, int tile)
+// 1,800 rows of D = 8,192 for 0.9 ms).
+int64_t narrow_max(int64_t nq) { return std::min<int64_t>(2048, 64 + nq / 4); }
+// Most pairs of a narrow tile per query. 256-query matrix-core tiles take over
+// from the scan at these (D = 8,192, 2,000,000 rows, windows of 1,800: 9,000
+// queries fp4 2.6 ms where a few tiles were narrow and 1.8 by tiles, 16,000 fp8
+// 4.9 and 3.9). It is the mean of a tile's windows that counts: by the largest,
+// half of the tiles of a call would be narrow near the limit, and the call waits
+// for both ways (6,000 queries fp4, windows of 909 rows: 0.95 ms by scan, 1.07 so).
+int64_t narrow_mean(int64_t nq, int32_t engine, uint32_t words, int tile)
 {
-    const int64_t most = engine == HOMS_ENGINE_POPCOUNT || tile != 256 || words < 128 ? 2048
-                         : engine == HOMS_ENGINE_MFMA_F4                              ? 1024
-                                                                                      : 1536;
-    const int64_t rows = std::min<int64_t>(most, 64 + nq / 4);
-    if (engine != HOMS_ENGINE_POPCOUNT) return rows;
-    const int64_t pairs = std::min<int64_t>(60000000, 14000000 + 750000 * (int64_t)words);
-    return std::min(rows, std::max<int64_t>(1, pairs / nq));
+    if (engine == HOMS_ENGINE_POPCOUNT) {
+        const int64_t pairs = words >= 128  ? 16000000
+                              : words >= 64 ? 30000000
+                              : words >= 32 ? 6000000
+                                            : 3000000;
+        return std::max<int64_t>(1, pairs / nq);
+    }
+    if (tile != 256 || words < 128) return 2048;
+    return engine == HOMS_ENGINE_MFMA_F4 ? 1024 : 1536;
+}
+// Popcount: a scan fetches the row of every pair, and the tiles of long rows take
+// a time of their own (chains of scalar loads), so that scans of some million pairs
+// are the faster. Beyond, the windows' share of the union decides. Milliseconds by
+// scan and by tiles, 20,000 queries over 400,000 rows, windows of 550 / 900 rows (1/10
+// and 1/6.7, 11M and 18M pairs): D = 512 0.26 / 0.40 and 0.23 / 0.23, 1,024 0.27 / 0.41
+// and 0.34 / 0.35, 2,048 0.36 / 0.55 and 0.58 / 0.60, 8,192 1.6 / 2.6 and 2.3 / 2.3;
+// 100,000 over 1,600,000, 300 / 550 rows (1/15 and 1/8.5, 30M and 55M): D = 512 0.65 /
+// 1.05 and 0.69 / 0.74, 1,024 0.66 / 1.07 and 1.07 / 1.11, 2,048 0.90 / 1.51 and 1.85 /
+// 1.94, 8,192 4.4 / 8.1 and 6.6 / 6.8.
+int64_t narrow_far10(int32_t engine, uint32_t words)
+{
+    if (engine != HOMS_ENGINE_POPCOUNT) return 0;
+    return words >= 512 ? 120 : words >= 256 ? 100 : words >= 32 ? 80 : 130;
 }
 
 struct PlanArgs {
@@ -86,7 +103,7 @@ struct PlanArgs {
     const uint32_t* charge_first;
     int64_t nlib;
     int tile;
-    int64_t narrow_ratio10, narrow_max;
+    int64_t narrow_ratio10, narrow_far10, narrow_max, narrow_mean;
     uint32_t words;
     const uint32_t* q_hv;  // rows of the fp4 query constants (NULL: not wanted)
     QueryPlan w;
@@ -140,7 +157,10 @@ __device__ __forceinline__ void tile_shape(const PlanArgs& a, int64_t t, At at)
     }
     if (l == 0) {
         // a narrow tile keeps no rows for the tile kernels
-        const bool narrow = big <= a.narrow_max && sum * a.narrow_ratio10 <= 10 * (mx - mn) * a.tile;
+        const int64_t pairs = 10 * (mx - mn) * a.tile;
+        const bool narrow = big <= a.narrow_max && sum * a.narrow_ratio10 <= pairs &&
+                            (sum <= a.narrow_mean * (end - t * (int64_t)a.tile) ||
+                             (a.narrow_far10 > 0 && sum * a.narrow_far10 <= pairs));
         a.w.tile_narrow[t] = narrow || mx == 0 ? 1 : 0;
         a.w.tile_lo[t] = narrow || mx == 0 ? 0 : mn;
         a.w.tile_hi[t] = narrow ? 0 : mx;
@@ -407,7 +427,9 @@ hipError_t launch_query_plan(const homs_ctx* c, int64_t nq, const double* q_pmz,
                      c->lib.pmz,  c->lib.charge_first,
                      c->lib.n,    tile,
                      narrow_ratio10(engine, tile),
-                     narrow_max(nq, engine, c->words, tile),
+                     narrow_far10(engine, c->words),
+                     narrow_max(nq),
+                     narrow_mean(nq, engine, c->words, tile),
                      c->words,    q_hv,
                      w};
     if (nq <= kSmallPlan) {

@@ -6,7 +6,8 @@
 // candidates, so a tile's candidates are one contiguous range of the sorted
 // library (the union of its queries' windows, a few rows wider than any one
 // window). The range is cut into chunks of up to kChunk rows; one workgroup of
-// four waves handles one (tile, chunk) pair, every lane owning one query.
+// four waves handles the (tile, chunk) pairs of a chunk and up to eight tiles,
+// one after the other, every lane owning one query of a tile.
 //
 // Inner loop. A wave walks its chunk kRefs rows at a time. For each block of
 // kWords words of the packed vectors the lane loads that slice of its own
@@ -19,8 +20,8 @@
 // scalar cache serves one fetch of a row to all 256 queries of the tile, and
 // a vector load of one word per line brings the next block's rows into L2
 // ahead of the scalar loads (with the XCD map of the launch, 2,001 queries
-// over 200,000 rows: 3.98 -> 3.11 ms, later 2.6 ms with the window-middle
-// query order).
+// over 200,000 rows: 3.98 -> 3.11 ms, later 2.7 ms with the window-middle
+// query order and 2.3 with an odd number of tiles per turn).
 // Scalar loads are software-pipelined two rows ahead: without it every row
 // waits out a full scalar-load round trip and the kernel sits near 70% of
 // the VALU issue rate; with it, above 90%.
@@ -42,20 +43,32 @@ __global__ __launch_bounds__(kTile) void search_popcount_kernel(
     const uint32_t* __restrict__ qperm, const int64_t* __restrict__ lo,
     const int64_t* __restrict__ hi, const int64_t* __restrict__ tile_lo,
     const int64_t* __restrict__ tile_hi, const uint32_t* __restrict__ lib_hv,
-    const uint32_t* __restrict__ lib_orig, uint32_t tile0, uint32_t n_tiles, uint32_t round0,
-    int64_t chunk, uint64_t* __restrict__ keys)
+    const uint32_t* __restrict__ lib_orig, uint32_t n_tiles, uint32_t slots, uint32_t per,
+    uint32_t slot0, uint32_t n_slots, uint32_t round0, uint32_t chunk,
+    uint64_t* __restrict__ keys)
 {
-    // workgroup i runs on XCD i mod 8, which takes chunks c = i mod 8 and,
-    // chunk after chunk, every tile, so that a chunk's rows come into one L2
-    // once and serve all the tiles there; this launch: n_tiles tiles from tile0
-    // on, rounds of eight chunks from round0 on
+    // workgroup i runs on XCD i mod 8, which takes chunks c = i mod 8 and, chunk
+    // after chunk, every slot of tiles, so that a chunk's rows come into one L2
+    // once and serve all the tiles there; this launch: n_slots slots from slot0
+    // on, rounds of eight chunks from round0 on. Slot x: tiles x, x + slots, ...
     const uint32_t wg = blockIdx.x;
-    const uint32_t tile = tile0 + (wg / 8) % n_tiles;
-    const int64_t c0 = ((int64_t)(round0 + (wg / 8) / n_tiles) * 8 + wg % 8) * chunk;
-    const int64_t a = max(c0, tile_lo[tile]), b = min(c0 + chunk, tile_hi[tile]);
-    if (a >= b) return;  // the chunk holds none of the tile's candidates
-    popcount_tile_rows(words, nq, q_hv, qperm, lo, hi, tile, (uint32_t)a, (uint32_t)b, lib_hv,
-                       lib_orig, keys);
+    const uint32_t slot = slot0 + (wg / 8) % n_slots;
+    const int64_t c0 = ((int64_t)(round0 + (wg / 8) / n_slots) * 8 + wg % 8) * chunk;
+    const uint32_t l = threadIdx.x & 63;
+    int64_t a = 0, b = 0;  // lane l: the slot's tile l
+    const uint32_t mine = slot + l * slots;
+    if (l < per && mine < n_tiles) {
+        const int64_t t_lo = tile_lo[mine], t_hi = tile_hi[mine];
+        a = max(c0, t_lo);
+        b = min(c0 + chunk, t_hi);
+    }
+    // the tiles with candidates in the chunk: short windows leave one or none
+    for (uint64_t todo = __ballot(a < b); todo; todo &= todo - 1) {
+        const int i = __builtin_ctzll(todo);
+        popcount_tile_rows(words, nq, q_hv, qperm, lo, hi, slot + (uint32_t)i * slots,
+                           (uint32_t)__builtin_amdgcn_readlane((int)a, i),
+                           (uint32_t)__builtin_amdgcn_readlane((int)b, i), lib_hv, lib_orig, keys);
+    }
 }
 
 __global__ void tile_bounds_kernel(int64_t nq, int64_t n_tiles, int tile,
@@ -107,27 +120,41 @@ hipError_t launch_tile_bounds(int64_t nq, const uint32_t* qperm, const int64_t* 
 hipError_t launch_search_popcount(const homs_ctx* c, int64_t nq, const uint32_t* q_hv,
                                   const uint32_t* qperm, const int64_t* lo, const int64_t* hi,
                                   const int64_t* tile_lo, const int64_t* tile_hi,
-                                  uint64_t* keys, int32_t kind, double value, hipStream_t s)
+                                  uint64_t* keys, hipStream_t s)
 {
     const int64_t n_tiles = (nq + kTile - 1) / kTile;
     if (n_tiles <= 0 || c->lib.n <= 0) return hipSuccess;
-    // Enough (tile, chunk) items to fill the chip evenly (2,001 queries,
-    // 200,000 rows, D = 8,192: 4.03 ms with 2,048-row chunks, 3.11 ms so). A
-    // chunk is a chain of scalar loads (2,048 rows of D = 8,192: 7 ms), which
-    // windows of a few thousand rows wait for (9,000 queries +-2.75 Da of
-    // 2,000,000 rows 12.3 ms with chunks of 2,048 rows, 10.0 with 1,024). The
-    // shortest windows are scanned instead and leave hardly an item here, but
-    // each workgroup costs its dispatch (6,000 queries +-5 ppm of 2,000,000 rows,
-    // D = 2,048: 41 us in all, 63 with chunks of 512 rows).
-    const double da = kind == HOMS_TOL_PPM ? value / 1000.0 : value;  // near 1,000 Da
-    int64_t chunk = da <= 0.15 ? kChunk : kChunk / 2;
+    // A chunk is a chain of scalar loads (256 rows of D = 8,192: 0.9 ms), and the
+    // items that hold candidates should be many more than the 1,800 workgroups
+    // the chip has room for (20,000 queries +-8.25 Da of 400,000 rows, D = 8,192:
+    // 5.1 ms with 1,024 rows, 2.7 with 256; 2,001 queries +-500 Da of 200,000 rows,
+    // D = 8,192: 4.0 ms with 2,048, 2.3 with 64). But each workgroup costs its
+    // dispatch, 0.3 ns and more, and where windows are short hardly an item holds
+    // candidates: a workgroup takes eight of a chunk's items, of tiles far from
+    // each other (100,000 queries of 2,000,000 rows, D = 1,024: +-0.1 Da 1.27 ms with
+    // a workgroup for each item, 0.51 so; +-1.65 Da 2.62 and 1.74, with chunks of 512
+    // rows 2.28 and 1.79). Where all of them do, the rows are at hand (20,000
+    // queries +-500 Da of 60,000 rows, D = 8,192: 5.65 and 5.59 ms).
+    int64_t chunk = 256, per = 8;
+    while (chunk < kChunk && n_tiles * (c->lib.n / chunk) > (per << 21)) chunk *= 2;
     while (chunk > 64 && n_tiles * ((c->lib.n + chunk - 1) / chunk) < 16384) chunk /= 2;
+    const int64_t n_chunks = (c->lib.n + chunk - 1) / chunk;
+    while (per > 1 && (n_tiles + per - 1) / per * n_chunks < 8192) per /= 2;
+    // An odd number of slots, if need be with an empty one: where one or two of a
+    // chunk's hold candidates, these come to the same few compute units of an XCD
+    // turn after turn if the turns are 2, 4, 8 or 16 long (4,000 queries, 16 tiles,
+    // +-1.65 Da of 2,000,000 rows, D = 8,192: 16.0 ms, 7.2 with an empty tile; 1,000
+    // queries +-5 Da 22.6 and 7.1). Few workgroups run all at once (1,000 queries of
+    // 60,000 rows, +-50 Da: 0.36 ms, 0.42 with an empty tile).
+    int64_t slots = (n_tiles + per - 1) / per;
+    if (slots * n_chunks >= 4096) slots |= 1;
     // whole rounds of 8 chunks, so every XCD's sequence is complete
-    const int64_t n_rounds = ((c->lib.n + chunk - 1) / chunk + 7) / 8;
-    in_pieces(n_tiles, n_rounds, kTile, [&](int64_t t, int64_t tiles, int64_t r, int64_t rounds) {
-        search_popcount_kernel<<<(uint32_t)(tiles * rounds * 8), kTile, 0, s>>>(
+    const int64_t n_rounds = (n_chunks + 7) / 8;
+    in_pieces(slots, n_rounds, kTile, [&](int64_t t, int64_t count, int64_t r, int64_t rounds) {
+        search_popcount_kernel<<<(uint32_t)(count * rounds * 8), kTile, 0, s>>>(
             c->words, nq, q_hv, qperm, lo, hi, tile_lo, tile_hi, c->lib.hv, c->lib.orig,
-            (uint32_t)t, (uint32_t)tiles, (uint32_t)r, chunk, keys);
+            (uint32_t)n_tiles, (uint32_t)slots, (uint32_t)per, (uint32_t)t, (uint32_t)count,
+            (uint32_t)r, (uint32_t)chunk, keys);
     });
     return hipGetLastError();
 }
