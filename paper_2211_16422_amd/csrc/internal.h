@@ -176,6 +176,7 @@ struct QueryPlan {
     int64_t* tile_hi;    // kernels)
     uint32_t* tile_narrow;  // windows left to launch_finish
     uint32_t* hist;
+    uint64_t* pairs;     // the call's candidate pairs, in parts
 };
 size_t query_plan_bytes(int64_t nq, int tile);
 QueryPlan query_plan_carve(void* base, int64_t nq, int tile);

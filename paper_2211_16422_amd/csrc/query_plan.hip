@@ -28,6 +28,7 @@ constexpr int kThreads = 256;
 constexpr int kBuckets = 16384;
 constexpr int kSmallThreads = 1024;
 constexpr int kSmallPlan = 512;   // queries of the one-workgroup plan
+constexpr int kSums = 64, kSumStride = 8;  // the call's pairs in parts, a cache line each
 
 inline uint32_t blocks_for(int64_t n) { return (uint32_t)((n + kThreads - 1) / kThreads); }
 
@@ -59,23 +60,22 @@ int64_t narrow_ratio10(int32_t engine, int tile)  // in tenths
 // kernel's chunks would beat on long windows (a wave scans its two queries of
 // 1,800 rows of D = 8,192 for 0.9 ms).
 int64_t narrow_max(int64_t nq) { return std::min<int64_t>(2048, 64 + nq / 4); }
-// Most pairs of a narrow tile per query. 256-query matrix-core tiles take over
-// from the scan at these (D = 8,192, 2,000,000 rows, windows of 1,800: 9,000
-// queries fp4 2.6 ms where a few tiles were narrow and 1.8 by tiles, 16,000 fp8
-// 4.9 and 3.9). It is the mean of a tile's windows that counts: by the largest,
-// half of the tiles of a call would be narrow near the limit, and the call waits
-// for both ways (6,000 queries fp4, windows of 909 rows: 0.95 ms by scan, 1.07 so).
-int64_t narrow_mean(int64_t nq, int32_t engine, uint32_t words, int tile)
+// Most pairs of a call whose tiles may be narrow. 256-query matrix-core tiles take
+// over from the scan at these (D = 8,192, 2,000,000 rows, windows of 1,800: 9,000
+// queries fp4 2.6 ms where a few tiles were narrow and 1.8 by tiles, 16,000 fp8 4.9
+// and 3.9). It is the call's windows that count: near a limit for each tile a part
+// of the tiles would be narrow, and the call waits for both ways (100,000 popcount
+// queries of 60,000 rows, windows of 55, D = 1,024: 154 us by scan, 170 by tiles, 232
+// so; 6,000 fp4, 909 of 2,000,000, D = 8,192: 0.95 ms by scan, 1.07 so).
+int64_t narrow_pairs(int64_t nq, int32_t engine, uint32_t words, int tile)
 {
-    if (engine == HOMS_ENGINE_POPCOUNT) {
-        const int64_t pairs = words >= 128  ? 16000000
-                              : words >= 64 ? 30000000
-                              : words >= 32 ? 6000000
-                                            : 3000000;
-        return std::max<int64_t>(1, pairs / nq);
-    }
-    if (tile != 256 || words < 128) return 2048;
-    return engine == HOMS_ENGINE_MFMA_F4 ? 1024 : 1536;
+    if (engine == HOMS_ENGINE_POPCOUNT)
+        return words >= 128  ? 20000000
+               : words >= 64 ? 30000000
+               : words >= 32 ? 8000000
+                             : 3000000;
+    if (tile != 256 || words < 128) return INT64_MAX;
+    return nq * (engine == HOMS_ENGINE_MFMA_F4 ? 1024 : 1536);
 }
 // Popcount: a scan fetches the row of every pair, and the tiles of long rows take
 // a time of their own (chains of scalar loads), so that scans of some million pairs
@@ -103,7 +103,7 @@ struct PlanArgs {
     const uint32_t* charge_first;
     int64_t nlib;
     int tile;
-    int64_t narrow_ratio10, narrow_far10, narrow_max, narrow_mean;
+    int64_t narrow_ratio10, narrow_far10, narrow_max, narrow_pairs;
     uint32_t words;
     const uint32_t* q_hv;  // rows of the fp4 query constants (NULL: not wanted)
     QueryPlan w;
@@ -131,9 +131,9 @@ __device__ __forceinline__ void query_offset(const PlanArgs& a, int64_t q)
 }
 
 // one wave: the union of tile t's windows and whether the tile is narrow;
-// at(i) is the query in place i of the order
+// at(i) is the query in place i of the order, total the call's pairs
 template <class At>
-__device__ __forceinline__ void tile_shape(const PlanArgs& a, int64_t t, At at)
+__device__ __forceinline__ void tile_shape(const PlanArgs& a, int64_t t, int64_t total, At at)
 {
     const int l = threadIdx.x & 63;
     int64_t mn = INT64_MAX, mx = 0, sum = 0, big = 0;
@@ -159,7 +159,7 @@ __device__ __forceinline__ void tile_shape(const PlanArgs& a, int64_t t, At at)
         // a narrow tile keeps no rows for the tile kernels
         const int64_t pairs = 10 * (mx - mn) * a.tile;
         const bool narrow = big <= a.narrow_max && sum * a.narrow_ratio10 <= pairs &&
-                            (sum <= a.narrow_mean * (end - t * (int64_t)a.tile) ||
+                            (total <= a.narrow_pairs ||
                              (a.narrow_far10 > 0 && sum * a.narrow_far10 <= pairs));
         a.w.tile_narrow[t] = narrow || mx == 0 ? 1 : 0;
         a.w.tile_lo[t] = narrow || mx == 0 ? 0 : mn;
@@ -207,16 +207,18 @@ __global__ __launch_bounds__(kSmallThreads) void plan_small_kernel(PlanArgs a)
     __syncthreads();
     for (int i = threadIdx.x; i < n; i += kSmallThreads) a.w.qperm[i] = (uint32_t)s_key[i];
     for (int t = threadIdx.x >> 6; t * a.tile < n; t += kSmallThreads / 64)
-        tile_shape(a, t, [&](int64_t i) { return (uint32_t)s_key[i]; });
+        // (few queries: windows of up to narrow_max rows are always few pairs)
+        tile_shape(a, t, 0, [&](int64_t i) { return (uint32_t)s_key[i]; });
 }
 
 // ---- any number of queries, five launches
 
-// buckets cleared, fp4 query constants (one wave per query)
+// buckets and sums cleared, fp4 query constants (one wave per query)
 __global__ __launch_bounds__(kThreads) void plan_init_kernel(PlanArgs a)
 {
     const int64_t t = (int64_t)blockIdx.x * kThreads + threadIdx.x;
     if (t <= kBuckets) a.w.hist[t] = 0;
+    if (t < kSums) a.w.pairs[t * kSumStride] = 0;
     if (a.q_hv && t / 64 < a.nq) query_offset(a, t / 64);
 }
 
@@ -233,6 +235,12 @@ __global__ __launch_bounds__(64) void plan_bounds_kernel(PlanArgs a)
         a.w.hi[q] = hi;
         a.w.keys[q] = ~0ull;
     }
+    int64_t pairs = hi - lo;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) pairs += (int64_t)__shfl_xor((long long)pairs, o);
+    if (threadIdx.x == 0)
+        atomicAdd((unsigned long long*)a.w.pairs + blockIdx.x % kSums * kSumStride,
+                  (unsigned long long)pairs);
     // queries without candidates: the wave's first takes places for all
     const uint64_t none = __ballot(in && hi <= lo);
     const int l = threadIdx.x & 63;
@@ -301,7 +309,11 @@ __global__ __launch_bounds__(kThreads) void plan_order_kernel(PlanArgs a)
 __global__ __launch_bounds__(kThreads) void plan_tiles_kernel(PlanArgs a)
 {
     const int64_t t = (int64_t)blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6);
-    if (t * a.tile < a.nq) tile_shape(a, t, [&](int64_t i) { return a.w.qperm[i]; });
+    if (t * a.tile >= a.nq) return;
+    int64_t total = (int64_t)a.w.pairs[(threadIdx.x & 63) * kSumStride];
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) total += (int64_t)__shfl_xor((long long)total, o);
+    tile_shape(a, t, total, [&](int64_t i) { return a.w.qperm[i]; });
 }
 
 // ---- after the search: the results of every query, and the narrow tiles
@@ -388,7 +400,8 @@ size_t al(size_t x) { return (x + 255) & ~(size_t)255; }
 size_t query_plan_bytes(int64_t nq, int tile)
 {
     const int64_t nt = (nq + tile - 1) / tile;
-    return 3 * al(nq * 8) + 4 * al(nq * 4) + 2 * al(nt * 8) + al(nt * 4) + al((kBuckets + 1) * 4);
+    return 3 * al(nq * 8) + 4 * al(nq * 4) + 2 * al(nt * 8) + al(nt * 4) + al((kBuckets + 1) * 4) +
+           al(kSums * kSumStride * 8);
 }
 
 QueryPlan query_plan_carve(void* base, int64_t nq, int tile)
@@ -412,6 +425,7 @@ QueryPlan query_plan_carve(void* base, int64_t nq, int tile)
     w.tile_hi = (int64_t*)take(nt * 8);
     w.tile_narrow = (uint32_t*)take(nt * 4);
     w.hist = (uint32_t*)take((kBuckets + 1) * 4);
+    w.pairs = (uint64_t*)take(kSums * kSumStride * 8);
     return w;
 }
 
@@ -429,7 +443,7 @@ hipError_t launch_query_plan(const homs_ctx* c, int64_t nq, const double* q_pmz,
                      narrow_ratio10(engine, tile),
                      narrow_far10(engine, c->words),
                      narrow_max(nq),
-                     narrow_mean(nq, engine, c->words, tile),
+                     narrow_pairs(nq, engine, c->words, tile),
                      c->words,    q_hv,
                      w};
     if (nq <= kSmallPlan) {

@@ -1,7 +1,7 @@
 """The popcount search's map of (tile, chunk) items: workgroups of one, two, four
 and eight tiles, slot counts that get an empty slot more (even) and that don't (odd,
 or few workgroups), chunks of 64 to 256 rows, and windows about where the plan turns
-from window scans to tiles, by the number of pairs (1M) and by the windows' share of
+from window scans to tiles, by the number of pairs (3M) and by the windows' share of
 the union (1/13). Against the fp4 engine on every query and the oracle on a sample."""
 import numpy as np
 import pytest
@@ -37,7 +37,7 @@ def _map(n, nq):
     (512, 140_000, 2_001, 500.0, 5, 2, 64),
     (1024, 270_001, 8_193, 0.5, 9, 4, 256),
     (512, 300_000, 15_001, 500.0, 9, 8, 256),
-    (512, 280_000, 15_400, 0.13, 9, 8, 256),    # 65 rows: 1M pairs
+    (512, 280_000, 15_400, 0.383, 9, 8, 256),   # 195 rows: 3M pairs
     (512, 700_000, 100_096, 0.23, 49, 8, 256),  # 149 rows of a union of 1,940
     (512, 700_000, 100_096, 3.0, 49, 8, 256),
     (512, 700_000, 98_304, 150.0, 49, 8, 256),
