@@ -22,8 +22,10 @@
 // operation is an IEEE operation (no contraction; the device double square
 // root is correctly rounded), so results equal the host path's.
 //
-// Two passes over the spectra: the first counts each spectrum's unique bins,
-// an exclusive scan gives the CSR offsets, the second recomputes and writes.
+// Usually one pass over the spectra, which writes each one's count and entries
+// to a staging area; an exclusive scan of the counts gives the CSR offsets and
+// the entries move to their place. Where the staging area would exceed 2 GB, two
+// passes: the first counts, the second recomputes and writes.
 
 #include <algorithm>
 #include <cmath>

@@ -564,13 +564,22 @@ hipError_t launch_search_mfma(const homs_ctx* c, int fmt, int64_t nq, const uint
     // 1,000,000 rows: 39,000 items, 84 us of nothing else). A fixed grid whose
     // workgroups first list their items with candidates, one item a thread,
     // passes over them in 5 us; where most items hold work, one workgroup each
-    // is the better balanced. 100,000 queries of 2,000,000 rows, D = 8,192, 4,096
-    // and 65,536 workgroups and one for each of the 382,000 items: +-0.66 Da 2.4,
-    // 2.6 and 3.8 ms, +-2.75 Da 3.2, 3.5 and 4.6, +-16.5 Da 9.3, 9.5 and 10.2,
-    // +-500 Da 170.5, 157.8 and 155.0; D = 512, +-2.75 Da 0.78, 1.06 and 2.28.
+    // is the better balanced. 100,000 queries of 2,000,000 rows with 1,024, 4,096 and
+    // 65,536 workgroups and one for each of the 382,000 items: D = 8,192, +-1.4 Da 3.0,
+    // 2.8, 3.0 and 4.2 ms, +-3 Da 3.7, 3.4, 3.8 and 4.7, +-500 Da 170.5 (4,096), 157.8
+    // and 155.0; D = 512, +-3 Da 0.86, 0.78, 1.07 and 2.24; 30,000 of 400,000 rows, D =
+    // 512, +-1.4 Da 0.17, 0.19, 0.34 and 0.34. Against one each, 4,096 take 0.96 and 0.87
+    // of the time at +-25 Da, D = 8,192 and 512, 0.97 and 0.88 at +-50, 1.00 and 0.91 at
+    // +-100 and 1.02 and 0.97 at +-500 (6,000 to 60,000 queries of 60,000 to 1,000,000
+    // rows).
+    // Few items are listed by 1,024 in 10 us less (6,000 queries +-0.5 Da of 400,000
+    // rows, D = 2,048: 78 us, 89 with 4,096), but many or long ones keep those waiting
+    // for each other (30,000 +-1.4 Da of 900,000 rows, D = 512: 364 us, 265 with 4,096;
+    // 4,000 +-5 Da of 200,000 rows, D = 32,768: 1.36 ms, 1.16).
     const double da = kind == HOMS_TOL_PPM ? value / 1000.0 : value;  // near 1,000 Da
-    const int64_t most_groups =
-        da > 25.0 ? INT64_MAX : da > 1.0 ? 65536 : da > 0.1 && blocks > 65536 ? 4096 : 1024;
+    const bool many = (da > 1.0 && (c->words >= 256 || blocks > 32768)) ||
+                      (da > 0.1 && blocks > 65536);
+    const int64_t most_groups = da > 50.0 ? INT64_MAX : many ? 4096 : 1024;
     m.listed = blocks > most_groups;
     auto go = [&](auto kern) {
         in_pieces(m.listed ? most_groups : blocks, DirectLayout::kThreads,

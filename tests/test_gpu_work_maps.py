@@ -1,8 +1,8 @@
 """One-shot search of thousands of queries against hundreds of thousands of rows,
 where a tile of 256 queries meets chunks of several 256-row blocks in patches of
 8 x 4: with a workgroup for each (tile, chunk) item (open windows), and with
-grids of 65,536 and of 4,096 workgroups that list theirs (windows of a few Da and
-below), with and without a patch more per group of tiles. All engines against
+grids of 4,096 and of 1,024 workgroups that list theirs (windows of up to 50 Da,
+many and few items), with and without a patch more per group of tiles. All engines against
 each other on every query, and against the oracle on a sample."""
 import numpy as np
 import pytest
@@ -37,16 +37,19 @@ def _matrix_map(dim, n, nq):
 @pytest.mark.parametrize("dim,n,nq,value,chunk,grid,padded", [
     (512, 300_000, 20_000, 500.0, 1024, None, False),
     (1536, 320_000, 20_000, 500.0, 1024, None, False),
-    (512, 400_000, 100_000, 3.0, 2048, 65536, True),
-    (512, 400_000, 100_000, 0.5, 2048, 4096, True),
-    (512, 900_000, 70_000, 2.0, 2048, 65536, False),
-    (1536, 120_000, 9_000, 20.0, 256, None, False),
+    (512, 400_000, 100_000, 3.0, 2048, 4096, True),
+    (512, 400_000, 100_000, 0.05, 2048, 1024, True),
+    (512, 900_000, 70_000, 2.0, 2048, 4096, False),
+    (1536, 120_000, 9_000, 20.0, 256, 1024, False),
+    (1536, 120_000, 9_000, 60.0, 256, None, False),
 ])
 def test_engines_agree(dim, n, nq, value, chunk, grid, padded):
     import torch
     import paper_2211_16422_amd.hyperoms as h
     got = _matrix_map(dim, n, nq)
-    assert got[:3] == (chunk, 4, padded) and (grid is None) == (value > 25 or got[3] <= 65536)
+    many = got[3] > (32768 if value > 1 else 65536) and value > 0.1
+    listed = None if value > 50 else 4096 if many else 1024
+    assert got[:3] == (chunk, 4, padded) and grid == listed and (not grid or got[3] > grid)
     g = torch.Generator(device="cuda")
     g.manual_seed(n + nq)
     with h.Context(h.Params(dim=dim)) as ctx:
